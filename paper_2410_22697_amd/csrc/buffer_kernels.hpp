@@ -71,7 +71,9 @@ __global__ void k_fill(T* __restrict__ p, int64_t n, T v) {
 // stands at the start of the step. Hits count this step for the lazy S_E
 // decay (hitcnt); misses take S_A += 1. Rows go to two gather lists, (row,
 // HBM slab row) and (row, halo id), compacted with wave ballots and one
-// atomic per wave. Also clears pos_of for the next step.
+// atomic per block. The launch's later blocks turn the step's sampled ids into
+// frontier positions: that work needs the finished frontier too, and is as
+// latency-bound, so it costs no launch and next to no time of its own.
 struct ClassifyArgs {
   const int32_t* nodes;
   StepSizes* sz;
@@ -82,7 +84,6 @@ struct ClassifyArgs {
   int32_t* hitcnt;
   float* S_A;                 // by halo rank, or by global id
   const int32_t* sa_idx;      // halo id -> its S_A index (rank, or global id)
-  int32_t* pos_of;
   uint8_t* mask;
   int2* hbm_list;
   int2* miss_list;
@@ -90,13 +91,24 @@ struct ClassifyArgs {
   const int32_t* slot_round;  // round that last refilled each slot
   const int32_t* landed;      // round whose refill row has landed in each slot
   int32_t pend_round;         // refill of this round may still be in flight (-1: none)
-  const int32_t* seeds;       // the step's seeds (their frontier positions are taken back if invalid)
+  const int32_t* seeds;       // the step's seeds (their marks are taken back if invalid)
   int32_t n0;
+  uint32_t* seen;             // frontier bitmap, which holds those marks
+  uint32_t cls_blocks;        // blocks [0, cls_blocks) classify, the rest relabel
+  int64_t n_bound;            // bound of the frontier's rows
+  const int32_t* pos_of;      // frontier position of an id
+  // the relabelling blocks: hop k + 1's are [rel_first[k], rel_first[k + 1])
+  // after the first cls_blocks; its sampled ids (at most e_bound[k] of them)
+  // are replaced by their positions
+  uint32_t rel_first[9];
+  int32_t* ids[8];
+  int64_t e_bound[8];
 };
 
 constexpr int kClsNT = 256;
 constexpr int kClsItems = 4;  // rows per thread: one block classifies 1024 rows per pass
 constexpr int kClsBlocks = 512;  // grid bound: the blocks stride over the frontier the step found
+constexpr int kRelBlocks = 1024;  // grid bound of the relabelling blocks of the same launch
 
 // Block-level aggregation: each block counts its rows per list, takes one
 // base per list with a single atomic, and places rows with wave ballots. The
@@ -116,30 +128,36 @@ __global__ __launch_bounds__(kClsNT) void k_classify(ClassifyArgs a) {
   constexpr int NW = kClsNT / MS_WAVE;
   __shared__ int32_t wc[NW][3];          // per-wave counts: hbm list, host list, pending hits
   __shared__ unsigned long long base[2];
-  if (a.sz->status) {
-    // invalid seeds: every kernel of the step has skipped, and the frontier
-    // positions the seed check marked are taken back, so the step leaves no trace
-    if (a.sz->status & 3)
-      for (int64_t i = (int64_t)blockIdx.x * kClsNT + threadIdx.x; i < a.n0; i += (int64_t)gridDim.x * kClsNT) {
-        const int32_t v = a.seeds[i];
-        if (v >= 0 && v < a.L) a.pos_of[v] = -1;
-      }
+  if (blockIdx.x >= a.cls_blocks) {
+    const uint32_t b = blockIdx.x - a.cls_blocks;
+    for (int k = 0; k < a.K; ++k)
+      if (b >= a.rel_first[k] && b < a.rel_first[k + 1])
+        relabel_hop<kClsNT>(a.ids[k], a.sz, k + 1, a.e_bound[k], a.pos_of, b - a.rel_first[k],
+                            a.rel_first[k + 1] - a.rel_first[k]);
     return;
   }
+  const int32_t status = a.sz->status;
   const int64_t n = a.sz->n[a.K];
   const int lane = lane_id(), wave = wave_id();
   const int64_t tile = (int64_t)kClsNT * kClsItems;
   const bool pending = a.pend_round >= 0;
-  for (int64_t b0 = (int64_t)blockIdx.x * tile; b0 < n; b0 += (int64_t)gridDim.x * tile) {
+  for (int64_t b0 = (int64_t)blockIdx.x * tile; b0 < a.n_bound; b0 += (int64_t)a.cls_blocks * tile) {
     int32_t v[kClsItems], slot[kClsItems];
 #pragma unroll
     for (int it = 0; it < kClsItems; ++it) {
-      // wave w of item it covers rows b0 + it*256 + w*64 + lane
+      // wave w of item it covers rows b0 + it*256 + w*64 + lane; the first
+      // pass's ids are loaded together with the frontier's size
       const int64_t i = b0 + (int64_t)it * kClsNT + threadIdx.x;
-      v[it] = a.nodes[i < n ? i : n - 1];
+      v[it] = a.nodes[min(i, a.n_bound - 1)];
     }
 #pragma unroll
     for (int it = 0; it < kClsItems; ++it) pin(v[it]);
+    if (status || b0 >= n) break;
+#pragma unroll
+    for (int it = 0; it < kClsItems; ++it) {
+      const int64_t i = b0 + (int64_t)it * kClsNT + threadIdx.x;
+      if (i >= n) v[it] = 0;  // (the array is not written past the frontier's end)
+    }
     {
       v4u w0[kClsItems], w1[kClsItems];
 #pragma unroll
@@ -199,7 +217,6 @@ __global__ __launch_bounds__(kClsNT) void k_classify(ClassifyArgs a) {
       src[it] = 0;
       wslot[it] = -1;
       if (i < n) {
-        a.pos_of[v[it]] = -1;
         const int32_t h = v[it] - a.L;
         if (v[it] < a.L) {
           cls[it] = 0;
@@ -265,6 +282,14 @@ __global__ __launch_bounds__(kClsNT) void k_classify(ClassifyArgs a) {
     }
     __syncthreads();
   }
+  // invalid seeds: every kernel of the step has skipped, and the marks that
+  // the seed check set (the only ones then) are taken back, so the step leaves
+  // no trace
+  if (status & 3)
+    for (int64_t i = (int64_t)blockIdx.x * kClsNT + threadIdx.x; i < a.n0; i += (int64_t)a.cls_blocks * kClsNT) {
+      const int32_t v = a.seeds[i];
+      if (v >= 0 && v < a.L) a.seen[v >> 5] = 0u;
+    }
 }
 
 // The step's completion, done by the step's last kernel on the side stream:
@@ -327,33 +352,53 @@ __device__ __forceinline__ void chunk_of(uint64_t cc, uint32_t cpr, uint64_t mag
   off = (cc - task * cpr) * sizeof(V);
 }
 
+// The list entries of a pass are loaded during the pass before it, the first
+// pass's together with the list's length: the list's array has room for
+// `bound` rows (>= 1), and an entry past the length is read and dropped.
 template <typename V, bool ONE, int U>
 __device__ __forceinline__ void gather_body(const int2* __restrict__ list, const int64_t* __restrict__ count,
-                                            const uint8_t* __restrict__ src, uint8_t* __restrict__ dst, int64_t rb,
-                                            uint32_t cpr, uint64_t magic) {
+                                            uint64_t bound, const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
+                                            int64_t rb, uint32_t cpr, uint64_t magic, uint64_t block, uint64_t blocks) {
+  const uint64_t stride = blocks * blockDim.x;
+  uint64_t c = block * blockDim.x + threadIdx.x;
   const uint64_t n = (uint64_t)*count;
+  int2 e[U];
+  auto entries = [&](uint64_t c0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      uint64_t task, off;
+      chunk_of<V, ONE>(c0 + u * stride, cpr, magic, task, off);
+      e[u] = list[task < bound ? task : bound - 1];
+    }
+  };
+  entries(c);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    pin(e[u].x);
+    pin(e[u].y);
+  }
   const uint64_t total = n * cpr;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < total; c += U * stride) {
-    uint64_t task[U], off[U];
+  for (; c < total; c += U * stride) {
+    uint64_t task, off[U], row[U];
+    int32_t to[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint64_t cc = c + u * stride;
-      chunk_of<V, ONE>(cc < total ? cc : c, cpr, magic, task[u], off[u]);
+      const bool in = cc < total;
+      chunk_of<V, ONE>(in ? cc : c, cpr, magic, task, off[u]);
+      row[u] = (uint64_t)(uint32_t)(in ? e[u].y : e[0].y);
+      to[u] = e[u].x;
     }
-    int2 e[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) e[u] = list[task[u]];
     V v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      v[u] = *reinterpret_cast<const V*>(src + (uint64_t)(uint32_t)e[u].y * rb + off[u]);
+    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const V*>(src + row[u] * rb + off[u]);
+    if (c + U * stride < total) entries(c + U * stride);
 #pragma unroll
     for (int u = 0; u < U; ++u) asm volatile("" : "+v"(v[u]));
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (c + u * stride < total)
-        __builtin_nontemporal_store(v[u], reinterpret_cast<V*>(dst + (uint64_t)(uint32_t)e[u].x * rb + off[u]));
+        __builtin_nontemporal_store(v[u], reinterpret_cast<V*>(dst + (uint64_t)(uint32_t)to[u] * rb + off[u]));
   }
 }
 
@@ -363,10 +408,11 @@ __device__ __forceinline__ void gather_body(const int2* __restrict__ list, const
 // per launch against 32.0 on the papers-sized share).
 template <typename V, bool ONE>
 __global__ __launch_bounds__(256) void k_gather_hbm(const int2* __restrict__ list, const int64_t* __restrict__ count,
-                                                    const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
-                                                    int64_t rb, uint32_t cpr, uint64_t magic) {
+                                                    uint64_t bound, const uint8_t* __restrict__ src,
+                                                    uint8_t* __restrict__ dst, int64_t rb, uint32_t cpr,
+                                                    uint64_t magic) {
   __builtin_amdgcn_s_setprio(3);
-  gather_body<V, ONE, 4>(list, count, src, dst, rb, cpr, magic);
+  gather_body<V, ONE, 4>(list, count, bound, src, dst, rb, cpr, magic, blockIdx.x, gridDim.x);
 }
 // misses: pinned host store (over the host link) -> output rows. The list
 // also holds the hits on slots whose refill had not landed when the step was
@@ -1226,12 +1272,18 @@ __global__ void k_swap(const int32_t* __restrict__ E, const int32_t* __restrict_
 }  // namespace ms
 
 namespace ms {
-// G_p sanity: non-decreasing offsets, column ids inside [0, R).
+// G_p sanity: non-decreasing offsets, column ids inside [0, R). Also counts the
+// rows longer than big_min.
 __global__ void k_validate_csr(const int64_t* __restrict__ indptr, int64_t R, const int32_t* __restrict__ indices,
-                               int64_t nnz, int32_t* __restrict__ bad) {
+                               int64_t nnz, int64_t big_min, int32_t* __restrict__ bad, int64_t* __restrict__ n_long) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < R; i += stride)
-    if (indptr[i + 1] < indptr[i]) atomicOr(bad, 1);
+  int64_t longer = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < R; i += stride) {
+    const int64_t d = indptr[i + 1] - indptr[i];
+    if (d < 0) atomicOr(bad, 1);
+    longer += d > big_min;
+  }
+  if (longer) atomicAdd((unsigned long long*)n_long, (unsigned long long)longer);
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz; e += stride) {
     const int32_t v = indices[e];
     if (v < 0 || v >= R) atomicOr(bad, 2);

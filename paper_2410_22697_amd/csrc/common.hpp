@@ -28,9 +28,30 @@ __device__ __forceinline__ int64_t wave_uniform(int64_t x) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave.
+// x of the lane that a data-parallel-primitive control names, 0 in the lanes
+// that it leaves out (and in rows outside the row mask).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave. 32-bit sums go through DPP
+// moves (shifts within a row of 16 lanes, then the last lane of each row
+// broadcast to the rows after it), which a following add takes in a few
+// cycles; a shuffle goes through the LDS unit, and a chain of six cost ~0.25 us
+// in the latency-bound kernels that scan.
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T x) {
+  if constexpr (sizeof(T) == 4) {
+    uint32_t v = (uint32_t)x;
+    v += dpp<0x111, 0xF>(v);  // row_shr:1
+    v += dpp<0x112, 0xF>(v);  // row_shr:2
+    v += dpp<0x114, 0xF>(v);  // row_shr:4
+    v += dpp<0x118, 0xF>(v);  // row_shr:8
+    v += dpp<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return (T)v;
+  }
   const int lane = lane_id();
 #pragma unroll
   for (int o = 1; o < MS_WAVE; o <<= 1) {
@@ -49,8 +70,10 @@ __device__ __forceinline__ void pin(T& x) {
   asm volatile("" : "+v"(x));
 }
 
+// Sum over the wave's lanes, the same in every lane.
 template <typename T>
 __device__ __forceinline__ T wave_sum(T x) {
+  if constexpr (sizeof(T) == 4) return (T)__builtin_amdgcn_readlane((int)wave_inclusive_scan(x), MS_WAVE - 1);
 #pragma unroll
   for (int o = MS_WAVE / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, MS_WAVE);
   return x;

@@ -125,7 +125,8 @@ struct massive_ctx {
   double mu32[MASSIVE_MAX_HOPS] = {};    // sampler threshold targets, x 2^32
   int32_t* d_big = nullptr;             // row list of the current hop (long rows first)
   int64_t big_min = ms::kBigRow;        // rows longer than this are sampled by a whole block
-  int64_t big_blocks = ms::kBigBlocks;  // blocks that walk the list of such rows
+  int64_t big_blocks = ms::kBigBlocks;  // blocks that walk the list of such rows (at most)
+  int64_t long_rows = 0;                // rows of G_p that long
   int32_t tau_iters = ms::kTauIters;    // threshold passes per row (0 makes every long row fail)
   // streams and events
   hipStream_t s_main = nullptr, s_miss = nullptr, s_copy = nullptr;
@@ -217,7 +218,10 @@ struct massive_ctx {
   int64_t* d_deg = nullptr;          // [H] degrees, during init only
   uint64_t* d_tab = nullptr;
   int32_t* d_pos_of = nullptr;
-  uint32_t* d_bits = nullptr;
+  uint32_t* d_bits = nullptr;         // sampled-id bitmap of the current hop
+  uint32_t* d_seen = nullptr;         // frontier bitmap of the current step (in the same allocation)
+  ms::v4r* d_rec = nullptr;           // [L+H] row records of the current frontier
+  uint64_t* d_tile_flags = nullptr;   // tile states of the frontier scans (in the same allocation)
   ms::StepSizes* d_sz = nullptr;      // [kSlots], by step slot
   ms::StepSizes* h_sz = nullptr;      // [kSlots] pinned mailboxes
   int32_t* h_bad = nullptr;           // [kSlots] pinned: eviction-round consistency flag
@@ -231,7 +235,7 @@ struct massive_ctx {
   int32_t* d_landed = nullptr;        // [cap] round whose refill row has landed
   int32_t* d_part = nullptr;
   int32_t* d_part2 = nullptr;
-  uint64_t* d_scan_flags = nullptr;  // the sampler's single-pass scans (rounds use d_part, d_part2)
+  uint64_t* d_scan_flags = nullptr;  // the seed rows' single-pass scan (rounds use d_part, d_part2)
   int64_t scan_tiles = 0;
   uint32_t scan_epoch = 0;           // of the last scan launched
   // gather lists by step slot (written by classify, read by the side stream)
@@ -416,16 +420,17 @@ void launch_gather(massive_ctx* c, int group, GatherKind kind, hipStream_t s, co
     vec = 8;
   const uint32_t cpr = (uint32_t)(rb / vec);
   const uint64_t magic = cpr > 1 ? (~0ull) / cpr + 1 : 0;
-  const int64_t chunks = std::max<int64_t>(max_rows, 1) * cpr;
+  const uint64_t bound = (uint64_t)std::max<int64_t>(max_rows, 1);
+  const int64_t chunks = (int64_t)bound * cpr;
   const unsigned grid = grid_for(chunks / 4, 256, max_blocks);
 #define MS_ONE(V, ONE)                                                                                         \
   do {                                                                                                         \
     if (kind == kHbm) {                                                                                        \
       if (timed)                                                                                               \
-        hipExtLaunchKernelGGL(ms::k_gather_hbm<V, ONE>, dim3(grid), dim3(256), 0, s, ea, eb, 0, list, count, src, \
+        hipExtLaunchKernelGGL(ms::k_gather_hbm<V, ONE>, dim3(grid), dim3(256), 0, s, ea, eb, 0, list, count, bound, src, \
                               dst, rb, cpr, magic);                                                            \
       else                                                                                                     \
-        ms::k_gather_hbm<V, ONE><<<grid, 256, 0, s>>>(list, count, src, dst, rb, cpr, magic);                  \
+        ms::k_gather_hbm<V, ONE><<<grid, 256, 0, s>>>(list, count, bound, src, dst, rb, cpr, magic);                  \
     } else {                                                                                                   \
       if (timed)                                                                                               \
         hipExtLaunchKernelGGL(ms::k_gather_miss<V, ONE>, dim3(grid), dim3(256), 0, s, ea, eb, 0, list, wslot,  \
@@ -768,7 +773,7 @@ void free_ctx(massive_ctx* c) {
   delete c->pool;
   (void)hipDeviceSynchronize();
   void* dev[] = {c->d_indptr, c->d_indices, c->d_slab, c->d_slot_id, c->d_S_E, c->d_hitcnt, c->d_S_A,
-                 c->d_rank_of, c->d_h_of_rank, c->d_tab, c->d_pos_of, c->d_bits, c->d_sz, c->d_rs,
+                 c->d_rank_of, c->d_h_of_rank, c->d_tab, c->d_pos_of, c->d_bits, c->d_rec, c->d_sz, c->d_rs,
                  c->d_part, c->d_part2, c->d_scan_flags, c->d_dummy, c->d_E, c->d_R,
                  c->d_fill, c->d_ctr, c->d_slot_round, c->d_landed,
                  c->d_k0, c->d_k1, c->d_v0, c->d_v1, c->d_hist, c->d_ghist, c->d_big,
@@ -810,6 +815,23 @@ void free_ctx(massive_ctx* c) {
   if (c->s_copy) (void)hipStreamDestroy(c->s_copy);
   if (c->s_link) (void)hipStreamDestroy(c->s_link);
   delete c;
+}
+
+// Threads per block and bitmap words per tile of the frontier scans, by the
+// words of the id space. Small spaces are dense (a hop finds a large part of
+// the ids new), so many small tiles spread the work; in large ones a tile
+// holds few new nodes and the look-back over the tiles bounds the launch:
+// 487K words (15.6M ids), per launch: 2048 words by 512 threads 13.4 us, 1024
+// by 256 17.2, 512 by 512 27.3.
+struct FrontierShape {
+  int nt, tw;
+  int64_t rows() const { return (int64_t)nt * ms::kFrItems; }  // rows of a tile of old rows
+};
+
+FrontierShape frontier_shape(int64_t W) {
+  if (W <= 16384) return {256, 64};
+  if (W <= 131072) return {256, 256};
+  return {512, 2048};
 }
 
 int init_impl(massive_ctx* c, const massive_init_args* a) {
@@ -925,7 +947,11 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_tab, c->hcap * 8);
   CKA(c->d_pos_of, R * 4);
   CKA(c->d_big, R * 4);
-  CKA(c->d_bits, (c->W + 4) * 4);
+  // both bitmaps in one allocation, the second one 16-byte aligned
+  const int64_t map_words = cdiv(c->W + 4, 4) * 4;
+  CKA(c->d_bits, 2 * map_words * 4);
+  c->d_seen = c->d_bits + map_words;
+  CKA(c->d_rec, R * 16);
   CKA(c->d_sz, kSlots * sizeof(ms::StepSizes));
   CKA(c->d_rs, sizeof(ms::RoundState));
   CKA(c->d_ctr, sizeof(ms::Counters));
@@ -933,8 +959,10 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_landed, cap * 4);
   CKA(c->d_part, c->pmax * 4);
   CKA(c->d_part2, c->pmax * 4);
-  c->scan_tiles = std::max(cdiv(R, ms::kScanTile), cdiv(c->W, ms::kScanTile)) + 1;
-  CKA(c->d_scan_flags, c->scan_tiles * 8);
+  c->scan_tiles = cdiv(R, ms::kScanTile) + 1;
+  const FrontierShape fs = frontier_shape(c->W);
+  CKA(c->d_scan_flags, (c->scan_tiles + cdiv(R, fs.rows()) + cdiv(c->W, fs.tw)) * 8);
+  c->d_tile_flags = c->d_scan_flags + c->scan_tiles;
   for (int i = 0; i < kSlots; ++i) {
     CKA(c->d_hbm_list[i], R * 8);
     CKA(c->d_miss_list[i], R * 8);
@@ -989,16 +1017,17 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   if (c->L) CK(hipMemcpyAsync(c->d_slab, a->local_feat, (int64_t)c->L * rb, hipMemcpyHostToDevice, s));
   {
     CK(hipMemsetAsync(c->d_ctr, 0, sizeof(ms::Counters), s));
-    ms::k_validate_csr<<<grid_for(std::max(R, c->nnz), 256, 8192), 256, 0, s>>>(c->d_indptr, R, c->d_indices, c->nnz,
-                                                                                &c->d_ctr->bad);
+    // (`evicted` holds the number of long rows for this one copy)
+    ms::k_validate_csr<<<grid_for(std::max(R, c->nnz), 256, 8192), 256, 0, s>>>(
+        c->d_indptr, R, c->d_indices, c->nnz, c->big_min, &c->d_ctr->bad, &c->d_ctr->evicted);
     CK(hipMemcpyAsync(c->h_ctr, c->d_ctr, sizeof(ms::Counters), hipMemcpyDeviceToHost, s));
     CK(hipStreamSynchronize(s));
     if (c->h_ctr->bad)
       return c->fail(MASSIVE_EINVAL, (c->h_ctr->bad & 2) ? "indices has ids outside [0, L+H)"
                                                           : "indptr is not non-decreasing");
+    c->long_rows = c->h_ctr->evicted;
   }
-  CK(hipMemsetAsync(c->d_pos_of, 0xFF, R * 4, s));
-  CK(hipMemsetAsync(c->d_bits, 0, (c->W + 4) * 4, s));
+  CK(hipMemsetAsync(c->d_bits, 0, 2 * map_words * 4, s));
   CK(hipMemsetAsync(c->d_ghist, 0, 256 * 4, s));
   CK(hipMemsetAsync(c->d_scan_flags, 0, c->scan_tiles * 8, s));
   CK(hipMemsetAsync(c->d_ctr, 0, sizeof(ms::Counters), s));
@@ -1185,6 +1214,23 @@ int check_step_args(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_ba
   return MASSIVE_OK;
 }
 
+void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream_t s, const ms::FrontierArgs& fa) {
+#define MS_FR(NT, TW)                                         \
+  do {                                                        \
+    if (last)                                                 \
+      ms::k_frontier<NT, TW, true><<<grid, NT, 0, s>>>(fa);   \
+    else                                                      \
+      ms::k_frontier<NT, TW, false><<<grid, NT, 0, s>>>(fa);  \
+  } while (0)
+  if (f.tw == 64)
+    MS_FR(256, 64);
+  else if (f.tw == 256)
+    MS_FR(256, 256);
+  else
+    MS_FR(512, 2048);
+#undef MS_FR
+}
+
 // Enqueues one step (sampling and classify on the main stream, the gathers
 // and the step's completion on the side stream) with the per-step buffers sb.
 int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch* io, const int64_t* nb,
@@ -1215,21 +1261,22 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
   if (!sb.from_scratch) c->slot_clear[slot] = false;
   {
     massive_ctx::Range tr(c, s, 0);
+    const FrontierShape fs = frontier_shape(c->W);
+    const int64_t bit_tiles = cdiv(c->W, fs.tw);
+    {
+      const int64_t nbk = std::max<int64_t>(1, cdiv(nb[0], ms::kScanTile));
+      ms::k_seed_rows<<<(unsigned)nbk, ms::kScanNT, 0, s>>>(
+          c->d_indptr, seeds, n0, c->L, io->nodes, sz, c->fo[0], io->indptr[0], sb.flags, epoch(), c->d_pos_of,
+          c->d_seen, c->d_rec, sb.big, c->big_min, nb[0] > ms::kBlockRowsMax ? nb[0] : 0);
+    }
     for (int k = 1; k <= c->K; ++k) {
       const int64_t nprev = nb[k - 1];
-      const int64_t nbk = std::max<int64_t>(1, cdiv(nprev, ms::kScanTile));
-      // the previous hop's relabel shares the launch
-      const int64_t nrel = k > 1 ? (int64_t)grid_for(eb[k - 2], ms::kScanTile, 1024) : 0;
       // a large frontier lists every row for the one-wave-per-row sampler
       const bool by_waves = nprev > ms::kBlockRowsMax;
-      ms::k_row_scan<<<(unsigned)(nbk + nrel), ms::kScanNT, 0, s>>>(
-          c->d_indptr, io->nodes, sz, k, c->fo[k - 1], io->indptr[k - 1], sb.flags, epoch(),
-          sb.big, c->big_min, nbk, k > 1 ? io->indices[k - 2] : nullptr, c->d_pos_of, by_waves ? nprev : 0,
-          k == 1 ? seeds : nullptr, n0, c->L);
+      const int64_t old_tiles = k < c->K ? cdiv(nprev, fs.rows()) : 0;
       ms::SampleArgs sa;
-      sa.csr_indptr = c->d_indptr;
       sa.csr_indices = c->d_indices;
-      sa.nodes = io->nodes;
+      sa.rec = c->d_rec;
       sa.sz = sz;
       sa.bptr = io->indptr[k - 1];
       sa.out = io->indices[k - 1];
@@ -1242,9 +1289,11 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
       sa.mu32 = c->mu32[k - 1];
       sa.big_min = c->big_min;
       sa.big_rows = sb.big;
-      sa.pos_of = c->d_pos_of;
       sa.bits = c->d_bits;
       sa.tau_iters = c->tau_iters;
+      sa.n_bound = nprev;
+      sa.flags = c->d_tile_flags;
+      sa.n_flags = old_tiles + bit_tiles;
       // a small frontier is bound by its longest rows: a block each; a large
       // one keeps the chip busy: a wave each, longest first. The last hop's
       // dispatch can carry its own start/stop events (timing group 6).
@@ -1252,7 +1301,7 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
       const bool timed = k == c->K && c->kernel_pair(6, &hop_a, &hop_b);
       if (!by_waves) {
         sa.row_waves = 0;
-        sa.big_blocks = std::max<int64_t>(1, std::min<int64_t>(nprev, c->big_blocks));
+        sa.big_blocks = std::min(std::min(nprev, c->long_rows), c->big_blocks);
         const dim3 grid((unsigned)(sa.big_blocks + std::max<int64_t>(1, cdiv(nprev, ms::kSampleWaves))));
         if (timed)
           hipExtLaunchKernelGGL(ms::k_sample_blocks, grid, dim3(ms::kSampleWaves * MS_WAVE), 0, s, hop_a, hop_b, 0, sa);
@@ -1268,12 +1317,28 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
           ms::k_sample_waves<<<grid, ms::kRowWaves * MS_WAVE, 0, s>>>(sa);
       }
       if (timed) c->pending.push_back({hop_a, hop_b, 6});
-      const int64_t nbw = std::max<int64_t>(1, cdiv(c->W, ms::kScanTile));
-      ms::k_bits_scan<<<(unsigned)nbw, ms::kScanNT, 0, s>>>(c->d_bits, c->W, c->L, sz, k, sb.flags,
-                                                             epoch(), io->nodes, c->d_pos_of);
-      if (k == c->K)
-        ms::k_relabel<<<grid_for(eb[k - 1], ms::kScanTile, 1024), ms::kScanNT, 0, s>>>(io->indices[k - 1], sz, k,
-                                                                                     c->d_pos_of);
+      ms::FrontierArgs fa = {};
+      fa.bits = c->d_bits;
+      fa.seen = c->d_seen;
+      fa.W = c->W;
+      fa.L = c->L;
+      fa.sz = sz;
+      fa.hop = k;
+      fa.flags = c->d_tile_flags;
+      fa.old_tiles = old_tiles;
+      fa.n_bound = nprev;
+      fa.nodes = io->nodes;
+      fa.pos_of = c->d_pos_of;
+      if (k < c->K) {
+        fa.csr_indptr = c->d_indptr;
+        fa.rec = c->d_rec;
+        fa.fo = c->fo[k];
+        fa.bptr = io->indptr[k];
+        fa.big_rows = sb.big;
+        fa.big_min = c->big_min;
+        fa.small_end = nb[k] > ms::kBlockRowsMax ? nb[k] : 0;
+      }
+      launch_frontier(fs, k == c->K, (unsigned)(old_tiles + bit_tiles), s, fa);
     }
   }
   // A refill that may still be in flight: hits on its slots read the host
@@ -1321,7 +1386,6 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     ca.hitcnt = c->d_hitcnt;
     ca.S_A = c->d_S_A;
     ca.sa_idx = c->d_sa_idx;
-    ca.pos_of = c->d_pos_of;
     ca.mask = io->mask;
     ca.hbm_list = sb.hbm_list;
     ca.miss_list = miss_list;
@@ -1334,7 +1398,19 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     // the frontier's size is known on the device only: at most kClsBlocks
     // blocks stride over it (a frontier far below the bound leaves the blocks
     // past its end idle, not a long tail of dispatches)
-    ms::k_classify<<<grid_for(nb[c->K], ms::kClsNT * ms::kClsItems, ms::kClsBlocks), ms::kClsNT, 0, s>>>(ca);
+    ca.cls_blocks = grid_for(nb[c->K], ms::kClsNT * ms::kClsItems, ms::kClsBlocks);
+    ca.seen = c->d_seen;
+    ca.pos_of = c->d_pos_of;
+    ca.n_bound = nb[c->K];
+    // relabelling blocks by hop, at most kRelBlocks each
+    ca.rel_first[0] = 0;
+    for (int k = 0; k < c->K; ++k) {
+      ca.ids[k] = io->indices[k];
+      ca.e_bound[k] = eb[k];
+      ca.rel_first[k + 1] =
+          ca.rel_first[k] + (eb[k] > 0 ? grid_for(eb[k], ms::kClsNT * ms::kRelItems, ms::kRelBlocks) : 0u);
+    }
+    ms::k_classify<<<ca.cls_blocks + ca.rel_first[c->K], ms::kClsNT, 0, s>>>(ca);
   }
   CK(hipEventRecord(c->ev_cls_done[slot], s));
   // The gathers run on the side stream, so the main stream goes on to the

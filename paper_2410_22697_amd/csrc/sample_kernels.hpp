@@ -76,68 +76,42 @@ __device__ __forceinline__ uint32_t lookback_exclusive(uint64_t* flags, int64_t 
   return *excl_lds;
 }
 
-// ------------------------------------------------------ per-row counts + scan
-// Block b < nbk: the rows of tile b get min(deg(F[i]), fo) positions; the
-// tile's exclusive prefix comes from the single-pass scan, and bptr[0..n]
-// gets the offsets. Rows longer than big_min go to the front of big_rows (one
-// global atomic per block). With small_end > 0 the other rows go to its back,
-// the r-th listed one at big_rows[small_end - 1 - r]: with n <= small_end
-// rows the two parts never meet, and the one-wave-per-row sampler then finds
-// a row for each of its first n waves. Every load of a thread is issued
-// before the first is used.
-// Blocks b >= nbk relabel the previous hop's sampled ids (rel_ids, if given):
-// that work depends on the same kernels and shares the launch.
-// For hop 1 (seeds given) the rows are the seed batch: the launch also checks
-// each seed (a local id, not repeated: the first to mark pos_of keeps it) and
-// places it, F_0 = seeds, pos_of[seed] = its position, n_0 = n0; a bad seed
-// sets the step's status, which every later kernel checks first.
-__device__ __forceinline__ void relabel_tiles(int32_t* __restrict__ ids, int64_t e, const int32_t* __restrict__ pos_of,
-                                              int64_t b, int64_t nblocks) {
-  for (int64_t b0 = b * kScanTile; b0 < e; b0 += nblocks * kScanTile) {
-    int32_t u[kScanItems], p[kScanItems];
-    // lanes past the end read the last id (or its new value, also a valid
-    // index) and store nothing
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) {
-      const int64_t i = b0 + (int64_t)it * kScanNT + threadIdx.x;
-      u[it] = ids[i < e ? i : e - 1];
-    }
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) pin(u[it]);
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) p[it] = pos_of[u[it]];
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) pin(p[it]);
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) {
-      const int64_t i = b0 + (int64_t)it * kScanNT + threadIdx.x;
-      if (i < e) ids[i] = p[it];
-    }
-  }
+// A frontier row as the sampler takes it, read in one 16-byte load: the node,
+// its row length and where its row starts in the CSR (a row is shorter than
+// 2^32 entries).
+typedef uint32_t v4r __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4r row_record(int32_t v, int64_t start, int64_t d) {
+  return v4r{(uint32_t)v, (uint32_t)d, (uint32_t)start, (uint32_t)((uint64_t)start >> 32)};
 }
 
-__global__ __launch_bounds__(kScanNT) void k_row_scan(const int64_t* __restrict__ csr_indptr,
-                                                      int32_t* __restrict__ nodes, StepSizes* sz, int hop,
-                                                      int32_t fo, int32_t* __restrict__ bptr, uint64_t* flags,
-                                                      uint32_t epoch, int32_t* __restrict__ big_rows,
-                                                      int64_t big_min, int64_t nbk, int32_t* __restrict__ rel_ids,
-                                                      int32_t* __restrict__ pos_of, int64_t small_end,
-                                                      const int32_t* __restrict__ seeds, int32_t n0, int32_t L) {
+// -------------------------------------------------------------- hop 1's rows
+// The seed batch is hop 1's frontier. Block b: the rows of tile b get
+// min(deg, fo) positions; the tile's exclusive prefix comes from the
+// single-pass scan, and bptr[0..n0] gets the offsets. Rows longer than big_min
+// go to the front of big_rows (one global atomic per block). With
+// small_end > 0 the other rows go to its back, the r-th listed one at
+// big_rows[small_end - 1 - r]: with n0 <= small_end rows the two parts never
+// meet, and the one-wave-per-row sampler then finds a row for each of its
+// first n0 waves. Every load of a thread is issued before the first is used.
+// Each seed is checked (a local id, not repeated: the first to set its bit in
+// `seen` keeps it) and placed: F_0 = seeds, pos_of[seed] = its position, its
+// row record, n_0 = n0. A bad seed sets the step's status, which every later
+// kernel checks first.
+__global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict__ csr_indptr,
+                                                       const int32_t* __restrict__ seeds, int32_t n0, int32_t L,
+                                                       int32_t* __restrict__ nodes, StepSizes* sz, int32_t fo,
+                                                       int32_t* __restrict__ bptr, uint64_t* flags, uint32_t epoch,
+                                                       int32_t* __restrict__ pos_of, uint32_t* __restrict__ seen,
+                                                       v4r* __restrict__ rec, int32_t* __restrict__ big_rows,
+                                                       int64_t big_min, int64_t small_end) {
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
   __shared__ int32_t big_lds[kScanTile];  // long rows from the front, the others from the back
   __shared__ int32_t big_n, small_n;
   __shared__ unsigned long long big_base, small_base;
   __shared__ uint32_t excl_lds;
-  if (sz->status) return;
-  if ((int64_t)blockIdx.x >= nbk) {
-    if (rel_ids) relabel_tiles(rel_ids, sz->e[hop - 2], pos_of, blockIdx.x - nbk, gridDim.x - nbk);
-    return;
-  }
-  // hop 1 with seeds: the rows are the seeds, which this launch checks and
-  // places (F_0 = seeds, pos_of[seed] = its position; an out-of-range or
-  // repeated seed flags the step, which every later kernel then abandons)
-  const int64_t n = seeds ? (int64_t)n0 : sz->n[hop - 1];
-  if (seeds && blockIdx.x == 0 && threadIdx.x == 0) sz->n[0] = n0;
+  // (the step's sizes are clear here: no status to check)
+  const int64_t n = n0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) sz->n[0] = n;
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   if (threadIdx.x == 0) big_n = small_n = 0;
   __syncthreads();
@@ -147,25 +121,25 @@ __global__ __launch_bounds__(kScanNT) void k_row_scan(const int64_t* __restrict_
     int32_t v[kScanItems];
     int64_t lo[kScanItems], hi[kScanItems];
 #pragma unroll
-    for (int it = 0; it < kScanItems; ++it) v[it] = (seeds ? seeds : nodes)[base + it < n ? base + it : n - 1];
+    for (int it = 0; it < kScanItems; ++it) v[it] = seeds[base + it < n ? base + it : n - 1];
 #pragma unroll
     for (int it = 0; it < kScanItems; ++it) pin(v[it]);
-    if (seeds) {
 #pragma unroll
-      for (int it = 0; it < kScanItems; ++it) {
-        const int64_t i = base + it;
-        const int32_t x = v[it];
-        const bool ok = x >= 0 && x < L;
-        if (i < n) {
-          if (!ok) {
-            atomicOr(&sz->status, 1);
-          } else {
-            if (atomicCAS(&pos_of[x], -1, (int32_t)i) != -1) atomicOr(&sz->status, 2);
-            nodes[i] = x;
-          }
+    for (int it = 0; it < kScanItems; ++it) {
+      const int64_t i = base + it;
+      const int32_t x = v[it];
+      const bool ok = x >= 0 && x < L;
+      if (i < n) {
+        if (!ok) {
+          atomicOr(&sz->status, 1);
+        } else {
+          const uint32_t bit = 1u << (x & 31);
+          if (atomicOr(&seen[x >> 5], bit) & bit) atomicOr(&sz->status, 2);
+          pos_of[x] = (int32_t)i;
+          nodes[i] = x;
         }
-        v[it] = ok ? x : 0;  // an in-range row for the loads below (the step is abandoned anyway)
       }
+      v[it] = ok ? x : 0;  // an in-range row for the loads below (the step is abandoned anyway)
     }
 #pragma unroll
     for (int it = 0; it < kScanItems; ++it) {
@@ -182,6 +156,7 @@ __global__ __launch_bounds__(kScanNT) void k_row_scan(const int64_t* __restrict_
       const int64_t i = base + it;
       if (i < n) {
         const int64_t d = hi[it] - lo[it];
+        rec[i] = row_record(v[it], lo[it], d);
         c[it] = d < fo ? (int32_t)d : fo;
         s += c[it];
         if (d > big_min)
@@ -204,13 +179,10 @@ __global__ __launch_bounds__(kScanNT) void k_row_scan(const int64_t* __restrict_
     }
   }
   if (threadIdx.x == 0) {
-    if (blockIdx.x == 0) {
-      bptr[0] = 0;
-      sz->n[hop] = n;  // new nodes are added by k_bits_scan
-    }
-    if ((int64_t)blockIdx.x == nbk - 1) sz->e[hop - 1] = (int64_t)before + tot;
-    big_base = big_n ? atomicAdd((unsigned long long*)&sz->n_big[hop - 1], (unsigned long long)big_n) : 0ull;
-    small_base = small_n ? atomicAdd((unsigned long long*)&sz->n_small[hop - 1], (unsigned long long)small_n) : 0ull;
+    if (blockIdx.x == 0) bptr[0] = 0;
+    if (blockIdx.x == gridDim.x - 1) sz->e[0] = (int64_t)before + tot;
+    big_base = big_n ? atomicAdd((unsigned long long*)&sz->n_big[0], (unsigned long long)big_n) : 0ull;
+    small_base = small_n ? atomicAdd((unsigned long long*)&sz->n_small[0], (unsigned long long)small_n) : 0ull;
   }
   __syncthreads();
   for (int j = threadIdx.x; j < big_n; j += kScanNT) big_rows[big_base + j] = big_lds[j];
@@ -259,8 +231,7 @@ __global__ __launch_bounds__(kScanNT) void k_scan_partials(int32_t* __restrict__
 //      key T (it starts below tau's top bit), ties at T are taken in list
 //      order (= ascending j), and the chosen positions are written in
 //      ascending j.
-// The chosen ids not yet in the frontier are marked in the new-node bitmap
-// as they are written. Rows longer than big_min (listed by k_row_scan) are
+// The chosen ids are marked in the sampled-id bitmap as they are written. Rows longer than big_min (listed by k_row_scan) are
 // taken first. Where the frontier is small, so that its few longest rows bound
 // the hop's time, each of them gets a whole block: its waves filter
 // consecutive quarters of the row with the same tau, and the four candidate
@@ -278,9 +249,8 @@ constexpr int64_t kBlockRowsMax = 65536;  // frontiers up to this size sample lo
 constexpr int kTauIters = 64;         // threshold passes: x4 growth (<= 16) then bisection (<= 33)
 
 struct SampleArgs {
-  const int64_t* csr_indptr;
   const int32_t* csr_indices;
-  const int32_t* nodes;
+  const v4r* rec;           // row records of the frontier
   StepSizes* sz;
   const int32_t* bptr;
   int32_t* out;
@@ -291,13 +261,38 @@ struct SampleArgs {
   double mu32;              // (fo + 3 sqrt(fo) + 3) * 2^32
   int64_t big_min;          // rows longer than this are listed in big_rows
   const int32_t* big_rows;  // appended by k_row_scan
+  int64_t n_bound;          // bound of the frontier's rows
   int64_t row_waves;        // k_sample_waves: small_end of k_row_scan (the other rows' list ends there)
   int64_t big_blocks;       // k_sample_blocks: blocks [0, big_blocks) walk the big list, one row per
                             // block; the rest take all other rows, one per wave
-  const int32_t* pos_of;    // frontier position of an id, or -1
-  uint32_t* bits;           // new-node bitmap
+  uint32_t* bits;           // sampled-id bitmap
   int32_t* err;             // threshold search could not isolate a candidate set
   int32_t tau_iters;        // threshold passes allowed per row (kTauIters)
+  uint64_t* flags;          // tile states of the frontier scan that follows: cleared here
+  int64_t n_flags;
+};
+
+__device__ __forceinline__ void clear_flags(const SampleArgs& a) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n_flags;
+       i += (int64_t)gridDim.x * blockDim.x)
+    a.flags[i] = 0ull;
+}
+
+// A row record, the same in every lane, in scalar registers.
+struct Row {
+  int32_t v;
+  uint32_t d;
+  int64_t start;
+  __device__ __forceinline__ Row(const v4r* rec, int64_t row) {
+    const v4r r = rec[row];
+    set(r);
+  }
+  __device__ __forceinline__ explicit Row(const v4r& r) { set(r); }
+  __device__ __forceinline__ void set(const v4r& r) {
+    v = wave_uniform((int32_t)r.x);
+    d = (uint32_t)wave_uniform((int32_t)r.y);
+    start = (int64_t)(((uint64_t)(uint32_t)wave_uniform((int32_t)r.w) << 32) | (uint32_t)wave_uniform((int32_t)r.z));
+  }
 };
 
 // Philox4x32-10 with counter (q, v, t, hop) for every q of one row. Words 1-3
@@ -363,12 +358,12 @@ struct TauSearch {
   }
 };
 
-__device__ __forceinline__ void emit_id(int32_t* __restrict__ out, int p, int32_t u, const int32_t* __restrict__ pos_of,
-                                        uint32_t* __restrict__ bits) {
+__device__ __forceinline__ void emit_id(int32_t* __restrict__ out, int p, int32_t u, uint32_t* __restrict__ bits) {
   out[p] = u;
-  // a no-return atomic OR, with no read of the word first: a read would put a
-  // second dependent load on the row's last steps (hop 3: 181 against 184 us)
-  if (pos_of[u] < 0) atomicOr(&bits[u >> 5], 1u << (u & 31));
+  // a no-return atomic OR, with no read before it (of the word, or of the
+  // frontier): a read would put a second dependent load on the row's last
+  // steps. Ids already in the frontier are marked too; the dedup scan drops them.
+  atomicOr(&bits[u >> 5], 1u << (u & 31));
 }
 
 // Selection among cnt <= kCandCap candidates held in LDS in ascending j
@@ -376,7 +371,7 @@ __device__ __forceinline__ void emit_id(int32_t* __restrict__ out, int p, int32_
 // ascending j. One wavefront; element i sits in slot i / 64 of lane i % 64.
 __device__ __forceinline__ void select_emit(const uint64_t* list, int cnt, int fo, uint64_t tau,
                                             const int32_t* __restrict__ nb, int32_t* __restrict__ out,
-                                            const int32_t* __restrict__ pos_of, uint32_t* __restrict__ bits) {
+                                            uint32_t* __restrict__ bits) {
   const int lane = lane_id();
   const int S = (cnt + MS_WAVE - 1) / MS_WAVE;  // 1..kCandSlots
   uint32_t key[kCandSlots], pos[kCandSlots];
@@ -419,7 +414,7 @@ __device__ __forceinline__ void select_emit(const uint64_t* list, int cnt, int f
     const bool is_lt = (lt[s] >> lane) & 1ull, is_eq = (eq[s] >> lane) & 1ull;
     const bool sel = is_lt || (is_eq && eq_before + lanes_below(eq[s]) < need);
     const uint64_t sm = ballot(sel);
-    if (sel) emit_id(out, p_before + lanes_below(sm), nb[pos[s]], pos_of, bits);
+    if (sel) emit_id(out, p_before + lanes_below(sm), nb[pos[s]], bits);
     p_before += __popcll(sm);
     eq_before += __popcll(eq[s]);
   }
@@ -525,20 +520,20 @@ __device__ __forceinline__ int filter_groups(const PhiloxRow& ph, uint32_t g0, u
 __global__ __launch_bounds__(kRowWaves* MS_WAVE) void k_sample_waves(SampleArgs a) {
   __shared__ uint64_t cand[kRowWaves][kCandCap];
   if (a.sz->status) return;
+  clear_flags(a);
   const int lane = lane_id(), wave = wave_uniform(wave_id());
   const int64_t w = (int64_t)blockIdx.x * kRowWaves + wave;
   const int64_t nbig = a.sz->n_big[a.hop - 1];
   if (w >= a.sz->n[a.hop - 1]) return;
   const int64_t row = wave_uniform((int32_t)a.big_rows[w < nbig ? w : a.row_waves - 1 - (w - nbig)]);
-  // the row, its node and its extent are the same in every lane
-  const int32_t v = wave_uniform(a.nodes[row]);
-  const int64_t start = wave_uniform(a.csr_indptr[v]);
-  const int64_t d = wave_uniform(a.csr_indptr[v + 1]) - start;
+  const Row r(a.rec, row);
+  const int32_t v = r.v;
+  const int64_t start = r.start, d = r.d;
   const int32_t fo = a.fo;
   int32_t* out = a.out + a.bptr[row];
   const int32_t* nb = a.csr_indices + start;
   if (d <= fo) {
-    for (int64_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.pos_of, a.bits);
+    for (int64_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.bits);
     return;
   }
   uint64_t* c = cand[wave];
@@ -560,23 +555,22 @@ __global__ __launch_bounds__(kRowWaves* MS_WAVE) void k_sample_waves(SampleArgs 
     return;
   }
   wave_lds_sync();
-  select_emit(c, cnt, fo, ts.tau, nb, out, a.pos_of, a.bits);
+  select_emit(c, cnt, fo, ts.tau, nb, out, a.bits);
 }
 
-// One row by one wavefront (skipped if it is longer than skip_above).
-__device__ __forceinline__ void sample_row_wave(const SampleArgs& a, int64_t row, uint64_t* c,
-                                                int64_t skip_above = INT64_MAX) {
+// One row by one wavefront (skipped if it is longer than skip_above): its
+// record r, its offset in the output at.
+__device__ __forceinline__ void sample_row_wave(const SampleArgs& a, const Row& r, int64_t at, uint64_t* c,
+                                                int64_t skip_above) {
   const int lane = lane_id();
   const int32_t fo = a.fo;
-  // the row, its node and its extent are the same in every lane
-  const int32_t v = wave_uniform(a.nodes[row]);
-  const int64_t start = wave_uniform(a.csr_indptr[v]);
-  const int64_t d = wave_uniform(a.csr_indptr[v + 1]) - start;
+  const int32_t v = r.v;
+  const int64_t start = r.start, d = r.d;
   if (d > skip_above) return;
-  int32_t* out = a.out + a.bptr[row];
+  int32_t* out = a.out + at;
   const int32_t* nb = a.csr_indices + start;
   if (d <= fo) {
-    for (int64_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.pos_of, a.bits);
+    for (int64_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.bits);
     return;
   }
   TauSearch ts;
@@ -594,7 +588,7 @@ __device__ __forceinline__ void sample_row_wave(const SampleArgs& a, int64_t row
     return;
   }
   wave_lds_sync();
-  select_emit(c, cnt, fo, ts.tau, nb, out, a.pos_of, a.bits);
+  select_emit(c, cnt, fo, ts.tau, nb, out, a.bits);
   // (a wave samples one row: no fence at the end, which would hold the wave
   // until its stores and bitmap atomics have completed)
 }
@@ -603,19 +597,42 @@ __device__ __forceinline__ void sample_row_wave(const SampleArgs& a, int64_t row
 // list; every other row one per wave.
 __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleArgs a) {
   __shared__ uint64_t cand[kSampleWaves][kCandCap];
-  if (a.sz->status) return;
   const int lane = lane_id(), wave = wave_uniform(wave_id());
   const int32_t fo = a.fo;
-  if ((int64_t)blockIdx.x < a.big_blocks) {
+  if ((int64_t)blockIdx.x >= a.big_blocks) {
+    // a row per wave: the step's state and the row's record in one round of
+    // loads (rows past the frontier's end have stale records, which are read
+    // and dropped)
+    const int64_t row = (int64_t)(blockIdx.x - a.big_blocks) * kSampleWaves + wave;
+    const int64_t at_row = min(row, a.n_bound - 1);
+    const int32_t status = a.sz->status;
+    const int64_t n = a.sz->n[a.hop - 1];
+    v4r rc = {0, 0, 0, 0};
+    int32_t at = 0;
+    if (at_row >= 0) {
+      rc = a.rec[at_row];
+      at = a.bptr[at_row];
+    }
+    pin(rc);
+    pin(at);
+    if (status) return;
+    clear_flags(a);
+    // rows longer than big_min are taken by the big list
+    if (row < n) sample_row_wave(a, Row(rc), wave_uniform(at), cand[wave], a.big_min);
+    return;
+  }
+  if (a.sz->status) return;
+  clear_flags(a);
+  {
     __shared__ uint64_t merged[kCandCap];
     __shared__ int counts[kSampleWaves];
     // long rows, one per block at a time
     const int64_t n_big = a.sz->n_big[a.hop - 1];
     for (int64_t b = blockIdx.x; b < n_big; b += a.big_blocks) {
       const int64_t row = wave_uniform((int32_t)a.big_rows[b]);
-      const int32_t v = wave_uniform(a.nodes[row]);
-      const int64_t start = wave_uniform(a.csr_indptr[v]);
-      const int64_t d = wave_uniform(a.csr_indptr[v + 1]) - start;  // > big_min >= fo
+      const Row r(a.rec, row);
+      const int32_t v = r.v;
+      const int64_t start = r.start, d = r.d;  // d > big_min >= fo
       int32_t* out = a.out + a.bptr[row];
       const int32_t* nb = a.csr_indices + start;
       const uint32_t d32 = (uint32_t)d;
@@ -648,77 +665,379 @@ __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleA
       for (int x = 0; x < wave; ++x) before += counts[x];
       for (int i = lane; i < counts[wave]; i += MS_WAVE) merged[before + i] = cand[wave][i];
       __syncthreads();
-      if (wave == 0) select_emit(merged, total, fo, ts.tau, nb, out, a.pos_of, a.bits);
+      if (wave == 0) select_emit(merged, total, fo, ts.tau, nb, out, a.bits);
       if (b + a.big_blocks < n_big) __syncthreads();  // merged and counts are reused for the next row
     }
-    return;
   }
-  const int64_t row = (int64_t)(blockIdx.x - a.big_blocks) * kSampleWaves + wave;
-  if (row >= a.sz->n[a.hop - 1]) return;
-  // rows longer than big_min are taken by the big list
-  sample_row_wave(a, row, cand[wave], a.big_min);
 }
 
 // ------------------------------------------------------------ dedup/relabel
-// New nodes in ascending id: F[n_{k-1} + rank] = u, pos_of[u] = that
-// position, with the rank from the single-pass scan of the bitmap's
-// popcounts; the bitmap is cleared for the next hop. The last tile writes
-// n_k. The new nodes below L (local ids) are the prefix at id L: the thread
-// whose words hold id L writes that count (the last tile, if every id is
-// below L). (bits holds W + 4 words, the last four always zero.)
-__global__ __launch_bounds__(kScanNT) void k_bits_scan(uint32_t* __restrict__ bits, int64_t W, int32_t L,
-                                                       StepSizes* sz, int hop, uint64_t* flags, uint32_t epoch,
-                                                       int32_t* __restrict__ nodes, int32_t* __restrict__ pos_of) {
-  __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  __shared__ uint32_t excl_lds;
-  if (sz->status) return;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
-  if (base < W) w4 = *reinterpret_cast<const uint4*>(bits + base);
-  const uint32_t w[kScanItems] = {w4.x, w4.y, w4.z, w4.w};
-  const int32_t s = __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
-  int32_t tot;
-  const int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot);
-  const uint32_t before = lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, &sz->status, &excl_lds);
-  const int64_t n_prev = sz->n[hop - 1];
-  const int64_t wL = (int64_t)(L >> 5);
-  if (wL < W && wL >= base && wL < base + kScanItems) {
-    int32_t below = 0;
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) {
-      if (base + it < wL) below += __popc(w[it]);
-      else if (base + it == wL) below += __popc(w[it] & ((1u << (L & 31)) - 1u));
+// One launch after each hop's sampling: the frontier F_k, and the rows that
+// the next hop samples for.
+// New nodes in ascending id: F[n_{k-1} + rank] = u, pos_of[u] = that position,
+// u the rank-th sampled id not in the frontier (bits & ~seen). `bits` is
+// cleared for the next hop; the new nodes join `seen`, which the last hop
+// clears for the next step. The new nodes below L (local ids) are the prefix
+// at id L: the thread whose words hold id L writes that count (the last tile,
+// if every id is below L). (Both bitmaps hold W + 4 words, the last four
+// always zero.) For every row of F_k (unless the hop is the last) also its
+// record, its offset bptr (prefix of min(deg, fo)) and its place in the row
+// list, as in k_seed_rows.
+// Tiles: first the rows of F_{k-1}, whose records are there (NT * kFrItems per
+// tile), then TW words of the bitmap per tile. A tile publishes its new nodes
+// and its sampled positions in one 64-bit word (state << 62 | positions << 31
+// | nodes, both below 2^31; the sampling launch before this one cleared it)
+// and takes the sums of the tiles before it by look-back, NT tiles at a time.
+// A tile's set bits are first spread into LDS, so that consecutive threads
+// take consecutive new nodes whatever the bitmap's density: their loads
+// (ascending ids) and stores are then coalesced. With one thread walking its
+// words instead, a dense bitmap kept one block busy with scattered stores:
+// 107K ids, 26K-33K new nodes, 28-34 us a hop, and 9 us for the next hop's
+// rows in a launch of their own; 6.5-7.9 us for both here. Of a launch on a
+// small frontier (6.2 us) most is the chain of dependent steps: loads,
+// look-back, loads.
+constexpr int kFrItems = 8;  // rows in flight per thread
+
+struct FrontierArgs {
+  uint32_t* bits;
+  uint32_t* seen;
+  int64_t W;
+  int32_t L;
+  StepSizes* sz;
+  int32_t hop;  // 1-based: the hop just sampled
+  uint64_t* flags;
+  int64_t old_tiles;
+  int64_t n_bound;  // bound of n_{hop-1}
+  int32_t* nodes;
+  int32_t* pos_of;
+  // rows of the next hop (not for the last one)
+  const int64_t* csr_indptr;
+  v4r* rec;
+  int32_t fo;
+  int32_t* bptr;
+  int32_t* big_rows;
+  int64_t big_min;
+  int64_t small_end;
+};
+
+__device__ __forceinline__ uint64_t fr_state(uint32_t st, uint32_t n, uint32_t e) {
+  return ((uint64_t)st << 62) | ((uint64_t)e << 31) | n;
+}
+
+struct FrSums {
+  uint32_t n, e;
+};
+
+// Publishes tile b's sums (state 1), waits for the sums of the tiles before it
+// and publishes the inclusive ones (state 2). Whole block; the wait is bounded
+// as in lookback_exclusive.
+template <int NT>
+__device__ __forceinline__ FrSums fr_lookback(uint64_t* flags, int64_t b, uint32_t n, uint32_t e, int32_t* status) {
+  constexpr int NW = NT / MS_WAVE;
+  __shared__ uint32_t w_n[NW], w_e[NW];
+  __shared__ int32_t w_st[NW];  // 0: not ready, 1: all aggregates, 2: ends at an inclusive sum
+  const int lane = lane_id(), wave = wave_id();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&flags[b], fr_state(b == 0 ? 2u : 1u, n, e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  FrSums x = {0, 0};
+  int64_t p = b - 1;  // thread t reads tile p - t
+  int spins = 0;
+  while (p >= 0) {
+    const int64_t i = p - (int64_t)threadIdx.x;
+    // before tile 0: an inclusive sum of nothing
+    const uint64_t f = i >= 0 ? __hip_atomic_load(&flags[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                              : fr_state(2u, 0, 0);
+    const uint32_t st = (uint32_t)(f >> 62);
+    const uint64_t ready = ballot(st != 0), inc = ballot(st == 2u);
+    // lanes 0..k count, k = the nearest inclusive sum (or the wave's last tile)
+    const int k = inc ? __ffsll((unsigned long long)inc) - 1 : MS_WAVE - 1;
+    const uint64_t need = k == MS_WAVE - 1 ? ~0ull : ((2ull << k) - 1);
+    const bool ok = (ready & need) == need;
+    const uint32_t sn = wave_sum(lane <= k ? (uint32_t)f & 0x7FFFFFFFu : 0u);
+    const uint32_t se = wave_sum(lane <= k ? (uint32_t)(f >> 31) & 0x7FFFFFFFu : 0u);
+    if (lane == 0) {
+      w_n[wave] = sn;
+      w_e[wave] = se;
+      w_st[wave] = !ok ? 0 : inc ? 2 : 1;
     }
-    sz->n_local_new[hop - 1] = (int64_t)before + ex + below;
-  }
-  int64_t off = n_prev + before + ex;
-#pragma unroll
-  for (int it = 0; it < kScanItems; ++it) {
-    uint32_t x = w[it];
-    if (!x) continue;
-    const int32_t ubase = (int32_t)((base + it) << 5);
-    while (x) {
-      const int b = __ffs(x) - 1;
-      x &= x - 1;
-      const int32_t u = ubase + b;
-      nodes[off] = u;
-      pos_of[u] = (int32_t)off;
-      ++off;
+    __syncthreads();
+    uint32_t an = 0, ae = 0;
+    int st_all = 1;
+    for (int w = 0; w < NW && st_all == 1; ++w) {
+      st_all = w_st[w];
+      if (st_all) {
+        an += w_n[w];
+        ae += w_e[w];
+      }
     }
-    bits[base + it] = 0u;
+    __syncthreads();
+    if (st_all) {
+      x.n += an;
+      x.e += ae;
+      if (st_all == 2) break;
+      p -= NT;
+      continue;
+    }
+    if (++spins > kLookbackSpins) {
+      if (threadIdx.x == 0) atomicOr(status, 8);
+      break;
+    }
+    __builtin_amdgcn_s_sleep(1);
   }
-  if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) {
-    sz->n[hop] = n_prev + before + tot;
-    if (wL >= W) sz->n_local_new[hop - 1] = (int64_t)before + tot;  // every id is below L
+  if (threadIdx.x == 0 && b > 0)
+    __hip_atomic_store(&flags[b], fr_state(2u, x.n + n, x.e + e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return x;
+}
+
+template <int NT, int TW, bool LAST>
+__global__ __launch_bounds__(NT) void k_frontier(FrontierArgs a) {
+  constexpr int kFrNT = NT, kFrWaves = NT / MS_WAVE, kFrChunk = NT * kFrItems;
+  constexpr int WPT = TW > NT ? TW / NT : 1;  // words per thread (of the first TW / WPT threads)
+  static_assert(WPT == 1 || WPT == 4, "one word or one 16-byte vector");
+  static_assert(kFrItems * kFrWaves <= MS_WAVE, "the waves' sums are scanned by one wave");
+  __shared__ int32_t lds[kFrWaves + 1];
+  __shared__ int32_t list[kFrChunk];
+  __shared__ int32_t wsum[kFrItems * kFrWaves + 1];
+  __shared__ int32_t red[2][kFrWaves];
+  __shared__ int32_t big_n, small_n;
+  __shared__ unsigned long long base_of[2];
+  const int lane = lane_id(), wave = wave_id();
+  const bool old = (int64_t)blockIdx.x < a.old_tiles;
+  const int64_t row0 = (int64_t)blockIdx.x * kFrChunk;             // of a tile of old rows
+  const int64_t word0 = ((int64_t)blockIdx.x - a.old_tiles) * TW;  // of a bitmap tile
+  const int64_t i0w = word0 + (int64_t)threadIdx.x * WPT;          // this thread's first word
+  const bool words = !old && (int)threadIdx.x * WPT < TW && i0w < a.W;
+  // the step's status and sizes, and the tile's words or row lengths, in one
+  // round of loads
+  const int32_t status = a.sz->status;
+  const int64_t n_prev = a.sz->n[a.hop - 1];
+  uint32_t w[WPT], sn[WPT];
+  uint32_t d[kFrItems] = {};
+#pragma unroll
+  for (int x = 0; x < WPT; ++x) w[x] = sn[x] = 0u;
+  if (words) {
+    if (WPT == 4) {  // (i0w is a multiple of four: aligned, and the padding words cover the last ones)
+      const uint4 b4 = *reinterpret_cast<const uint4*>(a.bits + i0w), s4 = *reinterpret_cast<const uint4*>(a.seen + i0w);
+      const uint32_t bb[4] = {b4.x, b4.y, b4.z, b4.w}, ss[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+      for (int x = 0; x < WPT; ++x) {
+        w[x] = bb[x];
+        sn[x] = ss[x];
+      }
+    } else {
+      w[0] = a.bits[i0w];
+      sn[0] = a.seen[i0w];
+    }
+  }
+  if (!LAST && old) {
+#pragma unroll
+    for (int it = 0; it < kFrItems; ++it) d[it] = a.rec[min(row0 + it * kFrNT + threadIdx.x, a.n_bound - 1)].y;
+  }
+#pragma unroll
+  for (int x = 0; x < WPT; ++x) {
+    pin(w[x]);
+    pin(sn[x]);
+  }
+  if (!LAST) {
+#pragma unroll
+    for (int it = 0; it < kFrItems; ++it) pin(d[it]);
+  }
+  if (status) return;
+  int32_t ex = 0, tot = 0, below = -1;
+  if (old) {
+    tot = (int32_t)min(max(n_prev - row0, (int64_t)0), (int64_t)kFrChunk);
+  } else {
+    int32_t mine = 0;
+#pragma unroll
+    for (int x = 0; x < WPT; ++x) {
+      const uint32_t b = w[x];
+      w[x] = b & ~sn[x];
+      mine += __popc(w[x]);
+      if (b) a.bits[i0w + x] = 0u;
+      if (LAST) {
+        if (sn[x]) a.seen[i0w + x] = 0u;
+      } else if (w[x]) {
+        a.seen[i0w + x] = sn[x] | w[x];
+      }
+    }
+    ex = block_exclusive_scan<kFrNT>(mine, lds, &tot);
+    const int64_t wL = (int64_t)(a.L >> 5);
+    if (words && wL < a.W && wL >= i0w && wL < i0w + WPT) {
+      below = ex;
+#pragma unroll
+      for (int x = 0; x < WPT; ++x) {
+        if (i0w + x < wL) below += __popc(w[x]);
+        else if (i0w + x == wL) below += __popc(w[x] & ((1u << (a.L & 31)) - 1u));
+      }
+    }
+  }
+  const int64_t id0 = word0 << 5;
+  int32_t u[kFrItems] = {};
+  int64_t lo[kFrItems] = {}, hi[kFrItems] = {};
+  // items c0 + it * kFrNT + thread of the tile: their nodes and row lengths
+  auto load = [&](int32_t c0) {
+    const int32_t m = min(tot - c0, kFrChunk);
+    if (old) return;  // (one chunk: its row lengths were loaded above)
+    __syncthreads();
+    int32_t o = ex;
+#pragma unroll
+    for (int x = 0; x < WPT; ++x)
+      for (uint32_t y = w[x]; y; y &= y - 1) {
+        if (o >= c0 && o < c0 + kFrChunk) list[o - c0] = (int32_t)((threadIdx.x * WPT + x) * 32 + __ffs(y) - 1);
+        ++o;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kFrItems; ++it) {
+      const int32_t j = it * kFrNT + threadIdx.x;
+      u[it] = (int32_t)id0 + list[j < m ? j : 0];
+    }
+    if (LAST) return;
+#pragma unroll
+    for (int it = 0; it < kFrItems; ++it)
+      if (it * kFrNT < m) {  // the same in every lane
+        lo[it] = a.csr_indptr[u[it]];
+        hi[it] = a.csr_indptr[u[it] + 1];
+      }
+#pragma unroll
+    for (int it = 0; it < kFrItems; ++it) {
+      pin(lo[it]);
+      pin(hi[it]);
+      d[it] = (uint32_t)(hi[it] - lo[it]);
+    }
+  };
+  // the tile's sampled positions and long rows
+  int32_t sum_e = 0, n_big = 0;
+  if (!LAST) {
+    for (int32_t c0 = 0; c0 < tot; c0 += kFrChunk) {
+      load(c0);
+#pragma unroll
+      for (int it = 0; it < kFrItems; ++it)
+        if (c0 + it * kFrNT + (int32_t)threadIdx.x < tot) {
+          sum_e += d[it] < (uint32_t)a.fo ? (int32_t)d[it] : a.fo;
+          n_big += (int64_t)d[it] > a.big_min;
+        }
+    }
+    sum_e = wave_sum(sum_e);
+    n_big = wave_sum(n_big);
+    if (lane == 0) {
+      red[0][wave] = sum_e;
+      red[1][wave] = n_big;
+    }
+    if (threadIdx.x == 0) big_n = small_n = 0;
+    __syncthreads();
+    sum_e = n_big = 0;
+    for (int x = 0; x < kFrWaves; ++x) {
+      sum_e += red[0][x];
+      n_big += red[1][x];
+    }
+    // (issued before the look-back, whose wait covers their latency)
+    if (threadIdx.x == 0) {
+      base_of[0] = n_big ? atomicAdd((unsigned long long*)&a.sz->n_big[a.hop], (unsigned long long)n_big) : 0ull;
+      base_of[1] = a.small_end && tot > n_big
+                       ? atomicAdd((unsigned long long*)&a.sz->n_small[a.hop], (unsigned long long)(tot - n_big))
+                       : 0ull;
+    }
+  }
+  const FrSums before = fr_lookback<NT>(a.flags, blockIdx.x, old ? 0u : (uint32_t)tot, (uint32_t)sum_e, &a.sz->status);
+  if (below >= 0) a.sz->n_local_new[a.hop - 1] = (int64_t)before.n + below;
+  if (threadIdx.x == 0) {
+    if (blockIdx.x == gridDim.x - 1) {
+      a.sz->n[a.hop] = n_prev + before.n + (old ? 0 : tot);
+      if (!LAST) a.sz->e[a.hop] = (int64_t)before.e + sum_e;
+      if ((int64_t)(a.L >> 5) >= a.W) a.sz->n_local_new[a.hop - 1] = (int64_t)before.n + tot;  // every id is below L
+    }
+    if (!LAST && blockIdx.x == 0) a.bptr[0] = 0;
+  }
+  const int64_t i0 = old ? row0 : n_prev + before.n;  // frontier row of item 0
+  __syncthreads();  // (base_of)
+  int64_t run = before.e;
+  for (int32_t c0 = 0; c0 < tot; c0 += kFrChunk) {
+    if (LAST || tot > kFrChunk) load(c0);  // (a tile of one chunk still holds it)
+    int32_t c[kFrItems], inc[kFrItems];
+    if (!LAST) {
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < kFrItems; ++it) {
+        const bool in = c0 + it * kFrNT + (int32_t)threadIdx.x < tot;
+        c[it] = !in ? 0 : d[it] < (uint32_t)a.fo ? (int32_t)d[it] : a.fo;
+        inc[it] = 0;
+        if (c0 + it * kFrNT < tot) inc[it] = wave_inclusive_scan(c[it]);  // (the same in every lane)
+        if (lane == MS_WAVE - 1) wsum[it * kFrWaves + wave] = inc[it];
+      }
+      __syncthreads();
+      if (wave == 0) {
+        const int32_t x = lane < kFrItems * kFrWaves ? wsum[lane] : 0;
+        const int32_t y = wave_inclusive_scan(x);
+        if (lane < kFrItems * kFrWaves) wsum[lane] = y - x;
+        if (lane == kFrItems * kFrWaves - 1) wsum[kFrItems * kFrWaves] = y;
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int it = 0; it < kFrItems; ++it) {
+      const int32_t j = c0 + it * kFrNT + (int32_t)threadIdx.x;
+      const bool in = j < tot;
+      const int64_t i = i0 + j;
+      if (c0 + it * kFrNT >= tot) break;
+      if (in && !old) {
+        a.nodes[i] = u[it];
+        a.pos_of[u[it]] = (int32_t)i;
+        if (!LAST) a.rec[i] = row_record(u[it], lo[it], d[it]);
+      }
+      if (!LAST) {
+        if (in) a.bptr[i + 1] = (int32_t)(run + wsum[it * kFrWaves + wave] + inc[it]);
+        const bool big = in && (int64_t)d[it] > a.big_min, small = in && !big && a.small_end;
+        const uint64_t mb = ballot(big), ms = ballot(small);
+        if (mb) {
+          int32_t at = 0;
+          if (lane == 0) at = atomicAdd(&big_n, __popcll(mb));
+          at = __shfl(at, 0, MS_WAVE);
+          if (big) a.big_rows[base_of[0] + at + lanes_below(mb)] = (int32_t)i;
+        }
+        if (ms) {
+          int32_t at = 0;
+          if (lane == 0) at = atomicAdd(&small_n, __popcll(ms));
+          at = __shfl(at, 0, MS_WAVE);
+          if (small) a.big_rows[a.small_end - 1 - (int64_t)(base_of[1] + at + lanes_below(ms))] = (int32_t)i;
+        }
+      }
+    }
+    if (!LAST) run += wsum[kFrItems * kFrWaves];
   }
 }
 
-// Relabel the last hop's sampled ids to their frontier positions (earlier
-// hops are relabelled by the next hop's k_row_scan).
-__global__ __launch_bounds__(kScanNT) void k_relabel(int32_t* __restrict__ ids, const StepSizes* sz, int hop,
-                                                     const int32_t* __restrict__ pos_of) {
-  if (sz->status) return;
-  relabel_tiles(ids, sz->e[hop - 1], pos_of, blockIdx.x, gridDim.x);
+// Sampled ids to their frontier positions: NT threads x kRelItems ids per
+// block and pass, block b of the hop's nblocks striding over them; every load
+// of a thread is issued before the first is used (the first pass's together
+// with the hop's size: the array holds e_bound ids), and lanes past the end
+// store nothing.
+constexpr int kRelItems = 4;
+template <int NT>
+__device__ __forceinline__ void relabel_hop(int32_t* __restrict__ ids, const StepSizes* sz, int hop, int64_t e_bound,
+                                            const int32_t* __restrict__ pos_of, int64_t b, int64_t nblocks) {
+  const int32_t status = sz->status;
+  const int64_t e = sz->e[hop - 1];
+  for (int64_t b0 = b * NT * kRelItems; b0 < e_bound; b0 += nblocks * NT * kRelItems) {
+    int32_t u[kRelItems], p[kRelItems];
+#pragma unroll
+    for (int it = 0; it < kRelItems; ++it) u[it] = ids[min(b0 + (int64_t)it * NT + threadIdx.x, e_bound - 1)];
+#pragma unroll
+    for (int it = 0; it < kRelItems; ++it) pin(u[it]);
+    if (status || b0 >= e) return;
+#pragma unroll
+    for (int it = 0; it < kRelItems; ++it) {
+      const int64_t i = b0 + (int64_t)it * NT + threadIdx.x;
+      p[it] = pos_of[i < e ? u[it] : 0];
+    }
+#pragma unroll
+    for (int it = 0; it < kRelItems; ++it) pin(p[it]);
+#pragma unroll
+    for (int it = 0; it < kRelItems; ++it) {
+      const int64_t i = b0 + (int64_t)it * NT + threadIdx.x;
+      if (i < e) ids[i] = p[it];
+    }
+  }
 }
 
 }  // namespace ms
