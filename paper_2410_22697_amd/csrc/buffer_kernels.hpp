@@ -429,16 +429,25 @@ __global__ __launch_bounds__(256) void k_gather_hbm(const int2* __restrict__ lis
 // link-bound steps). The last block to finish then clears the step's sizes,
 // so the slot's next step needs no clearing of its own (tail.clear).
 // dummy: a device row of row_bytes that lanes past the end move onto itself.
+struct MissArgs {
+  const int2* list;
+  const int32_t* wslot;
+  const int64_t* count;
+  uint64_t bound;  // rows that the list has room for (>= 1)
+  const uint8_t* src;
+  uint8_t* dst;
+  uint8_t* buf;
+  uint8_t* dummy;
+  StepTail tail;
+};
+
 template <typename V, bool ONE>
-__global__ __launch_bounds__(256) void k_gather_miss(const int2* __restrict__ list, const int32_t* __restrict__ wslot,
-                                                     const int64_t* __restrict__ count, const uint8_t* __restrict__ src,
-                                                     uint8_t* __restrict__ dst, uint8_t* __restrict__ buf,
-                                                     uint8_t* __restrict__ dummy, int64_t rb, uint32_t cpr,
-                                                     uint64_t magic, StepTail tail) {
+__device__ __forceinline__ void miss_body(const MissArgs& a, int64_t rb, uint32_t cpr, uint64_t magic, uint64_t blocks) {
   constexpr int U = 4;
-  const uint64_t n = (uint64_t)*count;
+  const StepTail& tail = a.tail;
+  const uint64_t n = (uint64_t)*a.count;
   const uint64_t total = n * cpr;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  const uint64_t stride = blocks * blockDim.x;
   for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < total; c += U * stride) {
     uint64_t task[U], off[U];
     bool in[U];
@@ -452,40 +461,62 @@ __global__ __launch_bounds__(256) void k_gather_miss(const int2* __restrict__ li
     int32_t ws[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      e[u] = list[task[u]];
-      ws[u] = wslot[task[u]];
+      e[u] = a.list[task[u]];
+      ws[u] = a.wslot[task[u]];
     }
     V v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint8_t* p = in[u] ? src + (uint64_t)(uint32_t)e[u].y * rb + off[u] : dummy + off[u];
+      const uint8_t* p = in[u] ? a.src + (uint64_t)(uint32_t)e[u].y * rb + off[u] : a.dummy + off[u];
       v[u] = *reinterpret_cast<const V*>(p);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      uint8_t* q = in[u] ? dst + (uint64_t)(uint32_t)e[u].x * rb + off[u] : dummy + off[u];
+      uint8_t* q = in[u] ? a.dst + (uint64_t)(uint32_t)e[u].x * rb + off[u] : a.dummy + off[u];
       __builtin_nontemporal_store(v[u], reinterpret_cast<V*>(q));
       if (in[u] && ws[u] >= 0) {
-        *reinterpret_cast<V*>(buf + (uint64_t)(uint32_t)ws[u] * rb + off[u]) = v[u];
+        *reinterpret_cast<V*>(a.buf + (uint64_t)(uint32_t)ws[u] * rb + off[u]) = v[u];
         if (off[u] == 0 && tail.round_id >= 0 && ws[u] < tail.cap)
           __hip_atomic_store(&tail.landed[ws[u]], tail.round_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
   if (blockIdx.x == 0) publish_step(tail);
+}
+
+template <typename V, bool ONE>
+__global__ __launch_bounds__(256) void k_gather_miss(MissArgs a, int64_t rb, uint32_t cpr, uint64_t magic) {
+  miss_body<V, ONE>(a, rb, cpr, magic, gridDim.x);
+  if (!a.tail.clear) return;
   // the last block to finish clears the sizes for the slot's next step (every
   // block has read its count, and block 0 has published them, by then)
   __shared__ int last;
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
-    last = atomicAdd(&tail.sz->blocks_done, 1) == (int)gridDim.x - 1;
+    last = atomicAdd(&a.tail.sz->blocks_done, 1) == (int)gridDim.x - 1;
   }
   __syncthreads();
-  if (last && tail.clear) {
+  if (last) {
     __threadfence();
-    for (int i = threadIdx.x; i < kSizeWords; i += blockDim.x) reinterpret_cast<int32_t*>(tail.sz)[i] = 0;
+    for (int i = threadIdx.x; i < kSizeWords; i += blockDim.x) reinterpret_cast<int32_t*>(a.tail.sz)[i] = 0;
   }
+}
+
+// Both gathers of a step that is waited for at once, in one launch: the first
+// `blocks` blocks are the miss gather's, the others the HBM gather's. No
+// sampling runs beside such a step, so the HBM rows move while the link's
+// rows are under way (in look-ahead they run alone, as the host reads would
+// throttle them). The sizes are left for the next step to clear (k_seed_rows).
+template <typename V, bool ONE>
+__global__ __launch_bounds__(256) void k_gather_both(MissArgs a, uint32_t blocks, const int2* __restrict__ list,
+                                                     const int64_t* __restrict__ count,
+                                                     const uint8_t* __restrict__ src, int64_t rb, uint32_t cpr,
+                                                     uint64_t magic) {
+  if (blockIdx.x < blocks)
+    miss_body<V, ONE>(a, rb, cpr, magic, blocks);
+  else
+    gather_body<V, ONE, 4>(list, count, a.bound, src, a.dst, rb, cpr, magic, blockIdx.x - blocks, gridDim.x - blocks);
 }
 
 // The step's completion as a kernel of its own, where no miss gather ends

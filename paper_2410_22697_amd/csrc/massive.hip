@@ -56,14 +56,14 @@ inline unsigned grid_for(int64_t n, int nt, int64_t cap = 16384) {
 // ------------------------------------------------------------- no-alloc path
 // massive_sample_noalloc takes a step's per-step buffers (sizes, the two
 // gather lists, the write-through slots, the sampler's row list, the scan flags)
-// from this file-scope array instead of the context's. Layout: StepSizes
-// (512 B) | hbm list int2[kNoAllocMaxRows] | miss list int2[..] | write-through
+// from this file-scope array instead of the context's. Layout: two StepSizes
+// (512 B each; the calls take them in turn, and each clears the other's) | hbm list int2[kNoAllocMaxRows] | miss list int2[..] | write-through
 // slots int32[..] | big rows int32[..] | scan flags uint64[kNoAllocFlagWords].
 // Each GPU holds its own copy (~30 MiB) while the library is loaded; its device
 // address is looked up once per device, in massive_init.
 constexpr int64_t kNoAllocMaxRows = 1310720;  // frontier rows (covers a 1,081,344-row bound)
-constexpr int64_t kNoAllocFlagWords = (int64_t(1) << 31) / 32 / ms::kScanTile + 2;  // any L + H < 2^31
-constexpr int64_t kNoAllocBytes = 512 + kNoAllocMaxRows * (8 + 8 + 4 + 4) + kNoAllocFlagWords * 8;
+constexpr int64_t kNoAllocFlagWords = kNoAllocMaxRows / ms::kScanTile + 2;  // a tile each of the seeds' scan
+constexpr int64_t kNoAllocBytes = 1024 + kNoAllocMaxRows * (8 + 8 + 4 + 4) + kNoAllocFlagWords * 8;
 static_assert(sizeof(ms::StepSizes) <= 512, "sizes fit the first 512 bytes");
 static __device__ __align__(256) uint8_t scratch[kNoAllocBytes];
 
@@ -71,6 +71,16 @@ namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_addr[kMaxDevices] = {};  // device address of `scratch` on each device, once looked up
+// The array's state on each device, which outlives a call: whose turn the two
+// sizes are, whether a call ended without leaving them clear, and the epoch of
+// the last scan (its flags are tagged, so they are cleared only when the tags
+// would wrap around; a loaded library starts with an all-zero array).
+struct ScratchState {
+  int turn = 0;
+  bool unclear = false;
+  uint32_t epoch = 0;
+};
+ScratchState g_scratch[kMaxDevices];
 
 // The device address of `scratch` on device dev, which must be current: the
 // array's name in host code is a host-side stand-in, not a device address.
@@ -395,25 +405,27 @@ bool device_visible(const void* p) {
          at.devicePointer != nullptr;
 }
 
-// the flattened gather, specialised on the widest vector the row allows
-enum GatherKind { kHbm, kMiss };
-
 // The flattened row gather, specialised on the widest vector the row and
 // both base pointers allow. max_blocks bounds the grid: host-link gathers
 // use a few CUs (16 blocks reach the link's rate; more only congest the
 // fabric that HBM traffic also needs).
 // With timing on, the dispatch itself is bracketed by hipExtLaunchKernelGGL's
 // start/stop events (no launch latency in the measured time).
-// The miss gather also takes the write-through slots (wslot) and the buffer
-// rows (buf) of the hits on slots still refilling.
-void launch_gather(massive_ctx* c, int group, GatherKind kind, hipStream_t s, const int2* list,
-                   const int64_t* count, const uint8_t* src, uint8_t* dst, int64_t rb, int64_t max_rows,
-                   int64_t max_blocks, const int32_t* wslot = nullptr, uint8_t* buf = nullptr,
-                   const ms::StepTail* tail = nullptr) {
+// The miss gather also takes the write-through slots and the buffer rows of
+// the hits on slots still refilling. kBoth: the two in one launch (`m` is the
+// miss gather's part, host_blocks its blocks); no timing group covers it.
+enum GatherKind { kHbm, kMiss, kBoth };
+
+void launch_gather(massive_ctx* c, GatherKind kind, hipStream_t s, const int2* list, const int64_t* count,
+                   uint8_t* dst, int64_t max_rows, int64_t host_blocks, const ms::MissArgs* m) {
   hipEvent_t ea = nullptr, eb = nullptr;
-  const bool timed = c->kernel_pair(group, &ea, &eb);
+  const int group = kind == kMiss ? 3 : 2;
+  const bool timed = kind != kBoth && c->kernel_pair(group, &ea, &eb);
+  const int64_t rb = c->rb;
+  const uint8_t* slab = c->d_slab;
   int vec = 4;
-  const uintptr_t al = (uintptr_t)src | (uintptr_t)dst | (uintptr_t)buf;
+  const uintptr_t al = (kind == kMiss ? 0 : (uintptr_t)slab) | (uintptr_t)dst |
+                       (m ? (uintptr_t)m->src | (uintptr_t)m->buf : 0);
   if (rb % 16 == 0 && al % 16 == 0)
     vec = 16;
   else if (rb % 8 == 0 && al % 8 == 0)
@@ -422,23 +434,25 @@ void launch_gather(massive_ctx* c, int group, GatherKind kind, hipStream_t s, co
   const uint64_t magic = cpr > 1 ? (~0ull) / cpr + 1 : 0;
   const uint64_t bound = (uint64_t)std::max<int64_t>(max_rows, 1);
   const int64_t chunks = (int64_t)bound * cpr;
-  const unsigned grid = grid_for(chunks / 4, 256, max_blocks);
-#define MS_ONE(V, ONE)                                                                                         \
-  do {                                                                                                         \
-    if (kind == kHbm) {                                                                                        \
-      if (timed)                                                                                               \
-        hipExtLaunchKernelGGL(ms::k_gather_hbm<V, ONE>, dim3(grid), dim3(256), 0, s, ea, eb, 0, list, count, bound, src, \
-                              dst, rb, cpr, magic);                                                            \
-      else                                                                                                     \
-        ms::k_gather_hbm<V, ONE><<<grid, 256, 0, s>>>(list, count, bound, src, dst, rb, cpr, magic);                  \
-    } else {                                                                                                   \
-      if (timed)                                                                                               \
-        hipExtLaunchKernelGGL(ms::k_gather_miss<V, ONE>, dim3(grid), dim3(256), 0, s, ea, eb, 0, list, wslot,  \
-                              count, src, dst, buf, c->d_dummy, rb, cpr, magic, *tail);                       \
-      else                                                                                                     \
-        ms::k_gather_miss<V, ONE><<<grid, 256, 0, s>>>(list, wslot, count, src, dst, buf, c->d_dummy, rb, cpr, \
-                                                       magic, *tail);                                          \
-    }                                                                                                          \
+  const unsigned hbm_grid = grid_for(chunks / 4, 256, c->hbm_blocks), host_grid = grid_for(chunks / 4, 256, host_blocks);
+#define MS_ONE(V, ONE)                                                                                          \
+  do {                                                                                                          \
+    if (kind == kHbm) {                                                                                         \
+      if (timed)                                                                                                \
+        hipExtLaunchKernelGGL(ms::k_gather_hbm<V, ONE>, dim3(hbm_grid), dim3(256), 0, s, ea, eb, 0, list, count, \
+                              bound, slab, dst, rb, cpr, magic);                                                \
+      else                                                                                                      \
+        ms::k_gather_hbm<V, ONE><<<hbm_grid, 256, 0, s>>>(list, count, bound, slab, dst, rb, cpr, magic);       \
+    } else if (kind == kMiss) {                                                                                 \
+      if (timed)                                                                                                \
+        hipExtLaunchKernelGGL(ms::k_gather_miss<V, ONE>, dim3(host_grid), dim3(256), 0, s, ea, eb, 0, *m, rb, cpr, \
+                              magic);                                                                           \
+      else                                                                                                      \
+        ms::k_gather_miss<V, ONE><<<host_grid, 256, 0, s>>>(*m, rb, cpr, magic);                                \
+    } else {                                                                                                    \
+      ms::k_gather_both<V, ONE><<<host_grid + hbm_grid, 256, 0, s>>>(*m, host_grid, list, count, slab, rb, cpr, \
+                                                                     magic);                                    \
+    }                                                                                                           \
   } while (0)
 #define MS_KIND(V)          \
   do {                      \
@@ -1159,10 +1173,11 @@ int massive_output_bounds(const massive_ctx* c, int32_t n_seeds, int64_t* n_boun
 namespace {
 
 // Per-step buffers of one enqueued step: those of the context's step slot,
-// or the no-alloc scratch array (then its scan flags are cleared per call,
-// fill kernels clear it, and nothing is timed).
+// or the no-alloc scratch array (then nothing is timed).
 struct StepBufs {
   ms::StepSizes* sz;
+  ms::StepSizes* next_sz;  // the next step's sizes, to be cleared (or nullptr)
+  uint32_t epoch;          // of the seed rows' scan
   int2* hbm_list;
   int2* miss_list;
   int32_t* miss_slot;
@@ -1231,34 +1246,25 @@ void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream
 #undef MS_FR
 }
 
-// Enqueues one step (sampling and classify on the main stream, the gathers
-// and the step's completion on the side stream) with the per-step buffers sb.
+// Enqueues one step with the per-step buffers sb: sampling and classify on the
+// main stream, the gathers and the step's completion on the side stream. A
+// step that is waited for at once (`alone`: no other batch in flight, loads
+// link) has no next step to make room for: it stays on the main stream, with
+// both gathers in one launch unless a refill chunk is to run after the HBM one
+// or either is timed. That spares the cross-stream wait (~8 us), the gap
+// between the gathers (~5 us) and the HBM gather's time behind the link's: us
+// per step, before -> after, 16 seeds on the 170K-node graph (no-alloc, whose
+// two clearing launches went too) 117 -> 93, 1024 seeds there 434 -> 408, on
+// the 111M-node share 645 -> 587.
 int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch* io, const int64_t* nb,
-                 const int64_t* eb, const StepBufs& sb) {
+                 const int64_t* eb, const StepBufs& sb, bool alone) {
   hipStream_t s = c->s_main;
   const int slot = (int)(c->t % kSlots);
   ms::StepSizes* sz = sb.sz;
   int2* miss_list = sb.miss_list;
   const uint32_t key0 = (uint32_t)c->seed, key1 = (uint32_t)(c->seed >> 32);
-  // this slot's sizes and lists were last used by the side stream kSlots
-  // steps ago (complete: that batch was waited for)
-  CK(hipStreamWaitEvent(s, c->ev_batch_done[slot], 0));
-  // the scratch array may be shared with other contexts on this device: its
-  // scan flags are cleared here (any epoch from 1 on is then fresh), and it is
-  // cleared by fill kernels (nothing that a captured graph would replay wrongly)
-  uint32_t scratch_epoch = 0;
-  auto epoch = [&]() { return sb.from_scratch ? ++scratch_epoch : next_scan_epoch(c, s); };
-  if (sb.from_scratch) {
-    ms::k_fill<int32_t><<<1, 256, 0, s>>>(reinterpret_cast<int32_t*>(sz), (int64_t)(sizeof(ms::StepSizes) / 4), 0);
-    const int64_t words = std::max(cdiv(nb[c->K], ms::kScanTile), cdiv(c->W, ms::kScanTile)) + 1;
-    ms::k_fill<uint64_t><<<grid_for(words, 256, 64), 256, 0, s>>>(sb.flags, words, 0ull);
-  } else if (!c->slot_clear[slot]) {
-    // (a slot's sizes are cleared by the miss gather of the step that last
-    // used it; the staged link and a context without halo nodes end a step
-    // with k_step_done, which does not clear them)
-    CK(hipMemsetAsync(sz, 0, sizeof(ms::StepSizes), s));
-  }
-  if (!sb.from_scratch) c->slot_clear[slot] = false;
+  // (this slot's sizes and lists were last used kSlots steps ago: complete, as
+  // that batch was waited for)
   {
     massive_ctx::Range tr(c, s, 0);
     const FrontierShape fs = frontier_shape(c->W);
@@ -1266,8 +1272,9 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     {
       const int64_t nbk = std::max<int64_t>(1, cdiv(nb[0], ms::kScanTile));
       ms::k_seed_rows<<<(unsigned)nbk, ms::kScanNT, 0, s>>>(
-          c->d_indptr, seeds, n0, c->L, io->nodes, sz, c->fo[0], io->indptr[0], sb.flags, epoch(), c->d_pos_of,
-          c->d_seen, c->d_rec, sb.big, c->big_min, nb[0] > ms::kBlockRowsMax ? nb[0] : 0);
+          c->d_indptr, seeds, n0, c->L, io->nodes, sz, c->fo[0], io->indptr[0], sb.flags, sb.epoch, c->d_pos_of,
+          c->d_seen, c->d_rec, sb.big, c->big_min, nb[0] > ms::kBlockRowsMax ? nb[0] : 0,
+          reinterpret_cast<int32_t*>(sb.next_sz));
     }
     for (int k = 1; k <= c->K; ++k) {
       const int64_t nprev = nb[k - 1];
@@ -1412,18 +1419,38 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     }
     ms::k_classify<<<ca.cls_blocks + ca.rel_first[c->K], ms::kClsNT, 0, s>>>(ca);
   }
-  CK(hipEventRecord(c->ev_cls_done[slot], s));
   // The gathers run on the side stream, so the main stream goes on to the
   // next step's sampling at once. HBM rows first, at full bandwidth: after the
   // previous step's miss gather (stream order) and the last refill chunk, as
   // concurrent host-link reads would throttle them; then the host-link rows,
   // beside the refill chunk launched after the HBM gather.
-  hipStream_t sm = c->s_miss;
-  CK(hipStreamWaitEvent(sm, c->ev_cls_done[slot], 0));
+  hipStream_t sm = alone ? s : c->s_miss;
+  if (!alone) {
+    CK(hipEventRecord(c->ev_cls_done[slot], s));
+    CK(hipStreamWaitEvent(sm, c->ev_cls_done[slot], 0));
+  }
   if (c->refill_inflight) CK(hipStreamWaitEvent(sm, c->ev_refill_done, 0));
-  launch_gather(c, 2, kHbm, sm, sb.hbm_list, &sz->n_hbm, c->d_slab, (uint8_t*)io->feat, c->rb, nb[c->K],
-                c->hbm_blocks);
-  CK(hipEventRecord(c->ev_hbm_done[slot], sm));
+  // the miss gather ends the step: it stamps the slots it writes through as
+  // landed and publishes the step's sizes to the host mailbox (a context
+  // without halo nodes publishes them with a kernel of its own)
+  const bool both = alone && c->H > 0 && c->chunks_left == 0 && !(c->timing & 0xC);
+  ms::MissArgs ma;
+  ma.list = miss_list;
+  ma.wslot = sb.miss_slot;
+  ma.count = &sz->n_miss;
+  ma.bound = (uint64_t)std::max<int64_t>(nb[c->K], 1);
+  ma.src = c->d_store;
+  ma.dst = (uint8_t*)io->feat;
+  ma.buf = c->d_slab + (int64_t)c->L * c->rb;
+  ma.dummy = c->d_dummy;
+  ma.tail = ms::StepTail{sz, c->K, &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot, c->d_landed, c->cap, pend,
+                         !both && !sb.from_scratch};
+  if (both) {
+    launch_gather(c, kBoth, sm, sb.hbm_list, &sz->n_hbm, (uint8_t*)io->feat, nb[c->K], c->host_blocks, &ma);
+  } else {
+    launch_gather(c, kHbm, sm, sb.hbm_list, &sz->n_hbm, (uint8_t*)io->feat, nb[c->K], 0, nullptr);
+    CK(hipEventRecord(c->ev_hbm_done[slot], sm));
+  }
   if (c->staged()) {
     // the host rows go to the worker, which enqueues the rest of the step
     // (and then one refill chunk) on the link stream
@@ -1454,25 +1481,20 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     c->pending_round = true;
     return MASSIVE_OK;
   }
-  {
+  if (!both) {
     int rc = launch_refill_chunks(c, 1, c->ev_hbm_done[slot]);
     if (rc != MASSIVE_OK) return rc;
+    if (c->H > 0) {
+      const bool heavy = alone || c->round_pending_rows || c->host_rows_seen < 0 ||
+                         c->host_rows_seen * c->rb > kLinkHeavyBytes;
+      launch_gather(c, kMiss, sm, nullptr, nullptr, (uint8_t*)io->feat, nb[c->K],
+                    heavy ? c->host_blocks : c->host_blocks_light, &ma);
+      if (!sb.from_scratch) c->slot_clear[slot] = true;
+    } else {
+      ms::k_step_done<<<1, 256, 0, sm>>>(sb.miss_slot, &sz->n_miss, c->d_landed, c->cap, -1, sz, c->K,
+                                         &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot);
+    }
   }
-  // the miss gather ends the step: it stamps the slots it writes through as
-  // landed and publishes the step's sizes to the host mailbox (a context
-  // without halo nodes publishes them with a kernel of its own)
-  const ms::StepTail tail{sz, c->K, &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot, c->d_landed, c->cap,
-                          pend, 1};
-  if (c->H > 0) {
-    const bool heavy = c->round_pending_rows || c->host_rows_seen < 0 || c->host_rows_seen * c->rb > kLinkHeavyBytes;
-    launch_gather(c, 3, kMiss, sm, miss_list, &sz->n_miss, c->d_store, (uint8_t*)io->feat, c->rb, nb[c->K],
-                  heavy ? c->host_blocks : c->host_blocks_light, sb.miss_slot, c->d_slab + (int64_t)c->L * c->rb,
-                  &tail);
-    if (!sb.from_scratch) c->slot_clear[slot] = true;
-  }
-  else
-    ms::k_step_done<<<1, 256, 0, sm>>>(sb.miss_slot, &sz->n_miss, c->d_landed, c->cap, -1, sz, c->K,
-                                       &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot);
   // (also the miss gather's completion, which the next round's refill follows)
   CK(hipEventRecord(c->ev_batch_done[slot], sm));
   CK(hipGetLastError());
@@ -1485,25 +1507,46 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
   return MASSIVE_OK;
 }
 
+bool any_in_flight(const massive_ctx* c) {
+  for (const auto& f : c->infl)
+    if (f.io) return true;
+  return false;
+}
+
+// massive_sample_async, and the first half of massive_sample (`waited`).
+int sample_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch* io, bool waited) {
+  if (!c) return MASSIVE_EINVAL;
+  int64_t nb[MASSIVE_MAX_HOPS + 1], eb[MASSIVE_MAX_HOPS];
+  int rc = check_step_args(c, seeds, n0, io, nb, eb);
+  if (rc != MASSIVE_OK) return rc;
+  const int slot = (int)(c->t % kSlots), next = (slot + 1) % kSlots;
+  if (c->infl[slot].io)
+    return c->fail(MASSIVE_ESTATE, "%d batches in flight: wait for the oldest one first", kSlots);
+  StepBufs sb{c->d_sz + slot, nullptr, next_scan_epoch(c, c->s_main), c->d_hbm_list[slot], c->d_miss_list[slot],
+              c->d_miss_slot[slot], c->d_big, c->d_scan_flags, false};
+  // A slot's sizes are cleared by the miss gather of the step that last used
+  // it, or, where that did not (both gathers in one launch, the staged link, no
+  // halo), by the step before its next one once it is no longer in flight.
+  if (!c->slot_clear[next] && !c->infl[next].io) sb.next_sz = c->d_sz + next;
+  if (!c->slot_clear[slot])
+    rc = hipMemsetAsync(sb.sz, 0, sizeof(ms::StepSizes), c->s_main) == hipSuccess
+             ? MASSIVE_OK
+             : c->fail(MASSIVE_EHIP, "clearing the step's sizes failed");
+  c->slot_clear[slot] = false;
+  if (sb.next_sz) c->slot_clear[next] = true;
+  if (rc == MASSIVE_OK) rc = enqueue_step(c, seeds, n0, io, nb, eb, sb, waited && !c->staged() && !any_in_flight(c));
+  // a HIP call that failed part-way left work on the queues that no batch
+  // tracks: the context takes no further work
+  if (rc == MASSIVE_EHIP) c->broken = true;
+  return rc;
+}
+
 }  // namespace
 
 extern "C" {
 
 int massive_sample_async(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch* io) {
-  if (!c) return MASSIVE_EINVAL;
-  int64_t nb[MASSIVE_MAX_HOPS + 1], eb[MASSIVE_MAX_HOPS];
-  int rc = check_step_args(c, seeds, n0, io, nb, eb);
-  if (rc != MASSIVE_OK) return rc;
-  const int slot = (int)(c->t % kSlots);
-  if (c->infl[slot].io)
-    return c->fail(MASSIVE_ESTATE, "%d batches in flight: wait for the oldest one first", kSlots);
-  const StepBufs sb{c->d_sz + slot, c->d_hbm_list[slot], c->d_miss_list[slot], c->d_miss_slot[slot], c->d_big,
-                    c->d_scan_flags, false};
-  rc = enqueue_step(c, seeds, n0, io, nb, eb, sb);
-  // a HIP call that failed part-way left work on the queues that no batch
-  // tracks: the context takes no further work
-  if (rc == MASSIVE_EHIP) c->broken = true;
-  return rc;
+  return sample_step(c, seeds, n0, io, false);
 }
 
 int massive_batch_wait(massive_ctx* c, massive_batch* io) {
@@ -1519,7 +1562,10 @@ int massive_batch_wait(massive_ctx* c, massive_batch* io) {
     const int rc = link_wait(c, [c, st] { return c->tail_step >= st; });
     if (rc != MASSIVE_OK) return rc;
   }
-  CK(hipEventSynchronize(c->ev_batch_done[slot]));
+  if (const hipError_t e = hipEventSynchronize(c->ev_batch_done[slot]); e != hipSuccess) {
+    c->broken = true;  // (the slot's buffers may still be in use)
+    return c->fail(MASSIVE_EHIP, "hipEventSynchronize: %s", hipGetErrorString(e));
+  }
   // Steps issued before this one and still in flight decide whether it is
   // valid: a step that failed on the device skipped its dedup scan and its
   // classify, so its bitmap marks and frontier positions stayed set, and every
@@ -1575,7 +1621,7 @@ int massive_batch_wait(massive_ctx* c, massive_batch* io) {
 }
 
 int massive_sample(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch* io) {
-  int rc = massive_sample_async(c, seeds, n0, io);
+  int rc = sample_step(c, seeds, n0, io, true);
   if (rc != MASSIVE_OK) return rc;
   return massive_batch_wait(c, io);
 }
@@ -1585,34 +1631,53 @@ int massive_sample_noalloc(massive_ctx* c, const int32_t* seeds, int32_t n0, mas
   int64_t nb[MASSIVE_MAX_HOPS + 1], eb[MASSIVE_MAX_HOPS];
   int rc = check_step_args(c, seeds, n0, io, nb, eb);
   if (rc != MASSIVE_OK) return rc;
-  for (int i = 0; i < kSlots; ++i)
-    if (c->infl[i].io) return c->fail(MASSIVE_ESTATE, "a batch is in flight: wait for it before a no-alloc step");
+  if (any_in_flight(c)) return c->fail(MASSIVE_ESTATE, "a batch is in flight: wait for it before a no-alloc step");
   if (nb[c->K] > kNoAllocMaxRows)
     return c->fail(MASSIVE_ECAPACITY, "the no-alloc scratch holds %lld frontier rows, this batch's bound is %lld "
                                       "(massive_sample has no such limit)",
                    (long long)kNoAllocMaxRows, (long long)nb[c->K]);
-  const int64_t words = std::max(cdiv(nb[c->K], ms::kScanTile), cdiv(c->W, ms::kScanTile)) + 1;
-  if (words > kNoAllocFlagWords)
-    return c->fail(MASSIVE_ECAPACITY, "the no-alloc scratch holds %lld scan flags, this step needs %lld",
-                   (long long)kNoAllocFlagWords, (long long)words);
   if (!c->d_scratch) return c->fail(MASSIVE_EHIP, "the no-alloc scratch has no device address");
   uint8_t* base = c->d_scratch;
   StepBufs sb;
-  sb.sz = reinterpret_cast<ms::StepSizes*>(base);
-  sb.hbm_list = reinterpret_cast<int2*>(base + 512);
+  ms::StepSizes* sizes[2] = {reinterpret_cast<ms::StepSizes*>(base), reinterpret_cast<ms::StepSizes*>(base + 512)};
+  bool unclear;
+  {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    ScratchState& st = g_scratch[c->device];
+    sb.sz = sizes[st.turn];
+    sb.next_sz = sizes[st.turn ^ 1];
+    st.turn ^= 1;
+    if (st.epoch >= (1u << 30)) {
+      st.epoch = 0;
+      st.unclear = true;
+    }
+    sb.epoch = ++st.epoch;
+    unclear = st.unclear;
+    st.unclear = true;  // until this call has succeeded
+  }
+  sb.hbm_list = reinterpret_cast<int2*>(base + 1024);
   sb.miss_list = sb.hbm_list + kNoAllocMaxRows;
   sb.miss_slot = reinterpret_cast<int32_t*>(sb.miss_list + kNoAllocMaxRows);
   sb.big = sb.miss_slot + kNoAllocMaxRows;
   sb.flags = reinterpret_cast<uint64_t*>(sb.big + kNoAllocMaxRows);
   sb.from_scratch = true;
+  if (unclear) {  // (fill kernels: nothing that a captured graph would replay wrongly)
+    ms::k_fill<int32_t><<<1, 256, 0, c->s_main>>>(reinterpret_cast<int32_t*>(base), 1024 / 4, 0);
+    ms::k_fill<uint64_t><<<64, 256, 0, c->s_main>>>(sb.flags, kNoAllocFlagWords, 0ull);
+  }
   // timing events are created on demand: this path records none
   const int timing = c->timing;
   c->timing = 0;
-  rc = enqueue_step(c, seeds, n0, io, nb, eb, sb);
+  rc = enqueue_step(c, seeds, n0, io, nb, eb, sb, !c->staged());
   c->timing = timing;
   if (rc == MASSIVE_EHIP) c->broken = true;  // as in massive_sample_async
   if (rc != MASSIVE_OK) return rc;
-  return massive_batch_wait(c, io);
+  rc = massive_batch_wait(c, io);
+  if (rc == MASSIVE_OK) {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    g_scratch[c->device].unclear = false;
+  }
+  return rc;
 }
 
 }  // extern "C"
@@ -1655,7 +1720,9 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
     if (rc != MASSIVE_OK) return rc;
   }
   c->round_pending_rows = false;
-  CK(hipStreamWaitEvent(s, c->ev_hbm_done[tl % kSlots], 0));
+  // (a step that was waited for has nothing left to wait for)
+  const bool step_in_flight = c->infl[tl % kSlots].io != nullptr;
+  if (step_in_flight) CK(hipStreamWaitEvent(s, c->ev_hbm_done[tl % kSlots], 0));
   {
     massive_ctx::Range tr(c, s, 4);
     ms::k_materialize<<<grid_for(cap, 256), 256, 0, s>>>(c->d_S_E, c->d_hitcnt, cap, (int32_t)(c->t - c->mat_t),
@@ -1735,7 +1802,7 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
   // replacements into slots this round reassigns, so the new refill comes after
   // it (in the staged mode the link stream orders them: the worker enqueues
   // the new chunks after that step's tail)
-  if (!c->staged()) CK(hipStreamWaitEvent(s, c->ev_batch_done[tl % kSlots], 0));
+  if (!c->staged() && step_in_flight) CK(hipStreamWaitEvent(s, c->ev_batch_done[tl % kSlots], 0));
   c->chunks_left = c->refill_chunks;
   c->round_pending_rows = true;
   CK(hipGetLastError());

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
                                                        int32_t* __restrict__ bptr, uint64_t* flags, uint32_t epoch,
                                                        int32_t* __restrict__ pos_of, uint32_t* __restrict__ seen,
                                                        v4r* __restrict__ rec, int32_t* __restrict__ big_rows,
-                                                       int64_t big_min, int64_t small_end) {
+                                                       int64_t big_min, int64_t small_end, int32_t* next_sizes) {
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
   __shared__ int32_t big_lds[kScanTile];  // long rows from the front, the others from the back
   __shared__ int32_t big_n, small_n;
@@ -112,6 +112,7 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
   // (the step's sizes are clear here: no status to check)
   const int64_t n = n0;
   if (blockIdx.x == 0 && threadIdx.x == 0) sz->n[0] = n;
+  if (blockIdx.x == 0 && next_sizes && threadIdx.x < sizeof(StepSizes) / 4) next_sizes[threadIdx.x] = 0;
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   if (threadIdx.x == 0) big_n = small_n = 0;
   __syncthreads();
