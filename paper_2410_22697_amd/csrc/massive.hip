@@ -133,6 +133,7 @@ struct massive_ctx {
   bool slot_clear[MASSIVE_MAX_INFLIGHT] = {};  // the slot's sizes were cleared by its last step's miss gather
   int64_t refill_blocks = 16; // grid of the refill (host link, off the critical path)
   double mu32[MASSIVE_MAX_HOPS] = {};    // sampler threshold targets, x 2^32
+  int quad_slots[MASSIVE_MAX_HOPS] = {};  // the sampler's candidate list (ms::quad_slots)
   int32_t* d_big = nullptr;             // row list of the current hop (long rows first)
   int64_t big_min = ms::kBigRow;        // rows longer than this are sampled by a whole block
   int64_t big_blocks = ms::kBigBlocks;  // blocks that walk the list of such rows (at most)
@@ -884,6 +885,7 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
     const double fo = a->fanout[k];
     const double mu = std::min(fo + 3.0 * std::sqrt(fo) + 3.0, 0.5 * (fo + ms::kCandCap));
     c->mu32[k] = mu * 4294967296.0;
+    c->quad_slots[k] = ms::quad_slots(mu);
   }
 
   if (const char* e = getenv("MASSIVE_HBM_BLOCKS")) c->hbm_blocks = std::max(1, atoi(e));
@@ -1229,6 +1231,35 @@ int check_step_args(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_ba
   return MASSIVE_OK;
 }
 
+// Timed if ea is given (hipExtLaunchKernelGGL's events around the dispatch).
+void launch_sampler(bool by_waves, int quads, unsigned grid, hipStream_t s, hipEvent_t ea, hipEvent_t eb,
+                    const ms::SampleArgs& sa) {
+  const dim3 block((by_waves ? ms::kRowWaves : ms::kSampleWaves) * MS_WAVE);
+#define MS_SAMPLE(KERNEL)                                                      \
+  do {                                                                         \
+    if (ea)                                                                    \
+      hipExtLaunchKernelGGL(KERNEL, dim3(grid), block, 0, s, ea, eb, 0, sa);   \
+    else                                                                       \
+      KERNEL<<<grid, block, 0, s>>>(sa);                                       \
+  } while (0)
+  if (by_waves) {
+    if (quads == 1)
+      MS_SAMPLE(ms::k_sample_waves<1>);
+    else if (quads == 2)
+      MS_SAMPLE(ms::k_sample_waves<2>);
+    else
+      MS_SAMPLE(ms::k_sample_waves<0>);
+  } else {
+    if (quads == 1)
+      MS_SAMPLE(ms::k_sample_blocks<1>);
+    else if (quads == 2)
+      MS_SAMPLE(ms::k_sample_blocks<2>);
+    else
+      MS_SAMPLE(ms::k_sample_blocks<0>);
+  }
+#undef MS_SAMPLE
+}
+
 void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream_t s, const ms::FrontierArgs& fa) {
 #define MS_FR(NT, TW)                                         \
   do {                                                        \
@@ -1309,20 +1340,14 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
       if (!by_waves) {
         sa.row_waves = 0;
         sa.big_blocks = std::min(std::min(nprev, c->long_rows), c->big_blocks);
-        const dim3 grid((unsigned)(sa.big_blocks + std::max<int64_t>(1, cdiv(nprev, ms::kSampleWaves))));
-        if (timed)
-          hipExtLaunchKernelGGL(ms::k_sample_blocks, grid, dim3(ms::kSampleWaves * MS_WAVE), 0, s, hop_a, hop_b, 0, sa);
-        else
-          ms::k_sample_blocks<<<grid, ms::kSampleWaves * MS_WAVE, 0, s>>>(sa);
       } else {
         sa.row_waves = nprev;  // the row list (nprev entries at most) ends there
         sa.big_blocks = 0;
-        const dim3 grid((unsigned)std::max<int64_t>(1, cdiv(nprev, ms::kRowWaves)));
-        if (timed)
-          hipExtLaunchKernelGGL(ms::k_sample_waves, grid, dim3(ms::kRowWaves * MS_WAVE), 0, s, hop_a, hop_b, 0, sa);
-        else
-          ms::k_sample_waves<<<grid, ms::kRowWaves * MS_WAVE, 0, s>>>(sa);
       }
+      const int64_t grid =
+          by_waves ? cdiv(std::min(nprev, ms::kRowWavesMax), ms::kRowWaves)
+                   : sa.big_blocks + std::max<int64_t>(1, cdiv(nprev, ms::kSampleWaves));
+      launch_sampler(by_waves, c->quad_slots[k - 1], (unsigned)grid, s, timed ? hop_a : nullptr, hop_b, sa);
       if (timed) c->pending.push_back({hop_a, hop_b, 6});
       ms::FrontierArgs fa = {};
       fa.bits = c->d_bits;

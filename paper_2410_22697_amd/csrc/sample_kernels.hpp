@@ -247,6 +247,7 @@ constexpr int kCandCap = kCandSlots * MS_WAVE;  // candidates per wave (LDS): 32
 constexpr int64_t kBigRow = 2048;
 constexpr int64_t kBigBlocks = 2048;  // blocks that walk the big list (8 per CU)
 constexpr int64_t kBlockRowsMax = 65536;  // frontiers up to this size sample long rows by blocks
+constexpr int64_t kRowWavesMax = 131072;  // waves of k_sample_waves at most
 constexpr int kTauIters = 64;         // threshold passes: x4 growth (<= 16) then bisection (<= 33)
 
 struct SampleArgs {
@@ -511,93 +512,254 @@ __device__ __forceinline__ int filter_groups(const PhiloxRow& ph, uint32_t g0, u
   return cnt;
 }
 
+// ---- rows of quads: the choice among whole Philox blocks
+// A quad is one Philox block: the keys of positions 4q..4q+3. The usual fanouts
+// keep few candidates per row, each in a quad of its own, so the filter keeps
+// whole quads (no compaction of the single keys: an iteration with a candidate
+// costs ~6 vector instructions more than one without, 17 when the candidates
+// were picked apart), and the choice is made among the quads' keys in
+// registers, one quad per lane and slot.
+constexpr uint32_t kShortRow = 4 * MS_WAVE;  // a row of one iteration: its quads never leave the registers
+
+template <int QS>
+struct QuadList {
+  static constexpr int kCap = QS * MS_WAVE;
+  uint4 k[kCap];
+  uint32_t q[kCap];
+};
+
+// Quads slots a fanout needs so that first thresholds (mu survivors expected)
+// hardly ever overflow them: five standard deviations of room; 0: the list of
+// single keys.
+inline int quad_slots(double mu) {
+  const double most = mu + 5.0 * sqrt(mu);
+  return most <= MS_WAVE ? 1 : most <= 2 * MS_WAVE ? 2 : 0;
+}
+
+// Filters groups [g0, g1) of a row of d positions: appends to l, in ascending
+// q, the quads with a key <= tm1 (keys of positions past the row's end count as
+// the largest key; the choice drops them), storing at most kCap of them but
+// counting them all. One wavefront.
+template <int QS>
+__device__ __forceinline__ int filter_quads(const PhiloxRow& ph, uint32_t g0, uint32_t g1, uint32_t d32, uint32_t tm1,
+                                            QuadList<QS>& l) {
+  const int lane = lane_id();
+  int n = 0;
+  const uint32_t gf = min(g1, d32 / 4);  // groups below gf are whole
+  uint64_t a1 = (uint64_t)0xD2511F53u * (g0 + lane);
+  for (uint32_t q0 = g0; q0 < g1; q0 += MS_WAVE, a1 += (uint64_t)0xD2511F53u * MS_WAVE) {
+    const uint32_t q = q0 + lane;
+    uint4 k = ph.from_a1(a1);
+    bool has;
+    if (q0 + MS_WAVE <= gf) {  // every position of this iteration exists
+      has = min4(k) <= tm1;
+    } else {
+      k.y = 4 * q + 1 < d32 ? k.y : ~0u;
+      k.z = 4 * q + 2 < d32 ? k.z : ~0u;
+      k.w = 4 * q + 3 < d32 ? k.w : ~0u;
+      has = q < g1 && min4(k) <= tm1;
+    }
+    const uint64_t m = ballot(has);
+    if (!m) continue;
+    const int p = n + lanes_below(m);
+    if (has && p < QuadList<QS>::kCap) {
+      l.k[p] = k;
+      l.q[p] = q;
+    }
+    n += __popcll(m);
+  }
+  return n;
+}
+
+// The quads of a lane, as the choice reads them: the keys of positions that do
+// not count (past the row's end, above tm1, no quad) are set to the largest
+// key, and `valid` has a bit for each that does.
+template <int QS>
+struct LaneQuads {
+  uint4 k[QS];
+  uint32_t q[QS];
+  uint32_t valid[QS];
+  int total;  // valid keys of the wave
+
+  __device__ __forceinline__ void set(int s, bool in, uint4 k4, uint32_t q_, uint32_t d32, uint32_t tm1) {
+    q[s] = q_;
+    const bool v0 = in && 4 * q_ < d32 && k4.x <= tm1, v1 = in && 4 * q_ + 1 < d32 && k4.y <= tm1;
+    const bool v2 = in && 4 * q_ + 2 < d32 && k4.z <= tm1, v3 = in && 4 * q_ + 3 < d32 && k4.w <= tm1;
+    k[s] = make_uint4(v0 ? k4.x : ~0u, v1 ? k4.y : ~0u, v2 ? k4.z : ~0u, v3 ? k4.w : ~0u);
+    valid[s] = (v0 ? 1u : 0u) | (v1 ? 2u : 0u) | (v2 ? 4u : 0u) | (v3 ? 8u : 0u);
+    total += __popcll(ballot(v0)) + __popcll(ballot(v1)) + __popcll(ballot(v2)) + __popcll(ballot(v3));
+  }
+  __device__ __forceinline__ void read(const QuadList<QS>& l, int n, uint32_t d32, uint32_t tm1) {
+    total = 0;
+#pragma unroll
+    for (int s = 0; s < QS; ++s) {
+      const int i = s * MS_WAVE + lane_id();
+      const bool in = i < n;
+      set(s, in, in ? l.k[i] : make_uint4(~0u, ~0u, ~0u, ~0u), in ? l.q[i] : 0u, d32, tm1);
+    }
+  }
+  __device__ __forceinline__ int below(uint32_t x) const {
+    int c = 0;
+#pragma unroll
+    for (int s = 0; s < QS; ++s)
+      c += __popcll(ballot(k[s].x < x)) + __popcll(ballot(k[s].y < x)) + __popcll(ballot(k[s].z < x)) +
+           __popcll(ballot(k[s].w < x));
+    return c;
+  }
+};
+
+// Chooses the fo smallest (key, j) of total >= fo valid keys, all <= tm1, and
+// writes their neighbours to out in ascending j. A bisection looks for a bound
+// below which exactly fo keys lie (with n keys about log2(n) + 1 steps: the
+// bound only has to fall between the fo-th key and the next), and ends at the
+// fo-th key itself where ties leave no such bound; the ties are then taken in
+// ascending j.
+template <int QS>
+__device__ __forceinline__ void choose_quads(const LaneQuads<QS>& c, int fo, uint32_t tm1,
+                                             const int32_t* __restrict__ nb, int32_t* __restrict__ out,
+                                             uint32_t* __restrict__ bits) {
+  uint32_t sel[QS];
+  bool exact = c.total == fo;
+  uint32_t lo = 0, hi = tm1, x = 0;
+  if (!exact) {
+    while (lo < hi) {  // fewer than fo keys below lo, more than fo at or below hi
+      x = lo + ((hi - lo) >> 1) + 1;
+      const int n = c.below(x);
+      if (n == fo) {
+        exact = true;
+        break;
+      }
+      if (n < fo)
+        lo = x;
+      else
+        hi = x - 1;
+    }
+    if (!exact) x = lo;
+#pragma unroll
+    for (int s = 0; s < QS; ++s)
+      sel[s] = (c.k[s].x < x ? 1u : 0u) | (c.k[s].y < x ? 2u : 0u) | (c.k[s].z < x ? 4u : 0u) | (c.k[s].w < x ? 8u : 0u);
+  } else {
+#pragma unroll
+    for (int s = 0; s < QS; ++s) sel[s] = c.valid[s];
+  }
+  if (!exact) {
+    int need = fo - c.below(x);
+#pragma unroll
+    for (int s = 0; s < QS; ++s) {
+      const uint32_t eq = c.valid[s] & ((c.k[s].x == x ? 1u : 0u) | (c.k[s].y == x ? 2u : 0u) |
+                                        (c.k[s].z == x ? 4u : 0u) | (c.k[s].w == x ? 8u : 0u));
+      const uint64_t m0 = ballot(eq & 1u), m1 = ballot(eq & 2u), m2 = ballot(eq & 4u), m3 = ballot(eq & 8u);
+      int r = lanes_below(m0) + lanes_below(m1) + lanes_below(m2) + lanes_below(m3);
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+        if (eq & (1u << y)) {
+          if (r < need) sel[s] |= 1u << y;
+          ++r;
+        }
+      need -= __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
+    }
+  }
+  int before = 0;
+#pragma unroll
+  for (int s = 0; s < QS; ++s) {
+    const uint64_t m0 = ballot(sel[s] & 1u), m1 = ballot(sel[s] & 2u), m2 = ballot(sel[s] & 4u),
+                   m3 = ballot(sel[s] & 8u);
+    int p = before + lanes_below(m0) + lanes_below(m1) + lanes_below(m2) + lanes_below(m3);
+    for (uint32_t y = sel[s]; y; y &= y - 1, ++p) emit_id(out, p, nb[4 * c.q[s] + __ffs(y) - 1], bits);
+    before += __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
+  }
+}
+
+// LDS of one wave's row.
+template <int QS>
+struct WaveList {
+  QuadList<QS> l;
+};
+template <>
+struct WaveList<0> {
+  uint64_t c[kCandCap];
+};
+
+// One row by one wavefront: its record r, its offset in the output at. QS:
+// quad slots per lane (0: the list of single keys).
+template <int QS>
+__device__ __forceinline__ void sample_row_wave(const SampleArgs& a, const Row& r, int64_t at, WaveList<QS>& w) {
+  const int lane = lane_id();
+  const int32_t fo = a.fo;
+  const uint32_t d = r.d;
+  int32_t* out = a.out + at;
+  const int32_t* nb = a.csr_indices + r.start;
+  if (d <= (uint32_t)fo) {
+    for (uint32_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.bits);
+    return;
+  }
+  const PhiloxRow ph((uint32_t)r.v, a.t, (uint32_t)a.hop, a.key0, a.key1);
+  if (d <= kShortRow && a.tau_iters > 0) {
+    // every key of the row is in the wave's registers: no threshold needed
+    LaneQuads<1> c;
+    c.total = 0;
+    c.set(0, true, ph.from_a1((uint64_t)0xD2511F53u * (uint32_t)lane), (uint32_t)lane, d, ~0u);
+    choose_quads<1>(c, fo, ~0u, nb, out, a.bits);
+    return;
+  }
+  TauSearch ts;
+  ts.tau = first_tau(a.mu32, (int64_t)d);
+  bool fail = false;
+  for (int iter = 0; iter < a.tau_iters && !fail; ++iter) {
+    const uint32_t tm1 = (uint32_t)(ts.tau - 1);
+    if constexpr (QS > 0) {
+      const int n = filter_quads<QS>(ph, 0, (d + 3) / 4, d, tm1, w.l);
+      LaneQuads<QS> c;
+      c.total = INT32_MAX;  // more quads than the list holds
+      if (n <= QuadList<QS>::kCap) {
+        wave_lds_sync();
+        c.read(w.l, n, d, tm1);
+      }
+      if (ts.step(c.total, fo, 4 * QuadList<QS>::kCap, &fail)) {
+        choose_quads<QS>(c, fo, tm1, nb, out, a.bits);
+        return;
+      }
+      wave_lds_sync();  // the next pass rewrites the list
+    } else {
+      const int cnt = filter_groups(ph, 0, (d + 3) / 4, d, tm1, w.c);
+      if (ts.step(cnt, fo, kCandCap, &fail)) {
+        wave_lds_sync();
+        select_emit(w.c, cnt, fo, ts.tau, nb, out, a.bits);
+        return;
+      }
+    }
+  }
+  if (lane == 0) atomicOr(a.err, 4);
+}
+
 // Large frontiers (many rows keep the chip busy): every row one per wave, the
-// long ones (waves [0, n_big), the front of the row list) dispatched first,
-// then the others (waves [n_big, n), its back); waves from n on find no row.
+// long ones (the front of the row list) dispatched first, then the others (its
+// back). Wave w takes rows w, w + waves, ... of that order: the host bounds the
+// grid, as most waves of a grid for the frontier's bound (the size is known on
+// the device only) would find no row.
 // Workgroups of two waves: a workgroup holds its LDS until its last wave
 // ends, and rows of a power-law frontier end at very different times, so
 // smaller workgroups keep more waves resident (hop 3 on the papers-sized
 // share: 212 us with four waves per workgroup, 199 us with two).
+template <int QS>
 __global__ __launch_bounds__(kRowWaves* MS_WAVE) void k_sample_waves(SampleArgs a) {
-  __shared__ uint64_t cand[kRowWaves][kCandCap];
-  if (a.sz->status) return;
+  __shared__ WaveList<QS> list[kRowWaves];
+  const int wave = wave_uniform(wave_id());
+  const int32_t status = a.sz->status;
+  const int64_t nbig = a.sz->n_big[a.hop - 1], n = a.sz->n[a.hop - 1];
+  if (status) return;
   clear_flags(a);
-  const int lane = lane_id(), wave = wave_uniform(wave_id());
-  const int64_t w = (int64_t)blockIdx.x * kRowWaves + wave;
-  const int64_t nbig = a.sz->n_big[a.hop - 1];
-  if (w >= a.sz->n[a.hop - 1]) return;
-  const int64_t row = wave_uniform((int32_t)a.big_rows[w < nbig ? w : a.row_waves - 1 - (w - nbig)]);
-  const Row r(a.rec, row);
-  const int32_t v = r.v;
-  const int64_t start = r.start, d = r.d;
-  const int32_t fo = a.fo;
-  int32_t* out = a.out + a.bptr[row];
-  const int32_t* nb = a.csr_indices + start;
-  if (d <= fo) {
-    for (int64_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.bits);
-    return;
+  for (int64_t w = (int64_t)blockIdx.x * kRowWaves + wave; w < n; w += (int64_t)gridDim.x * kRowWaves) {
+    const int64_t row = wave_uniform((int32_t)a.big_rows[w < nbig ? w : a.row_waves - 1 - (w - nbig)]);
+    sample_row_wave<QS>(a, Row(a.rec, row), wave_uniform(a.bptr[row]), list[wave]);
   }
-  uint64_t* c = cand[wave];
-  TauSearch ts;
-  ts.tau = first_tau(a.mu32, d);
-  int cnt = 0;
-  bool fail = false, ok = false;
-  const uint32_t d32 = (uint32_t)d;  // a row is shorter than 2^31
-  const PhiloxRow ph((uint32_t)v, a.t, (uint32_t)a.hop, a.key0, a.key1);
-  for (int iter = 0; iter < a.tau_iters && !fail; ++iter) {
-    cnt = filter_groups(ph, 0, (d32 + 3) / 4, d32, (uint32_t)(ts.tau - 1), c);
-    if (ts.step(cnt, fo, kCandCap, &fail)) {
-      ok = true;
-      break;
-    }
-  }
-  if (!ok) {
-    if (lane == 0) atomicOr(a.err, 4);
-    return;
-  }
-  wave_lds_sync();
-  select_emit(c, cnt, fo, ts.tau, nb, out, a.bits);
-}
-
-// One row by one wavefront (skipped if it is longer than skip_above): its
-// record r, its offset in the output at.
-__device__ __forceinline__ void sample_row_wave(const SampleArgs& a, const Row& r, int64_t at, uint64_t* c,
-                                                int64_t skip_above) {
-  const int lane = lane_id();
-  const int32_t fo = a.fo;
-  const int32_t v = r.v;
-  const int64_t start = r.start, d = r.d;
-  if (d > skip_above) return;
-  int32_t* out = a.out + at;
-  const int32_t* nb = a.csr_indices + start;
-  if (d <= fo) {
-    for (int64_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.bits);
-    return;
-  }
-  TauSearch ts;
-  ts.tau = first_tau(a.mu32, d);
-  int cnt = 0;
-  bool fail = false, ok = false;
-  const uint32_t d32 = (uint32_t)d;  // a row is shorter than 2^31
-  const PhiloxRow ph((uint32_t)v, a.t, (uint32_t)a.hop, a.key0, a.key1);
-  for (int iter = 0; iter < a.tau_iters && !ok && !fail; ++iter) {
-    cnt = filter_groups(ph, 0, (d32 + 3) / 4, d32, (uint32_t)(ts.tau - 1), c);
-    ok = ts.step(cnt, fo, kCandCap, &fail);
-  }
-  if (!ok) {
-    if (lane == 0) atomicOr(a.err, 4);
-    return;
-  }
-  wave_lds_sync();
-  select_emit(c, cnt, fo, ts.tau, nb, out, a.bits);
-  // (a wave samples one row: no fence at the end, which would hold the wave
-  // until its stores and bitmap atomics have completed)
 }
 
 // Small frontiers: the long rows one per block, the blocks walking the big
 // list; every other row one per wave.
+template <int QS>
 __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleArgs a) {
-  __shared__ uint64_t cand[kSampleWaves][kCandCap];
+  __shared__ WaveList<QS> list[kSampleWaves];
   const int lane = lane_id(), wave = wave_uniform(wave_id());
   const int32_t fo = a.fo;
   if ((int64_t)blockIdx.x >= a.big_blocks) {
@@ -618,56 +780,74 @@ __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleA
     pin(at);
     if (status) return;
     clear_flags(a);
+    const Row r(rc);
     // rows longer than big_min are taken by the big list
-    if (row < n) sample_row_wave(a, Row(rc), wave_uniform(at), cand[wave], a.big_min);
+    if (row < n && (int64_t)r.d <= a.big_min) sample_row_wave<QS>(a, r, wave_uniform(at), list[wave]);
     return;
   }
   if (a.sz->status) return;
   clear_flags(a);
-  {
-    __shared__ uint64_t merged[kCandCap];
-    __shared__ int counts[kSampleWaves];
-    // long rows, one per block at a time
-    const int64_t n_big = a.sz->n_big[a.hop - 1];
-    for (int64_t b = blockIdx.x; b < n_big; b += a.big_blocks) {
-      const int64_t row = wave_uniform((int32_t)a.big_rows[b]);
-      const Row r(a.rec, row);
-      const int32_t v = r.v;
-      const int64_t start = r.start, d = r.d;  // d > big_min >= fo
-      int32_t* out = a.out + a.bptr[row];
-      const int32_t* nb = a.csr_indices + start;
-      const uint32_t d32 = (uint32_t)d;
-      const PhiloxRow ph((uint32_t)v, a.t, (uint32_t)a.hop, a.key0, a.key1);
-      // this wave's quarter of the row's groups, in whole wave iterations
-      const uint32_t groups = (d32 + 3) / 4;
-      const uint32_t per = (groups + kSampleWaves * MS_WAVE - 1) / (kSampleWaves * MS_WAVE) * MS_WAVE;
-      const uint32_t g0 = min(groups, (uint32_t)wave * per), g1 = min(groups, g0 + per);
-      TauSearch ts;
-      ts.tau = first_tau(a.mu32, d);
-      int total = 0;
-      bool fail = false, ok = false;
-      for (int iter = 0; iter < a.tau_iters; ++iter) {
-        const int cnt = filter_groups(ph, g0, g1, d32, (uint32_t)(ts.tau - 1), cand[wave]);
-        if (lane == 0) counts[wave] = cnt;
-        __syncthreads();
-        total = 0;
-        for (int x = 0; x < kSampleWaves; ++x) total += counts[x];
-        // every wave takes the same decision from the same total
-        ok = ts.step(total, fo, kCandCap, &fail);
-        if (ok || fail) break;
-        __syncthreads();  // the next pass rewrites cand and counts
-      }
-      if (!ok) {
-        if (threadIdx.x == 0) atomicOr(a.err, 4);
-        return;  // every wave of the block leaves together
-      }
-      // the four lists, in order, are the row's candidates in ascending j
-      int before = 0;
-      for (int x = 0; x < wave; ++x) before += counts[x];
-      for (int i = lane; i < counts[wave]; i += MS_WAVE) merged[before + i] = cand[wave][i];
+  __shared__ WaveList<QS> merged;
+  __shared__ int counts[kSampleWaves];
+  // long rows, one per block at a time
+  const int64_t n_big = a.sz->n_big[a.hop - 1];
+  for (int64_t b = blockIdx.x; b < n_big; b += a.big_blocks) {
+    const int64_t row = wave_uniform((int32_t)a.big_rows[b]);
+    const Row r(a.rec, row);
+    const uint32_t d = r.d;  // > big_min >= fo
+    int32_t* out = a.out + a.bptr[row];
+    const int32_t* nb = a.csr_indices + r.start;
+    const PhiloxRow ph((uint32_t)r.v, a.t, (uint32_t)a.hop, a.key0, a.key1);
+    // this wave's quarter of the row's groups, in whole wave iterations
+    const uint32_t groups = (d + 3) / 4;
+    const uint32_t per = (groups + kSampleWaves * MS_WAVE - 1) / (kSampleWaves * MS_WAVE) * MS_WAVE;
+    const uint32_t g0 = min(groups, (uint32_t)wave * per), g1 = min(groups, g0 + per);
+    TauSearch ts;
+    ts.tau = first_tau(a.mu32, (int64_t)d);
+    bool fail = false, ok = false;
+    for (int iter = 0; iter < a.tau_iters && !ok && !fail; ++iter) {
+      const uint32_t tm1 = (uint32_t)(ts.tau - 1);
+      int cnt;
+      if constexpr (QS > 0)
+        cnt = filter_quads<QS>(ph, g0, g1, d, tm1, list[wave].l);
+      else
+        cnt = filter_groups(ph, g0, g1, d, tm1, list[wave].c);
+      if (lane == 0) counts[wave] = cnt;
       __syncthreads();
-      if (wave == 0) select_emit(merged, total, fo, ts.tau, nb, out, a.bits);
-      if (b + a.big_blocks < n_big) __syncthreads();  // merged and counts are reused for the next row
+      int total = 0, before = 0;
+      for (int x = 0; x < kSampleWaves; ++x) {
+        if (x == wave) before = total;
+        total += counts[x];
+      }
+      // every wave takes the same decision from the same counts; the four
+      // lists, in order, are the row's list in ascending j
+      if constexpr (QS > 0) {
+        constexpr int cap = QuadList<QS>::kCap;
+        LaneQuads<QS> c;
+        c.total = INT32_MAX;
+        if (total <= cap) {
+          for (int i = lane; i < cnt; i += MS_WAVE) {
+            merged.l.k[before + i] = list[wave].l.k[i];
+            merged.l.q[before + i] = list[wave].l.q[i];
+          }
+          __syncthreads();
+          c.read(merged.l, total, d, tm1);
+        }
+        ok = ts.step(c.total, fo, 4 * cap, &fail);
+        if (ok && wave == 0) choose_quads<QS>(c, fo, tm1, nb, out, a.bits);
+      } else {
+        ok = ts.step(total, fo, kCandCap, &fail);
+        if (ok) {
+          for (int i = lane; i < cnt; i += MS_WAVE) merged.c[before + i] = list[wave].c[i];
+          __syncthreads();
+          if (wave == 0) select_emit(merged.c, total, fo, ts.tau, nb, out, a.bits);
+        }
+      }
+      __syncthreads();  // the lists and counts are rewritten by the next pass or row
+    }
+    if (!ok) {
+      if (threadIdx.x == 0) atomicOr(a.err, 4);
+      return;  // every wave of the block leaves together
     }
   }
 }
