@@ -119,6 +119,7 @@ struct massive_ctx {
   uint32_t hmask = 0;
   float alpha = 1.0f;
   int64_t W = 0;        // bitmap words
+  int64_t map_words = 0;  // words of one copy of a bitmap (W and its padding)
   int64_t pmax = 0;     // partials capacity
   int64_t sort_cap = 0; // radix sort capacity
   int64_t hbm_blocks = 4096;  // grid bound of the HBM gather
@@ -840,13 +841,14 @@ void free_ctx(massive_ctx* c) {
 // by 256 17.2, 512 by 512 27.3.
 struct FrontierShape {
   int nt, tw;
+  int copies;  // of the sampled-id bitmap (ms::mark_bits)
   int64_t rows() const { return (int64_t)nt * ms::kFrItems; }  // rows of a tile of old rows
 };
 
 FrontierShape frontier_shape(int64_t W) {
-  if (W <= 16384) return {256, 64};
-  if (W <= 131072) return {256, 256};
-  return {512, 2048};
+  if (W <= 16384) return {256, 64, (int)ms::kSmallCopies};
+  if (W <= 131072) return {256, 256, 1};
+  return {512, 2048, 1};
 }
 
 int init_impl(massive_ctx* c, const massive_init_args* a) {
@@ -963,10 +965,11 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_tab, c->hcap * 8);
   CKA(c->d_pos_of, R * 4);
   CKA(c->d_big, R * 4);
-  // both bitmaps in one allocation, the second one 16-byte aligned
-  const int64_t map_words = cdiv(c->W + 4, 4) * 4;
-  CKA(c->d_bits, 2 * map_words * 4);
-  c->d_seen = c->d_bits + map_words;
+  // both bitmaps in one allocation, each copy on lines of its own
+  const FrontierShape fs = frontier_shape(c->W);
+  c->map_words = cdiv(c->W + 4, 32) * 32;
+  CKA(c->d_bits, (fs.copies + 1) * c->map_words * 4);
+  c->d_seen = c->d_bits + fs.copies * c->map_words;
   CKA(c->d_rec, R * 16);
   CKA(c->d_sz, kSlots * sizeof(ms::StepSizes));
   CKA(c->d_rs, sizeof(ms::RoundState));
@@ -976,7 +979,6 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_part, c->pmax * 4);
   CKA(c->d_part2, c->pmax * 4);
   c->scan_tiles = cdiv(R, ms::kScanTile) + 1;
-  const FrontierShape fs = frontier_shape(c->W);
   CKA(c->d_scan_flags, (c->scan_tiles + cdiv(R, fs.rows()) + cdiv(c->W, fs.tw)) * 8);
   c->d_tile_flags = c->d_scan_flags + c->scan_tiles;
   for (int i = 0; i < kSlots; ++i) {
@@ -1043,7 +1045,7 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
                                                           : "indptr is not non-decreasing");
     c->long_rows = c->h_ctr->evicted;
   }
-  CK(hipMemsetAsync(c->d_bits, 0, 2 * map_words * 4, s));
+  CK(hipMemsetAsync(c->d_bits, 0, (fs.copies + 1) * c->map_words * 4, s));
   CK(hipMemsetAsync(c->d_ghist, 0, 256 * 4, s));
   CK(hipMemsetAsync(c->d_scan_flags, 0, c->scan_tiles * 8, s));
   CK(hipMemsetAsync(c->d_ctr, 0, sizeof(ms::Counters), s));
@@ -1261,19 +1263,19 @@ void launch_sampler(bool by_waves, int quads, unsigned grid, hipStream_t s, hipE
 }
 
 void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream_t s, const ms::FrontierArgs& fa) {
-#define MS_FR(NT, TW)                                         \
-  do {                                                        \
-    if (last)                                                 \
-      ms::k_frontier<NT, TW, true><<<grid, NT, 0, s>>>(fa);   \
-    else                                                      \
-      ms::k_frontier<NT, TW, false><<<grid, NT, 0, s>>>(fa);  \
+#define MS_FR(NT, TW, COPIES)                                         \
+  do {                                                                \
+    if (last)                                                         \
+      ms::k_frontier<NT, TW, true, COPIES><<<grid, NT, 0, s>>>(fa);   \
+    else                                                              \
+      ms::k_frontier<NT, TW, false, COPIES><<<grid, NT, 0, s>>>(fa);  \
   } while (0)
   if (f.tw == 64)
-    MS_FR(256, 64);
+    MS_FR(256, 64, ms::kSmallCopies);
   else if (f.tw == 256)
-    MS_FR(256, 256);
+    MS_FR(256, 256, 1);
   else
-    MS_FR(512, 2048);
+    MS_FR(512, 2048, 1);
 #undef MS_FR
 }
 
@@ -1328,6 +1330,8 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
       sa.big_min = c->big_min;
       sa.big_rows = sb.big;
       sa.bits = c->d_bits;
+      sa.copies = (uint32_t)fs.copies;
+      sa.copy_words = c->map_words;
       sa.tau_iters = c->tau_iters;
       sa.n_bound = nprev;
       sa.flags = c->d_tile_flags;
@@ -1351,6 +1355,7 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
       if (timed) c->pending.push_back({hop_a, hop_b, 6});
       ms::FrontierArgs fa = {};
       fa.bits = c->d_bits;
+      fa.copy_words = c->map_words;
       fa.seen = c->d_seen;
       fa.W = c->W;
       fa.L = c->L;

@@ -267,12 +267,24 @@ struct SampleArgs {
   int64_t row_waves;        // k_sample_waves: small_end of k_row_scan (the other rows' list ends there)
   int64_t big_blocks;       // k_sample_blocks: blocks [0, big_blocks) walk the big list, one row per
                             // block; the rest take all other rows, one per wave
-  uint32_t* bits;           // sampled-id bitmap
+  uint32_t* bits;           // sampled-id bitmap: this block's copy is (block % copies)
+  int64_t copy_words;       // words from one copy to the next
+  uint32_t copies;          // a power of two
   int32_t* err;             // threshold search could not isolate a candidate set
   int32_t tau_iters;        // threshold passes allowed per row (kTauIters)
   uint64_t* flags;          // tile states of the frontier scan that follows: cleared here
   int64_t n_flags;
 };
+
+// The copy of the sampled-id bitmap that this block marks. Atomics on one
+// 128-byte line go through one after another (about 100 M/s), and a small id
+// space has few lines: 11.4K marks on the 8 lines of 7.8K ids took 14 of a
+// launch's 16.5 us. So small spaces have kSmallCopies copies, which the dedup
+// scan ors together.
+constexpr uint32_t kSmallCopies = 8;
+__device__ __forceinline__ uint32_t* mark_bits(const SampleArgs& a) {
+  return a.bits + (int64_t)(blockIdx.x & (a.copies - 1)) * a.copy_words;
+}
 
 __device__ __forceinline__ void clear_flags(const SampleArgs& a) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n_flags;
@@ -690,7 +702,7 @@ __device__ __forceinline__ void sample_row_wave(const SampleArgs& a, const Row& 
   int32_t* out = a.out + at;
   const int32_t* nb = a.csr_indices + r.start;
   if (d <= (uint32_t)fo) {
-    for (uint32_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], a.bits);
+    for (uint32_t j = lane; j < d; j += MS_WAVE) emit_id(out, (int)j, nb[j], mark_bits(a));
     return;
   }
   const PhiloxRow ph((uint32_t)r.v, a.t, (uint32_t)a.hop, a.key0, a.key1);
@@ -699,7 +711,7 @@ __device__ __forceinline__ void sample_row_wave(const SampleArgs& a, const Row& 
     LaneQuads<1> c;
     c.total = 0;
     c.set(0, true, ph.from_a1((uint64_t)0xD2511F53u * (uint32_t)lane), (uint32_t)lane, d, ~0u);
-    choose_quads<1>(c, fo, ~0u, nb, out, a.bits);
+    choose_quads<1>(c, fo, ~0u, nb, out, mark_bits(a));
     return;
   }
   TauSearch ts;
@@ -716,7 +728,7 @@ __device__ __forceinline__ void sample_row_wave(const SampleArgs& a, const Row& 
         c.read(w.l, n, d, tm1);
       }
       if (ts.step(c.total, fo, 4 * QuadList<QS>::kCap, &fail)) {
-        choose_quads<QS>(c, fo, tm1, nb, out, a.bits);
+        choose_quads<QS>(c, fo, tm1, nb, out, mark_bits(a));
         return;
       }
       wave_lds_sync();  // the next pass rewrites the list
@@ -724,7 +736,7 @@ __device__ __forceinline__ void sample_row_wave(const SampleArgs& a, const Row& 
       const int cnt = filter_groups(ph, 0, (d + 3) / 4, d, tm1, w.c);
       if (ts.step(cnt, fo, kCandCap, &fail)) {
         wave_lds_sync();
-        select_emit(w.c, cnt, fo, ts.tau, nb, out, a.bits);
+        select_emit(w.c, cnt, fo, ts.tau, nb, out, mark_bits(a));
         return;
       }
     }
@@ -834,13 +846,13 @@ __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleA
           c.read(merged.l, total, d, tm1);
         }
         ok = ts.step(c.total, fo, 4 * cap, &fail);
-        if (ok && wave == 0) choose_quads<QS>(c, fo, tm1, nb, out, a.bits);
+        if (ok && wave == 0) choose_quads<QS>(c, fo, tm1, nb, out, mark_bits(a));
       } else {
         ok = ts.step(total, fo, kCandCap, &fail);
         if (ok) {
           for (int i = lane; i < cnt; i += MS_WAVE) merged.c[before + i] = list[wave].c[i];
           __syncthreads();
-          if (wave == 0) select_emit(merged.c, total, fo, ts.tau, nb, out, a.bits);
+          if (wave == 0) select_emit(merged.c, total, fo, ts.tau, nb, out, mark_bits(a));
         }
       }
       __syncthreads();  // the lists and counts are rewritten by the next pass or row
@@ -856,7 +868,8 @@ __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleA
 // One launch after each hop's sampling: the frontier F_k, and the rows that
 // the next hop samples for.
 // New nodes in ascending id: F[n_{k-1} + rank] = u, pos_of[u] = that position,
-// u the rank-th sampled id not in the frontier (bits & ~seen). `bits` is
+// u the rank-th sampled id not in the frontier (bits & ~seen, the copies of
+// bits ored together). `bits` is
 // cleared for the next hop; the new nodes join `seen`, which the last hop
 // clears for the next step. The new nodes below L (local ids) are the prefix
 // at id L: the thread whose words hold id L writes that count (the last tile,
@@ -880,7 +893,8 @@ __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleA
 constexpr int kFrItems = 8;  // rows in flight per thread
 
 struct FrontierArgs {
-  uint32_t* bits;
+  uint32_t* bits;      // COPIES copies of the sampled-id bitmap
+  int64_t copy_words;  // words from one copy to the next
   uint32_t* seen;
   int64_t W;
   int32_t L;
@@ -970,11 +984,11 @@ __device__ __forceinline__ FrSums fr_lookback(uint64_t* flags, int64_t b, uint32
   return x;
 }
 
-template <int NT, int TW, bool LAST>
+template <int NT, int TW, bool LAST, int COPIES>
 __global__ __launch_bounds__(NT) void k_frontier(FrontierArgs a) {
   constexpr int kFrNT = NT, kFrWaves = NT / MS_WAVE, kFrChunk = NT * kFrItems;
   constexpr int WPT = TW > NT ? TW / NT : 1;  // words per thread (of the first TW / WPT threads)
-  static_assert(WPT == 1 || WPT == 4, "one word or one 16-byte vector");
+  static_assert(WPT == 1 || (WPT == 4 && COPIES == 1), "one word or one 16-byte vector");
   static_assert(kFrItems * kFrWaves <= MS_WAVE, "the waves' sums are scanned by one wave");
   __shared__ int32_t lds[kFrWaves + 1];
   __shared__ int32_t list[kFrChunk];
@@ -1006,8 +1020,12 @@ __global__ __launch_bounds__(NT) void k_frontier(FrontierArgs a) {
         sn[x] = ss[x];
       }
     } else {
-      w[0] = a.bits[i0w];
+      uint32_t b[COPIES];
+#pragma unroll
+      for (int x = 0; x < COPIES; ++x) b[x] = a.bits[x * a.copy_words + i0w];
       sn[0] = a.seen[i0w];
+#pragma unroll
+      for (int x = 0; x < COPIES; ++x) w[0] |= b[x];
     }
   }
   if (!LAST && old) {
@@ -1034,7 +1052,10 @@ __global__ __launch_bounds__(NT) void k_frontier(FrontierArgs a) {
       const uint32_t b = w[x];
       w[x] = b & ~sn[x];
       mine += __popc(w[x]);
-      if (b) a.bits[i0w + x] = 0u;
+      if (b) {
+#pragma unroll
+        for (int y = 0; y < COPIES; ++y) a.bits[y * a.copy_words + i0w + x] = 0u;
+      }
       if (LAST) {
         if (sn[x]) a.seen[i0w + x] = 0u;
       } else if (w[x]) {
