@@ -438,11 +438,88 @@ struct MissArgs {
   uint8_t* dst;
   uint8_t* buf;
   uint8_t* dummy;
+  int64_t src_bytes;  // of the store
+  int32_t lanes_log2;  // miss_rows: lanes per row
   StepTail tail;
 };
 
+// Host-link reads cost whole 128-byte lines (64-byte rows move at 20 GB/s,
+// aligned 256-byte and longer ones at 55-57), and their rate needs ~150 KB
+// under way. Rows whose size or place rules out 16-byte vectors are therefore
+// still read in 16-byte ones, from the aligned chunks that cover the row, 2^k
+// lanes a row, so that no line of it is fetched by two instructions; the
+// chunks are stored in the row's own vectors (E). Chunks that reach past the
+// store's ends are read in vectors too. Reading in the row's own vectors, 12
+// blocks: 100-byte rows 15.8 GB/s against 22.3 here, 200-byte rows 29.0
+// against 33.5 (alone; 400-byte rows, 16-byte vectors anyway, 43 either way).
+template <typename E>
+__device__ __forceinline__ void miss_rows(const MissArgs& a, int64_t rb, uint64_t blocks) {
+  constexpr int U = 4, PARTS = 16 / (int)sizeof(E);
+  const StepTail& tail = a.tail;
+  const int64_t n = *a.count;
+  const int lg = a.lanes_log2, rpw = MS_WAVE >> lg;
+  const int sub = lane_id() >> lg, cl = lane_id() & ((1 << lg) - 1);
+  const int64_t waves = (int64_t)blocks * (blockDim.x / MS_WAVE);
+  const int64_t per = (int64_t)U * rpw;
+  const uint64_t lo = (uint64_t)a.src, hi = lo + (uint64_t)a.src_bytes;
+  const int64_t chunks = (rb + 14) / 16 + 1;  // 16-byte chunks that a row can touch
+  for (int64_t base = ((int64_t)blockIdx.x * (blockDim.x / MS_WAVE) + wave_id()) * per; base < n; base += waves * per) {
+    int2 e[U];
+    int32_t ws[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t r = base + (int64_t)u * rpw + sub;
+      ok[u] = r < n;
+      e[u] = a.list[ok[u] ? r : base];
+      ws[u] = a.wslot[ok[u] ? r : base];
+    }
+    for (int64_t c = cl; c < chunks; c += 1 << lg) {
+      v4u v[U];
+      int64_t o[U];  // the chunk's first byte, in the row
+      bool in[U], edge[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint64_t row = lo + (uint64_t)(uint32_t)e[u].y * rb;
+        const uint64_t p = (row & ~15ull) + (uint64_t)c * 16;
+        o[u] = (int64_t)(p - row);
+        in[u] = ok[u] && o[u] < rb;
+        const bool whole = p >= lo && p + 16 <= hi;
+        edge[u] = in[u] && !whole;
+        v[u] = *reinterpret_cast<const v4u*>(in[u] && whole ? reinterpret_cast<const uint8_t*>(p) : a.dummy);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) pin(v[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        E x[PARTS];
+        __builtin_memcpy(x, &v[u], 16);
+        uint8_t* q = a.dst + (uint64_t)(uint32_t)e[u].x * rb;
+        uint8_t* b = a.buf + (uint64_t)(uint32_t)ws[u] * rb;
+#pragma unroll
+        for (int k = 0; k < PARTS; ++k) {
+          const int64_t at = o[u] + k * (int)sizeof(E);
+          if (!in[u] || at < 0 || at >= rb) continue;
+          if (edge[u]) x[k] = *reinterpret_cast<const E*>(a.src + (uint64_t)(uint32_t)e[u].y * rb + at);
+          *reinterpret_cast<E*>(q + at) = x[k];
+          if (ws[u] >= 0) {
+            *reinterpret_cast<E*>(b + at) = x[k];
+            if (at == 0 && tail.round_id >= 0 && ws[u] < tail.cap)
+              __hip_atomic_store(&tail.landed[ws[u]], tail.round_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+      }
+    }
+  }
+}
+
 template <typename V, bool ONE>
 __device__ __forceinline__ void miss_body(const MissArgs& a, int64_t rb, uint32_t cpr, uint64_t magic, uint64_t blocks) {
+  if constexpr (sizeof(V) < 16) {
+    miss_rows<V>(a, rb, blocks);
+    if (blockIdx.x == 0) publish_step(a.tail);
+    return;
+  }
   constexpr int U = 4;
   const StepTail& tail = a.tail;
   const uint64_t n = (uint64_t)*a.count;

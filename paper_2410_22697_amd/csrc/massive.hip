@@ -1473,6 +1473,9 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
   ma.dst = (uint8_t*)io->feat;
   ma.buf = c->d_slab + (int64_t)c->L * c->rb;
   ma.dummy = c->d_dummy;
+  ma.src_bytes = (int64_t)c->H * c->rb;
+  ma.lanes_log2 = 0;
+  while (ma.lanes_log2 < 6 && (1 << ma.lanes_log2) < (c->rb + 14) / 16 + 1) ++ma.lanes_log2;
   ma.tail = ms::StepTail{sz, c->K, &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot, c->d_landed, c->cap, pend,
                          !both && !sb.from_scratch};
   if (both) {
