@@ -236,13 +236,15 @@ int massive_info(const massive_ctx* ctx, int64_t* cap, float* alpha);
 /* Per-kernel-group timing with HIP events recorded on the stream each group
  * runs on (the groups of massive_get_timing). groups is a bit mask, bit i for
  * group i (MASSIVE_TIMING_ALL: every group, 0: off); it clears the totals.
- * Each timed group adds event packets to its streams, so a run that must not
- * be slowed times only what it needs. MASSIVE_EINVAL for bits outside the
+ * Each timed group adds event packets to its streams, and the two gathers run
+ * in one launch unless group 2 or 3 is on (then one after the other, each
+ * alone on its resource), so a run that must not be slowed times only what it
+ * needs. MASSIVE_EINVAL for bits outside the
  * mask. */
 #define MASSIVE_TIMING_ALL 0x7F
 int massive_set_timing(massive_ctx* ctx, int groups);
 /* Totals since enabled: out_ms[i] summed milliseconds and out_calls[i]
- * launches for i = 0 sample+dedup, 1 classify, 2 gather_hbm, 3 gather_miss,
+ * launches for i = 0 sample+dedup, 1 classify and relabel, 2 gather_hbm, 3 gather_miss,
  * 4 eviction round, 5 refill, 6 the last hop's sampler kernel alone (a part
  * of group 0). out_ms and out_calls have room for 7 entries each.
  * Synchronises the context's streams. */

@@ -580,11 +580,15 @@ __global__ __launch_bounds__(256) void k_gather_miss(MissArgs a, int64_t rb, uin
   }
 }
 
-// Both gathers of a step that is waited for at once, in one launch: the first
-// `blocks` blocks are the miss gather's, the others the HBM gather's. No
-// sampling runs beside such a step, so the HBM rows move while the link's
-// rows are under way (in look-ahead they run alone, as the host reads would
-// throttle them). The sizes are left for the next step to clear (k_seed_rows).
+// Both gathers of a step in one launch: the first `blocks` blocks are the miss
+// gather's, the others the HBM gather's. The HBM rows then move while the
+// link's rows are under way, and cost the link nothing measurable (the
+// 111M-node share: 250 us for both, 250 for the miss gather after the HBM
+// gather's 44), though the HBM gather itself slows beside host reads. us per
+// pass against one after the other: eight look-ahead steps on the 2.45M-node
+// graph 5773 -> 5323, on the 111M-node share 3038 -> 2984, four bf16 steps with
+// a round 7936 -> 7688, 16 steps with a round on the 170K-node graph 5219 ->
+// 4987. The sizes are left for the next step to clear (k_seed_rows).
 template <typename V, bool ONE>
 __global__ __launch_bounds__(256) void k_gather_both(MissArgs a, uint32_t blocks, const int2* __restrict__ list,
                                                      const int64_t* __restrict__ count,

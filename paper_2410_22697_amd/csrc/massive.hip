@@ -1,11 +1,12 @@
 // massive.hip - libmassive: the C ABI of include/massive.h on one MI355X.
 //
 // Streams: a step's sampling and classify run on the caller's stream
-// ("main"); its HBM gather, its miss gather from pinned host memory and its
-// completion kernel follow on a side stream, so the main stream goes on to the
-// next step at once; eviction rounds and their refill copies run on a copy
-// stream (the refill chunks and the HBM gathers wait for each other, and the
-// next classify waits for a round).
+// ("main"); its gathers (HBM rows and rows from pinned host memory) follow on
+// a side stream, so the main stream goes on to the next step at once (a step
+// that is waited for at once keeps them on the main stream); eviction rounds
+// and their refill copies run on a copy stream (a step's refill chunk starts
+// after its classify, its gathers wait for the chunk before, and the next
+// classify waits for a round).
 // In the staged link mode no kernel reads host memory: a worker thread of the
 // context gathers each step's host rows and each refill chunk's rows into a
 // pinned ring (with a pool of host threads), copies them with the DMA engines
@@ -199,6 +200,7 @@ struct massive_ctx {
   // (main), HBM gather done and miss gather + mailbox done (side)
   hipEvent_t ev_cls_done[kSlots] = {}, ev_hbm_done[kSlots] = {}, ev_batch_done[kSlots] = {};
   hipEvent_t ev_round_done = nullptr, ev_refill_done = nullptr;
+  bool slot_both[kSlots] = {};  // the slot's step ran both gathers in one launch (ev_hbm_done was not recorded)
   bool round_unclassified = false;  // a round was enqueued that no classify has waited for yet
   // The refill of the last round is copied in chunks, one after each of the
   // next steps' HBM gathers (host-link reads never overlap an HBM gather).
@@ -1282,11 +1284,9 @@ void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream
 // Enqueues one step with the per-step buffers sb: sampling and classify on the
 // main stream, the gathers and the step's completion on the side stream. A
 // step that is waited for at once (`alone`: no other batch in flight, loads
-// link) has no next step to make room for: it stays on the main stream, with
-// both gathers in one launch unless a refill chunk is to run after the HBM one
-// or either is timed. That spares the cross-stream wait (~8 us), the gap
-// between the gathers (~5 us) and the HBM gather's time behind the link's: us
-// per step, before -> after, 16 seeds on the 170K-node graph (no-alloc, whose
+// link) has no next step to make room for: it stays on the main stream. That
+// spares the cross-stream wait (~8 us); with both gathers in one launch, us
+// per step, before -> after: 16 seeds on the 170K-node graph (no-alloc, whose
 // two clearing launches went too) 117 -> 93, 1024 seeds there 434 -> 408, on
 // the 111M-node share 645 -> 587.
 int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch* io, const int64_t* nb,
@@ -1450,20 +1450,24 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     ms::k_classify<<<ca.cls_blocks + ca.rel_first[c->K], ms::kClsNT, 0, s>>>(ca);
   }
   // The gathers run on the side stream, so the main stream goes on to the
-  // next step's sampling at once. HBM rows first, at full bandwidth: after the
-  // previous step's miss gather (stream order) and the last refill chunk, as
-  // concurrent host-link reads would throttle them; then the host-link rows,
-  // beside the refill chunk launched after the HBM gather.
+  // next step's sampling at once, in one launch: the HBM rows move while the
+  // link's rows are under way. They follow the previous step's gathers (stream
+  // order) and the last refill chunk; the next chunk runs beside them. Where a
+  // gather is timed they run one after the other, each with the memory system
+  // to itself: the HBM gather after the previous host reads, the refill chunk
+  // and the miss gather after it.
+  const bool both = c->H > 0 && !c->staged() && !(c->timing & 0xC);
   hipStream_t sm = alone ? s : c->s_miss;
-  if (!alone) {
-    CK(hipEventRecord(c->ev_cls_done[slot], s));
-    CK(hipStreamWaitEvent(sm, c->ev_cls_done[slot], 0));
-  }
+  if (!alone || (both && c->chunks_left > 0)) CK(hipEventRecord(c->ev_cls_done[slot], s));
+  if (!alone) CK(hipStreamWaitEvent(sm, c->ev_cls_done[slot], 0));
   if (c->refill_inflight) CK(hipStreamWaitEvent(sm, c->ev_refill_done, 0));
+  c->slot_both[slot] = both;
+  const bool heavy = alone || c->round_pending_rows || c->host_rows_seen < 0 ||
+                     c->host_rows_seen * c->rb > kLinkHeavyBytes;
+  const int64_t host_blocks = heavy ? c->host_blocks : c->host_blocks_light;
   // the miss gather ends the step: it stamps the slots it writes through as
   // landed and publishes the step's sizes to the host mailbox (a context
   // without halo nodes publishes them with a kernel of its own)
-  const bool both = alone && c->H > 0 && c->chunks_left == 0 && !(c->timing & 0xC);
   ms::MissArgs ma;
   ma.list = miss_list;
   ma.wslot = sb.miss_slot;
@@ -1479,7 +1483,7 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
   ma.tail = ms::StepTail{sz, c->K, &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot, c->d_landed, c->cap, pend,
                          !both && !sb.from_scratch};
   if (both) {
-    launch_gather(c, kBoth, sm, sb.hbm_list, &sz->n_hbm, (uint8_t*)io->feat, nb[c->K], c->host_blocks, &ma);
+    launch_gather(c, kBoth, sm, sb.hbm_list, &sz->n_hbm, (uint8_t*)io->feat, nb[c->K], host_blocks, &ma);
   } else {
     launch_gather(c, kHbm, sm, sb.hbm_list, &sz->n_hbm, (uint8_t*)io->feat, nb[c->K], 0, nullptr);
     CK(hipEventRecord(c->ev_hbm_done[slot], sm));
@@ -1514,19 +1518,16 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     c->pending_round = true;
     return MASSIVE_OK;
   }
-  if (!both) {
-    int rc = launch_refill_chunks(c, 1, c->ev_hbm_done[slot]);
+  {
+    int rc = launch_refill_chunks(c, 1, both ? c->ev_cls_done[slot] : c->ev_hbm_done[slot]);
     if (rc != MASSIVE_OK) return rc;
-    if (c->H > 0) {
-      const bool heavy = alone || c->round_pending_rows || c->host_rows_seen < 0 ||
-                         c->host_rows_seen * c->rb > kLinkHeavyBytes;
-      launch_gather(c, kMiss, sm, nullptr, nullptr, (uint8_t*)io->feat, nb[c->K],
-                    heavy ? c->host_blocks : c->host_blocks_light, &ma);
-      if (!sb.from_scratch) c->slot_clear[slot] = true;
-    } else {
-      ms::k_step_done<<<1, 256, 0, sm>>>(sb.miss_slot, &sz->n_miss, c->d_landed, c->cap, -1, sz, c->K,
-                                         &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot);
-    }
+  }
+  if (!both && c->H > 0) {
+    launch_gather(c, kMiss, sm, nullptr, nullptr, (uint8_t*)io->feat, nb[c->K], host_blocks, &ma);
+    if (!sb.from_scratch) c->slot_clear[slot] = true;
+  } else if (!both) {
+    ms::k_step_done<<<1, 256, 0, sm>>>(sb.miss_slot, &sz->n_miss, c->d_landed, c->cap, -1, sz, c->K,
+                                       &c->d_ctr->bad, c->hd_sz + slot, c->hd_bad + slot);
   }
   // (also the miss gather's completion, which the next round's refill follows)
   CK(hipEventRecord(c->ev_batch_done[slot], sm));
@@ -1755,7 +1756,8 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
   c->round_pending_rows = false;
   // (a step that was waited for has nothing left to wait for)
   const bool step_in_flight = c->infl[tl % kSlots].io != nullptr;
-  if (step_in_flight) CK(hipStreamWaitEvent(s, c->ev_hbm_done[tl % kSlots], 0));
+  if (step_in_flight)
+    CK(hipStreamWaitEvent(s, c->slot_both[tl % kSlots] ? c->ev_cls_done[tl % kSlots] : c->ev_hbm_done[tl % kSlots], 0));
   {
     massive_ctx::Range tr(c, s, 4);
     ms::k_materialize<<<grid_for(cap, 256), 256, 0, s>>>(c->d_S_E, c->d_hitcnt, cap, (int32_t)(c->t - c->mat_t),
