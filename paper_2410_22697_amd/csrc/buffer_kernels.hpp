@@ -127,7 +127,7 @@ constexpr int kRelBlocks = 1024;  // grid bound of the relabelling blocks of the
 __global__ __launch_bounds__(kClsNT) void k_classify(ClassifyArgs a) {
   constexpr int NW = kClsNT / MS_WAVE;
   __shared__ int32_t wc[NW][3];          // per-wave counts: hbm list, host list, pending hits
-  __shared__ unsigned long long base[2];
+  __shared__ unsigned long long base[3];
   if (blockIdx.x >= a.cls_blocks) {
     const uint32_t b = blockIdx.x - a.cls_blocks;
     for (int k = 0; k < a.K; ++k)
@@ -189,56 +189,34 @@ __global__ __launch_bounds__(kClsNT) void k_classify(ClassifyArgs a) {
         slot[it] = r;
       }
     }
-    int32_t sr[kClsItems], ld[kClsItems], rk[kClsItems];
-#pragma unroll
-    for (int it = 0; it < kClsItems; ++it) {
-      const int32_t sl = slot[it] >= 0 ? slot[it] : 0;
-      rk[it] = a.sa_idx[v[it] >= a.L && slot[it] < 0 ? v[it] - a.L : 0];
-      sr[it] = 0;
-      ld[it] = 0;
-      if (pending) {  // the same in every lane
-        sr[it] = a.slot_round[sl];
-        ld[it] = __hip_atomic_load(&a.landed[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-#pragma unroll
-    for (int it = 0; it < kClsItems; ++it) {
-      pin(sr[it]);
-      pin(ld[it]);
-      pin(rk[it]);
-    }
+    // classes: 0 local, 1 hit, 2 miss, 3 hit on a slot whose refill may not
+    // have landed (reads the same row from the host store), -1 no row
     int cls[kClsItems];
-    int32_t src[kClsItems], wslot[kClsItems];
-    int ch = 0, cm = 0, cp = 0;  // hbm list, host list, pending hits
 #pragma unroll
     for (int it = 0; it < kClsItems; ++it) {
       const int64_t i = b0 + (int64_t)it * kClsNT + threadIdx.x;
-      cls[it] = -1;
-      src[it] = 0;
-      wslot[it] = -1;
-      if (i < n) {
-        const int32_t h = v[it] - a.L;
-        if (v[it] < a.L) {
-          cls[it] = 0;
-          src[it] = v[it];
-        } else if (slot[it] >= 0) {
-          cls[it] = 1;
-          src[it] = a.L + slot[it];
-          atomicAdd(&a.hitcnt[slot[it]], 1);  // each slot once per step: no contention
-          // a hit on a slot whose refill may not have landed reads the same
-          // row from the host store
-          if (pending && sr[it] == a.pend_round && ld[it] != a.pend_round) {
-            cls[it] = 3;
-            src[it] = h;
-            wslot[it] = slot[it];
-          }
-        } else {
-          cls[it] = 2;
-          src[it] = h;
-          atomicAdd(&a.S_A[rk[it]], 1.0f);
-        }
-        a.mask[i] = (uint8_t)(cls[it] == 3 ? 1 : cls[it]);
+      cls[it] = i >= n ? -1 : v[it] < a.L ? 0 : slot[it] >= 0 ? 1 : 2;
+    }
+    if (pending) {  // the same in every lane
+      int32_t sr[kClsItems], ld[kClsItems];
+#pragma unroll
+      for (int it = 0; it < kClsItems; ++it) {
+        const int32_t sl = slot[it] >= 0 ? slot[it] : 0;
+        sr[it] = a.slot_round[sl];
+        ld[it] = __hip_atomic_load(&a.landed[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
+#pragma unroll
+      for (int it = 0; it < kClsItems; ++it) {
+        pin(sr[it]);
+        pin(ld[it]);
+      }
+#pragma unroll
+      for (int it = 0; it < kClsItems; ++it)
+        if (cls[it] == 1 && sr[it] == a.pend_round && ld[it] != a.pend_round) cls[it] = 3;
+    }
+    int ch = 0, cm = 0, cp = 0;  // hbm list, host list, pending hits
+#pragma unroll
+    for (int it = 0; it < kClsItems; ++it) {
       ch += __popcll(ballot(cls[it] == 0 || cls[it] == 1));
       cm += __popcll(ballot(cls[it] >= 2));
       if (pending) cp += __popcll(ballot(cls[it] == 3));
@@ -248,17 +226,28 @@ __global__ __launch_bounds__(kClsNT) void k_classify(ClassifyArgs a) {
       wc[wave][1] = cm;
       wc[wave][2] = cp;
     }
+    // the S_A indices of the misses are on their way while the list bases are taken
+    int32_t rk[kClsItems];
+#pragma unroll
+    for (int it = 0; it < kClsItems; ++it) rk[it] = a.sa_idx[cls[it] == 2 ? v[it] - a.L : 0];
     __syncthreads();
-    if (threadIdx.x == 0) {
-      int th = 0, tm = 0, tp = 0;
-      for (int w = 0; w < NW; ++w) {
-        th += wc[w][0];
-        tm += wc[w][1];
-        tp += wc[w][2];
-      }
-      base[0] = th ? atomicAdd((unsigned long long*)&a.sz->n_hbm, (unsigned long long)th) : 0ull;
-      base[1] = tm ? atomicAdd((unsigned long long*)&a.sz->n_miss, (unsigned long long)tm) : 0ull;
-      if (tp) atomicAdd((unsigned long long*)&a.sz->n_pending, (unsigned long long)tp);
+    if (threadIdx.x < 3) {  // one atomic per list (and the pending count), side by side
+      int t = 0;
+      for (int w = 0; w < NW; ++w) t += wc[w][threadIdx.x];
+      int64_t* at = threadIdx.x == 0 ? &a.sz->n_hbm : threadIdx.x == 1 ? &a.sz->n_miss : &a.sz->n_pending;
+      unsigned long long was = 0ull;
+      if (t) was = atomicAdd((unsigned long long*)at, (unsigned long long)t);
+      base[threadIdx.x] = was;
+    }
+#pragma unroll
+    for (int it = 0; it < kClsItems; ++it) pin(rk[it]);
+#pragma unroll
+    for (int it = 0; it < kClsItems; ++it) {
+      const int64_t i = b0 + (int64_t)it * kClsNT + threadIdx.x;
+      if (cls[it] < 0) continue;
+      if (cls[it] == 1 || cls[it] == 3) atomicAdd(&a.hitcnt[slot[it]], 1);  // each slot once per step: no contention
+      if (cls[it] == 2) atomicAdd(&a.S_A[rk[it]], 1.0f);
+      a.mask[i] = (uint8_t)(cls[it] == 3 ? 1 : cls[it]);
     }
     __syncthreads();
     // this wave's offset inside the block's share of each list
@@ -272,10 +261,11 @@ __global__ __launch_bounds__(kClsNT) void k_classify(ClassifyArgs a) {
       const int64_t i = b0 + (int64_t)it * kClsNT + threadIdx.x;
       const uint64_t mh = ballot(cls[it] == 0 || cls[it] == 1);
       const uint64_t mm = ballot(cls[it] >= 2);
-      if (cls[it] == 0 || cls[it] == 1) a.hbm_list[oh + lanes_below(mh)] = make_int2((int32_t)i, src[it]);
-      else if (cls[it] >= 2) {
-        a.miss_list[om + lanes_below(mm)] = make_int2((int32_t)i, src[it]);
-        a.miss_slot[om + lanes_below(mm)] = wslot[it];
+      if (cls[it] == 0 || cls[it] == 1) {
+        a.hbm_list[oh + lanes_below(mh)] = make_int2((int32_t)i, cls[it] == 0 ? v[it] : a.L + slot[it]);
+      } else if (cls[it] >= 2) {
+        a.miss_list[om + lanes_below(mm)] = make_int2((int32_t)i, v[it] - a.L);
+        a.miss_slot[om + lanes_below(mm)] = cls[it] == 3 ? slot[it] : -1;
       }
       oh += __popcll(mh);
       om += __popcll(mm);
@@ -517,7 +507,6 @@ template <typename V, bool ONE>
 __device__ __forceinline__ void miss_body(const MissArgs& a, int64_t rb, uint32_t cpr, uint64_t magic, uint64_t blocks) {
   if constexpr (sizeof(V) < 16) {
     miss_rows<V>(a, rb, blocks);
-    if (blockIdx.x == 0) publish_step(a.tail);
     return;
   }
   constexpr int U = 4;
@@ -558,12 +547,12 @@ __device__ __forceinline__ void miss_body(const MissArgs& a, int64_t rb, uint32_
       }
     }
   }
-  if (blockIdx.x == 0) publish_step(tail);
 }
 
 template <typename V, bool ONE>
 __global__ __launch_bounds__(256) void k_gather_miss(MissArgs a, int64_t rb, uint32_t cpr, uint64_t magic) {
   miss_body<V, ONE>(a, rb, cpr, magic, gridDim.x);
+  if (blockIdx.x == 0) publish_step(a.tail);
   if (!a.tail.clear) return;
   // the last block to finish clears the sizes for the slot's next step (every
   // block has read its count, and block 0 has published them, by then)
@@ -581,7 +570,9 @@ __global__ __launch_bounds__(256) void k_gather_miss(MissArgs a, int64_t rb, uin
 }
 
 // Both gathers of a step in one launch: the first `blocks` blocks are the miss
-// gather's, the others the HBM gather's. The HBM rows then move while the
+// gather's, the next one publishes the step (no other block writes what it
+// reads, and the host looks once the launch has ended), the others are the HBM
+// gather's. The HBM rows then move while the
 // link's rows are under way, and cost the link nothing measurable (the
 // 111M-node share: 250 us for both, 250 for the miss gather after the HBM
 // gather's 44), though the HBM gather itself slows beside host reads. us per
@@ -596,8 +587,11 @@ __global__ __launch_bounds__(256) void k_gather_both(MissArgs a, uint32_t blocks
                                                      uint64_t magic) {
   if (blockIdx.x < blocks)
     miss_body<V, ONE>(a, rb, cpr, magic, blocks);
+  else if (blockIdx.x == blocks)
+    publish_step(a.tail);
   else
-    gather_body<V, ONE, 4>(list, count, a.bound, src, a.dst, rb, cpr, magic, blockIdx.x - blocks, gridDim.x - blocks);
+    gather_body<V, ONE, 4>(list, count, a.bound, src, a.dst, rb, cpr, magic, blockIdx.x - blocks - 1,
+                           gridDim.x - blocks - 1);
 }
 
 // The step's completion as a kernel of its own, where no miss gather ends

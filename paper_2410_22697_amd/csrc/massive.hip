@@ -465,7 +465,7 @@ void launch_gather(massive_ctx* c, GatherKind kind, hipStream_t s, const int2* l
       else                                                                                                      \
         ms::k_gather_miss<V, ONE><<<host_grid, 256, 0, s>>>(*m, rb, cpr, magic);                                \
     } else {                                                                                                    \
-      ms::k_gather_both<V, ONE><<<host_grid + hbm_grid, 256, 0, s>>>(*m, host_grid, list, count, slab, rb, cpr, \
+      ms::k_gather_both<V, ONE><<<host_grid + 1 + hbm_grid, 256, 0, s>>>(*m, host_grid, list, count, slab, rb, cpr, \
                                                                      magic);                                    \
     }                                                                                                           \
   } while (0)

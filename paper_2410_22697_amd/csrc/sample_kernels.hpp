@@ -125,28 +125,23 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
     for (int it = 0; it < kScanItems; ++it) v[it] = seeds[base + it < n ? base + it : n - 1];
 #pragma unroll
     for (int it = 0; it < kScanItems; ++it) pin(v[it]);
+    // the marks (an atomic each, whose old word says whether the seed is a
+    // repeat) and the row extents in one round, no result used before all are
+    // under way; lanes without a seed, and bad ones, mark nothing and load an
+    // in-range row
+    uint32_t was[kScanItems];
+    bool ok[kScanItems];
 #pragma unroll
     for (int it = 0; it < kScanItems; ++it) {
-      const int64_t i = base + it;
-      const int32_t x = v[it];
-      const bool ok = x >= 0 && x < L;
-      if (i < n) {
-        if (!ok) {
-          atomicOr(&sz->status, 1);
-        } else {
-          const uint32_t bit = 1u << (x & 31);
-          if (atomicOr(&seen[x >> 5], bit) & bit) atomicOr(&sz->status, 2);
-          pos_of[x] = (int32_t)i;
-          nodes[i] = x;
-        }
-      }
-      v[it] = ok ? x : 0;  // an in-range row for the loads below (the step is abandoned anyway)
+      ok[it] = v[it] >= 0 && v[it] < L;
+      const int32_t x = ok[it] ? v[it] : 0;
+      was[it] = 0u;
+      if (ok[it] && base + it < n) was[it] = atomicOr(&seen[x >> 5], 1u << (x & 31));
+      lo[it] = csr_indptr[x];
+      hi[it] = csr_indptr[x + 1];
     }
 #pragma unroll
-    for (int it = 0; it < kScanItems; ++it) {
-      lo[it] = csr_indptr[v[it]];
-      hi[it] = csr_indptr[v[it] + 1];
-    }
+    for (int it = 0; it < kScanItems; ++it) pin(was[it]);
 #pragma unroll
     for (int it = 0; it < kScanItems; ++it) {
       pin(lo[it]);
@@ -156,6 +151,13 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
     for (int it = 0; it < kScanItems; ++it) {
       const int64_t i = base + it;
       if (i < n) {
+        if (!ok[it]) {
+          atomicOr(&sz->status, 1);
+          continue;
+        }
+        if ((was[it] >> (v[it] & 31)) & 1u) atomicOr(&sz->status, 2);
+        pos_of[v[it]] = (int32_t)i;
+        nodes[i] = v[it];
         const int64_t d = hi[it] - lo[it];
         rec[i] = row_record(v[it], lo[it], d);
         c[it] = d < fo ? (int32_t)d : fo;
