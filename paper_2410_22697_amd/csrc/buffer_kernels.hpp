@@ -46,8 +46,21 @@ __device__ __forceinline__ int32_t hash_find_from(const uint64_t* __restrict__ t
   }
 }
 
+// box (if given): the round's k' and consistency flag go to the host, as this
+// is a round's last launch.
+struct RoundBox {
+  const int64_t* k;
+  const int32_t* bad;
+  int64_t* h_k;
+  int32_t* h_bad;
+};
 __global__ void k_hash_insert(uint64_t* __restrict__ tab, uint32_t mask, const int32_t* __restrict__ slot_id,
-                              int64_t cap, const int64_t* __restrict__ gate) {
+                              int64_t cap, const int64_t* __restrict__ gate, RoundBox box) {
+  if (box.h_k && blockIdx.x == 0 && threadIdx.x == 0) {
+    *box.h_k = *box.k;
+    *box.h_bad = *box.bad;
+    __threadfence_system();
+  }
   if (gate && *gate == 0) return;
   for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < cap;
        s += (int64_t)gridDim.x * blockDim.x) {
@@ -771,224 +784,257 @@ __global__ void k_materialize(float* __restrict__ S_E, int32_t* __restrict__ hit
   }
 }
 
-// ------------------------------------------------- ordered flag compaction
-// E = [s : S_E[s] < alpha] in ascending s, as count / scan / emit.
-__global__ __launch_bounds__(kScanNT) void k_evict_count(const float* __restrict__ S_E, int64_t cap, float alpha,
-                                                         int32_t* __restrict__ partials, int64_t* __restrict__ total) {
+// ------------------------------------------------------- a round's first part
+// In one launch: the decay of k_materialize; E = [s : S_E[s] < alpha] in
+// ascending s, by the single-pass scan; R filled with -1 (a replacement that is
+// never written is then caught by the swap); and, by the last tile, the round's
+// state: |E|, |C| = nC, k' = min(|E|, |C|), the select and the E narrowing set
+// up. |C| = H - cap always: a halo node has S_A = -1 exactly while it is
+// buffered (init, and the swap's S_A := -1 for a replacement) and S_A >= 0
+// otherwise (misses only add to it; an evicted node gets its last S_E >= 0).
+// (A round is bound by its launches where the buffer is small: 40 launches of
+// 1.5-5 us before, 8 to 19 now.)
+__global__ __launch_bounds__(kScanNT) void k_round_evict(float* __restrict__ S_E, int32_t* __restrict__ hitcnt,
+                                                         int64_t cap, int32_t steps, float gamma, float alpha,
+                                                         int32_t* __restrict__ E, int32_t* __restrict__ R,
+                                                         uint64_t* flags, uint32_t epoch,
+                                                         RoundState* __restrict__ rs, Counters* __restrict__ ctr,
+                                                         int64_t nC) {
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  int32_t s = 0;
+  __shared__ uint32_t excl_lds;
+  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  float x[kScanItems];
+  int32_t u[kScanItems];
+  int32_t most = 0;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
-    const int64_t i = base + (int64_t)it * kScanNT + threadIdx.x;
-    s += (i < cap && S_E[i] < alpha) ? 1 : 0;
+    const int64_t i = min(base + it, cap - 1);
+    x[it] = S_E[i];
+    u[it] = hitcnt[i];
   }
-  s = block_sum<kScanNT>(s, lds);
-  if (threadIdx.x == 0) {
-    partials[blockIdx.x] = s;
-    if (s) atomicAdd((unsigned long long*)total, (unsigned long long)s);
+#pragma unroll
+  for (int it = 0; it < kScanItems; ++it) {
+    pin(x[it]);
+    pin(u[it]);
+    u[it] = steps - u[it];
+    most = max(most, u[it]);
   }
-}
-
-__global__ __launch_bounds__(kScanNT) void k_evict_emit(const float* __restrict__ S_E, int64_t cap, float alpha,
-                                                        const int32_t* __restrict__ partials,
-                                                        int32_t* __restrict__ E) {
-  __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  bool f[kScanItems];
+  // one product per step in which the slot was not hit, in order (the four
+  // slots of a thread side by side)
+  for (int32_t j = 0; j < most; ++j)
+#pragma unroll
+    for (int it = 0; it < kScanItems; ++it) x[it] = j < u[it] ? __fmul_rn(x[it], gamma) : x[it];
   int32_t s = 0;
+  bool f[kScanItems];
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
     const int64_t i = base + it;
-    f[it] = i < cap && S_E[i] < alpha;
+    f[it] = i < cap && x[it] < alpha;
     s += f[it];
+    if (i < cap) {
+      S_E[i] = x[it];
+      hitcnt[i] = 0;
+      R[i] = -1;
+    }
   }
-  const int32_t before = preceding_sum<kScanNT>(partials, blockIdx.x, lds);
   int32_t tot;
-  int32_t o = block_exclusive_scan<kScanNT>(s, lds, &tot) + before;
+  const int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot);
+  const uint32_t before = lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, &ctr->bad, &excl_lds);
+  int64_t o = (int64_t)before + ex;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it)
     if (f[it]) E[o++] = (int32_t)(base + it);
-}
-
-// |C| = number of unbuffered halo nodes (S_A >= 0).
-// k' = min(|E|, |C|) on the device; sets the select and the E narrowing up.
-// |C| = H - cap always: a halo node has S_A = -1 exactly while it is buffered
-// (init, and the swap's S_A := -1 for a replacement) and S_A >= 0 otherwise
-// (misses only add to it; an evicted node gets its last S_E >= 0).
-__global__ void k_round_setup(RoundState* __restrict__ rs, Counters* __restrict__ ctr, int64_t nC) {
-  rs->nC = nC;
-  const int64_t k = rs->nE < nC ? rs->nE : nC;
-  rs->k = k;
-  rs->need = k;
-  rs->prefix = 0;
-  rs->pmask = 0;
-  rs->prefix_lo = 0;
-  rs->pmask_lo = 0;
-  rs->nE_sel = k < rs->nE ? rs->nE : 0;
-  rs->k_sel = k < rs->nE ? k : 0;
-  if (k > 0) {
-    ctr->rounds += 1;
-    ctr->evicted += k;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    const int64_t nE = (int64_t)before + tot, k = min(nE, nC);
+    rs->nE = nE;
+    rs->nC = nC;
+    rs->k = k;
+    rs->need = k;
+    rs->prefix = rs->pmask = rs->prefix_lo = rs->pmask_lo = 0;
+    rs->n_lt = rs->n_eq = 0;
+    rs->nE_sel = k < nE ? nE : 0;
+    rs->k_sel = k < nE ? k : 0;
+    rs->done = 0;
+    if (k > 0) {
+      ctr->rounds += 1;
+      ctr->evicted += k;
+    }
   }
-}
-
-template <typename T>
-__global__ void k_fill_gated(T* __restrict__ p, int64_t n, T v, const int64_t* __restrict__ gate) {
-  if (*gate == 0) return;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
 }
 
 // ------------------------------------------------------ replacement select
 // Candidate key: bitwise NOT of the fp32 bits of S_A >= 0, so ascending key
-// is descending S_A. Radix select, 8 bits per pass from the top, finds the
-// key T of the k'-th candidate and how many candidates with key T to take.
+// is descending S_A. Radix select from the top, 11, 11 and 10 bits, one launch
+// each, finds the key T of the k'-th candidate and how many candidates with key
+// T to take.
 __device__ __forceinline__ uint32_t cand_key(float a) { return ~__float_as_uint(a); }
 
-// One radix-select pass over the candidate keys (S_A >= 0, by rank) that
-// match the prefix so far. Each thread takes four consecutive scores per
-// iteration (one 16-byte load); a wave adds the lanes whose digit equals its
-// first active lane's with one LDS atomic (most candidates have S_A = 0, one
-// digit), the others one by one.
-__global__ __launch_bounds__(256) void k_select_hist(const float* __restrict__ S_A, int64_t H,
-                                                     const RoundState* __restrict__ rs, int shift,
-                                                     uint32_t* __restrict__ ghist) {
-  __shared__ uint32_t hist[256];
-  if (rs->k == 0) return;
-  hist[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t prefix = rs->prefix, pmask = rs->pmask;
-  const int lane = lane_id();
-  const int64_t H4 = H / 4;
-  const float4* S4 = reinterpret_cast<const float4*>(S_A);
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < (H + 3) / 4;
-       q += (int64_t)gridDim.x * blockDim.x) {
-    float a[4] = {-1.0f, -1.0f, -1.0f, -1.0f};
-    if (q < H4) {
-      const float4 x = S4[q];
-      a[0] = x.x;
-      a[1] = x.y;
-      a[2] = x.z;
-      a[3] = x.w;
-    } else {
-      for (int j = 0; j < 4; ++j)
-        if (4 * q + j < H) a[j] = S_A[4 * q + j];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t k = cand_key(a[j]);
-      const bool in = a[j] >= 0.0f && (k & pmask) == prefix;
-      const uint32_t d = (k >> shift) & 255u;
-      const uint64_t m = ballot(in);
-      if (!m) continue;
-      const int first = __ffsll((unsigned long long)m) - 1;
-      const uint32_t d0 = __shfl(d, first, MS_WAVE);
-      const uint64_t same = ballot(in && d == d0);
-      if (lane == first) atomicAdd(&hist[d0], (uint32_t)__popcll(same));
-      else if (in && d != d0) atomicAdd(&hist[d], 1u);
-    }
-  }
-  __syncthreads();
-  if (hist[threadIdx.x]) atomicAdd(&ghist[threadIdx.x], hist[threadIdx.x]);
-}
+constexpr int kSelBins = 2048;
+constexpr int kSelPasses = 3;
+constexpr int kSelUnroll = 4;
+constexpr int64_t kSelBlocks = 512;  // blocks of a pass at most (each adds to the one counter)
+constexpr int kSelShift[kSelPasses] = {21, 10, 0}, kSelBits[kSelPasses] = {11, 11, 10};
 
-__global__ __launch_bounds__(256) void k_select_pick(RoundState* __restrict__ rs, uint32_t* __restrict__ ghist,
-                                                     int shift, int32_t* __restrict__ bad, int lo_word = 0) {
+// The pass's pick, by its last block (256 threads): the bin that holds the
+// need-th candidate; the digit joins the prefix, and the bins are cleared.
+__device__ __forceinline__ void select_pick(RoundState* rs, uint32_t* __restrict__ ghist, int shift, int bits,
+                                            int32_t* __restrict__ bad, int lo_word) {
+  constexpr int PER = kSelBins / 256;
   __shared__ int64_t lds[256 / MS_WAVE + 1];
   __shared__ int32_t pick;
   __shared__ int64_t before;
-  if (rs->k == 0) return;
-  if (threadIdx.x == 0) {
-    pick = -1;
-    before = 0;
-  }
+  if (threadIdx.x == 0) pick = -1;
   __syncthreads();
   const int64_t need = rs->need;
-  const int64_t c = ghist[threadIdx.x];
-  int64_t tot;
-  const int64_t ex = block_exclusive_scan<256>(c, lds, &tot);
-  if (ex < need && ex + c >= need) {
-    pick = threadIdx.x;
-    before = ex;
+  const int bins = 1 << bits;
+  int64_t c[PER], s = 0, tot;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int b = threadIdx.x * PER + j;
+    c[j] = b < bins ? __hip_atomic_load(&ghist[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+  }
+#pragma unroll
+  for (int j = 0; j < PER; ++j) s += c[j];
+  int64_t ex = block_exclusive_scan<256>(s, lds, &tot);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int b = threadIdx.x * PER + j;
+    if (ex < need && ex + c[j] >= need) {
+      pick = b;
+      before = ex;
+    }
+    ex += c[j];
+    if (b < bins) ghist[b] = 0;
   }
   __syncthreads();
-  ghist[threadIdx.x] = 0;
   if (threadIdx.x == 0) {
+    rs->done = 0;
     if (pick < 0) {  // fewer candidates than asked for: never expected
       atomicOr(bad, 2);
       rs->need = 0;
     } else {
+      const uint32_t mask = (uint32_t)(bins - 1) << shift;
       rs->need = need - before;
       if (lo_word) {
         rs->prefix_lo |= (uint32_t)pick << shift;
-        rs->pmask_lo |= 255u << shift;
+        rs->pmask_lo |= mask;
       } else {
         rs->prefix |= (uint32_t)pick << shift;
-        rs->pmask |= 255u << shift;
+        rs->pmask |= mask;
       }
     }
   }
 }
 
-// In rank order r: candidates with key < T go to (keys, vals) for sorting,
-// the first `need` with key == T go straight to R[n_lt + ...]. S_A is kept by
-// rank, so both passes read it (and h_of_rank) in order.
-__global__ __launch_bounds__(kScanNT) void k_rank_count(const float* __restrict__ S_A, int64_t H,
-                                                        RoundState* __restrict__ rs,
-                                                        int32_t* __restrict__ p_lt, int32_t* __restrict__ p_eq) {
-  __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  const uint32_t T = rs->prefix;
-  const bool on = rs->k > 0;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  float a[kScanItems];
+// One radix-select pass over the candidates (S >= 0) that match the prefix so
+// far. GID: S over every global id, where the rank is part of the key (see
+// below): lo_word passes count the digits of the rank. Each thread takes four
+// consecutive scores per load, four loads per iteration; a wave adds the lanes
+// whose digit equals its first active lane's with one LDS atomic (most
+// candidates have S_A = 0, one digit), the others one by one. The last block
+// to add its bins picks.
+template <bool GID>
+__global__ __launch_bounds__(256) void k_select_pass(const float* __restrict__ S, const int32_t* __restrict__ rank_g,
+                                                     int64_t n, RoundState* rs, int lo_word, int shift, int bits,
+                                                     uint32_t* __restrict__ ghist, int32_t* __restrict__ bad) {
+  __shared__ uint32_t hist[kSelBins];
+  __shared__ int last;
+  if (rs->k == 0) return;
+  for (int i = threadIdx.x; i < kSelBins; i += 256) hist[i] = 0;
+  __syncthreads();
+  const uint32_t ph = rs->prefix, mh = rs->pmask, pl = rs->prefix_lo, ml = rs->pmask_lo;
+  const uint32_t digit = (1u << bits) - 1u;
+  const int lane = lane_id();
+  const int64_t n4 = n / 4;
+  const float4* S4 = reinterpret_cast<const float4*>(S);
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, nq = (n + 3) / 4;
+  for (int64_t q0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q0 < nq; q0 += kSelUnroll * stride) {
+    float4 x[kSelUnroll];
 #pragma unroll
-  for (int it = 0; it < kScanItems; ++it) {
-    const int64_t r = base + (int64_t)it * kScanNT + threadIdx.x;
-    a[it] = on && r < H ? S_A[r] : -1.0f;
-  }
-  int32_t clt = 0, ceq = 0;
+    for (int y = 0; y < kSelUnroll; ++y) {
+      const int64_t q = q0 + y * stride;
+      x[y] = S4[q < n4 ? q : 0];  // (S is never empty; a vector past the whole ones is read again below)
+    }
 #pragma unroll
-  for (int it = 0; it < kScanItems; ++it) {
-    if (a[it] >= 0.0f) {
-      const uint32_t k = cand_key(a[it]);
-      clt += k < T;
-      ceq += k == T;
+    for (int y = 0; y < kSelUnroll; ++y) {
+      pin(x[y].x);
+      pin(x[y].y);
+      pin(x[y].z);
+      pin(x[y].w);
+    }
+#pragma unroll
+    for (int y = 0; y < kSelUnroll; ++y) {
+      const int64_t q = q0 + y * stride;
+      float a[4] = {-1.0f, -1.0f, -1.0f, -1.0f};
+      if (q < n4) {
+        a[0] = x[y].x;
+        a[1] = x[y].y;
+        a[2] = x[y].z;
+        a[3] = x[y].w;
+      } else {
+        for (int j = 0; j < 4; ++j)
+          if (4 * q + j < n) a[j] = S[4 * q + j];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t k = cand_key(a[j]);
+        bool in = a[j] >= 0.0f && (k & mh) == ph;
+        uint32_t r = 0;
+        if (GID && lo_word) {
+          if (in) r = (uint32_t)rank_g[4 * q + j];
+          in = in && (r & ml) == pl;
+        }
+        const uint32_t d = ((GID && lo_word ? r : k) >> shift) & digit;
+        const uint64_t m = ballot(in);
+        if (!m) continue;
+        const int first = __ffsll((unsigned long long)m) - 1;
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+        const uint64_t same = ballot(in && d == d0);
+        if (lane == first) atomicAdd(&hist[d0], (uint32_t)__popcll(same));
+        else if (in && d != d0) atomicAdd(&hist[d], 1u);
+      }
     }
   }
-  clt = block_sum<kScanNT>(clt, lds);
-  ceq = block_sum<kScanNT>(ceq, lds);
-  if (threadIdx.x == 0) {
-    p_lt[blockIdx.x] = clt;
-    p_eq[blockIdx.x] = ceq;
-    if (clt) atomicAdd((unsigned long long*)&rs->n_lt, (unsigned long long)clt);
-    if (ceq) atomicAdd((unsigned long long*)&rs->n_eq, (unsigned long long)ceq);
-  }
+  __syncthreads();
+  // the bins, then the block's count: each atomic's old value is taken, so it
+  // has been performed before the barrier (a fence would write back the whole
+  // L2, beside gathers that fill it: passes of 36-350 us instead of 9-40)
+  for (int i = threadIdx.x; i <= (int)digit; i += 256)
+    if (hist[i]) {
+      uint32_t was = atomicAdd(&ghist[i], hist[i]);
+      pin(was);
+    }
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicAdd(&rs->done, 1) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  select_pick(rs, ghist, shift, bits, bad, lo_word);
 }
 
+// In rank order r: candidates with key < T go to (keys, vals) for sorting,
+// the first `need` with key == T go straight to R[n_lt + ...]. S_A is kept by
+// rank, so the one pass reads it in order; the halo ids are read only where
+// they are written. Two single-pass scans, one per class (flags_eq after
+// flags_lt); the last tile writes n_lt and n_eq.
 __global__ __launch_bounds__(kScanNT) void k_rank_emit(const float* __restrict__ S_A,
                                                        const int32_t* __restrict__ h_of_rank, int64_t H,
-                                                       const RoundState* __restrict__ rs,
-                                                       const int32_t* __restrict__ p_lt,
-                                                       const int32_t* __restrict__ p_eq,
+                                                       RoundState* rs, uint64_t* flags_lt, uint64_t* flags_eq,
+                                                       uint32_t epoch, int32_t* __restrict__ bad,
                                                        uint32_t* __restrict__ keys, int32_t* __restrict__ vals,
                                                        int32_t* __restrict__ R) {
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  if (rs->k == 0) return;
+  __shared__ uint32_t excl_lt, excl_eq;
+  const int64_t kk = rs->k, need = rs->need;
   const uint32_t T = rs->prefix;
-  const int64_t need = rs->need, n_lt = rs->k - rs->need;
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  uint32_t k[kScanItems];
   float a[kScanItems];
-  int32_t h[kScanItems];
+#pragma unroll
+  for (int it = 0; it < kScanItems; ++it) a[it] = base + it < H ? S_A[base + it] : -1.0f;
+  if (kk == 0) return;
+  const int64_t n_lt = kk - need;
+  uint32_t k[kScanItems];
   bool lt[kScanItems], eq[kScanItems];
   int32_t clt = 0, ceq = 0;
-#pragma unroll
-  for (int it = 0; it < kScanItems; ++it) {
-    const int64_t r = base + it;
-    a[it] = r < H ? S_A[r] : -1.0f;
-    h[it] = r < H ? h_of_rank[r] : -1;
-  }
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
     k[it] = cand_key(a[it]);
@@ -997,21 +1043,28 @@ __global__ __launch_bounds__(kScanNT) void k_rank_emit(const float* __restrict__
     clt += lt[it];
     ceq += eq[it];
   }
-  const int32_t blt = preceding_sum<kScanNT>(p_lt, blockIdx.x, lds);
-  const int32_t beq = preceding_sum<kScanNT>(p_eq, blockIdx.x, lds);
   int32_t tlt, teq;
-  int64_t olt = (int64_t)block_exclusive_scan<kScanNT>(clt, lds, &tlt) + blt;
-  int64_t oeq = (int64_t)block_exclusive_scan<kScanNT>(ceq, lds, &teq) + beq;
+  const int32_t xlt = block_exclusive_scan<kScanNT>(clt, lds, &tlt);
+  const int32_t xeq = block_exclusive_scan<kScanNT>(ceq, lds, &teq);
+  const uint32_t blt = lookback_exclusive(flags_lt, blockIdx.x, (uint32_t)tlt, epoch, bad, &excl_lt);
+  const uint32_t beq = lookback_exclusive(flags_eq, blockIdx.x, (uint32_t)teq, epoch, bad, &excl_eq);
+  int64_t olt = (int64_t)blt + xlt, oeq = (int64_t)beq + xeq;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
     if (lt[it]) {
-      keys[olt] = k[it];
-      vals[olt] = h[it];
+      if (olt < n_lt) {  // (always: T is the k'-th key)
+        keys[olt] = k[it];
+        vals[olt] = h_of_rank[base + it];
+      }
       ++olt;
     } else if (eq[it]) {
-      if (oeq < need) R[n_lt + oeq] = h[it];
+      if (oeq < need) R[n_lt + oeq] = h_of_rank[base + it];
       ++oeq;
     }
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    rs->n_lt = (int64_t)blt + tlt;
+    rs->n_eq = (int64_t)beq + teq;
   }
 }
 
@@ -1026,92 +1079,25 @@ __global__ void k_scores_by_id(const float* __restrict__ S_A, const int32_t* __r
 // With S_A over every global id g (non-halo ids hold -1 and are never
 // candidates), the scan runs in id order, not rank order, so the rank is part
 // of the key: candidate g has the 64-bit key (cand_key(S_A[g]), rank_g[g]),
-// unique per candidate. An exact radix select over it, 8 bits per pass from
-// the top (four passes on the score word, then four on the rank word), finds
-// the k'-th smallest key T; the replacements are exactly the keys <= T, which
-// are emitted and sorted by (score, rank). Each thread takes four
-// consecutive entries per iteration; a wave adds the lanes whose digit equals
-// its first active lane's with one LDS atomic.
-__global__ __launch_bounds__(256) void k_gselect_hist(const float* __restrict__ S, const int32_t* __restrict__ rank_g,
-                                                      int64_t n, const RoundState* __restrict__ rs, int lo_word,
-                                                      int shift, uint32_t* __restrict__ ghist) {
-  __shared__ uint32_t hist[256];
-  if (rs->k == 0) return;
-  hist[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t ph = rs->prefix, mh = rs->pmask, pl = rs->prefix_lo, ml = rs->pmask_lo;
-  const int lane = lane_id();
-  const int64_t n4 = n / 4;
-  const float4* S4 = reinterpret_cast<const float4*>(S);
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < (n + 3) / 4;
-       q += (int64_t)gridDim.x * blockDim.x) {
-    float a[4] = {-1.0f, -1.0f, -1.0f, -1.0f};
-    if (q < n4) {
-      const float4 x = S4[q];
-      a[0] = x.x;
-      a[1] = x.y;
-      a[2] = x.z;
-      a[3] = x.w;
-    } else {
-      for (int j = 0; j < 4; ++j)
-        if (4 * q + j < n) a[j] = S[4 * q + j];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t k = cand_key(a[j]);
-      bool in = a[j] >= 0.0f && (k & mh) == ph;
-      uint32_t r = 0;
-      if (lo_word && in) r = (uint32_t)rank_g[4 * q + j];
-      in = in && (!lo_word || (r & ml) == pl);
-      const uint32_t d = ((lo_word ? r : k) >> shift) & 255u;
-      const uint64_t m = ballot(in);
-      if (!m) continue;
-      const int first = __ffsll((unsigned long long)m) - 1;
-      const uint32_t d0 = __shfl(d, first, MS_WAVE);
-      const uint64_t same = ballot(in && d == d0);
-      if (lane == first) atomicAdd(&hist[d0], (uint32_t)__popcll(same));
-      else if (in && d != d0) atomicAdd(&hist[d], 1u);
-    }
-  }
-  __syncthreads();
-  if (hist[threadIdx.x]) atomicAdd(&ghist[threadIdx.x], hist[threadIdx.x]);
-}
-
+// unique per candidate. An exact radix select over it (three passes on the
+// score word, then three on the rank word: k_select_pass) finds the k'-th
+// smallest key T; the replacements are exactly the keys <= T, which are emitted
+// and sorted by (score, rank).
 __device__ __forceinline__ bool gsel_in(float a, uint32_t r, uint32_t th, uint32_t tl) {
   if (!(a >= 0.0f)) return false;
   const uint32_t k = cand_key(a);
   return k < th || (k == th && r <= tl);
 }
 
-// Per tile of kScanTile ids: how many replacements (keys <= T) it holds.
-__global__ __launch_bounds__(kScanNT) void k_gsel_count(const float* __restrict__ S, const int32_t* __restrict__ rank_g,
-                                                        int64_t n, const RoundState* __restrict__ rs,
-                                                        int32_t* __restrict__ partials) {
-  __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  const bool on = rs->k > 0;
-  const uint32_t th = rs->prefix, tl = rs->prefix_lo;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  int32_t c = 0;
-#pragma unroll
-  for (int it = 0; it < kScanItems; ++it) {
-    const int64_t g = base + (int64_t)it * kScanNT + threadIdx.x;
-    if (on && g < n) {
-      const float a = S[g];
-      if (a >= 0.0f) c += gsel_in(a, (uint32_t)rank_g[g], th, tl);
-    }
-  }
-  c = block_sum<kScanNT>(c, lds);
-  if (threadIdx.x == 0) partials[blockIdx.x] = c;
-}
-
-// Emits the replacements in id order as (rank, halo id) pairs at the tile's
-// prefix (partials scanned by k_scan_partials).
+// Emits the replacements (keys <= T) in id order as (rank, halo id) pairs, by
+// the single-pass scan.
 __global__ __launch_bounds__(kScanNT) void k_gsel_emit(const float* __restrict__ S, const int32_t* __restrict__ rank_g,
                                                        const int32_t* __restrict__ h_of_rank, int64_t n,
-                                                       const RoundState* __restrict__ rs,
-                                                       const int32_t* __restrict__ partials, uint32_t* __restrict__ keys,
-                                                       int32_t* __restrict__ vals) {
+                                                       const RoundState* __restrict__ rs, uint64_t* flags,
+                                                       uint32_t epoch, int32_t* __restrict__ bad, int64_t cap,
+                                                       uint32_t* __restrict__ keys, int32_t* __restrict__ vals) {
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
+  __shared__ uint32_t excl_lds;
   if (rs->k == 0) return;
   const uint32_t th = rs->prefix, tl = rs->prefix_lo;
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
@@ -1127,12 +1113,15 @@ __global__ __launch_bounds__(kScanNT) void k_gsel_emit(const float* __restrict__
     c += f[it];
   }
   int32_t tot;
-  int64_t o = (int64_t)block_exclusive_scan<kScanNT>(c, lds, &tot) + partials[blockIdx.x];
+  const int32_t ex = block_exclusive_scan<kScanNT>(c, lds, &tot);
+  int64_t o = (int64_t)lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, bad, &excl_lds) + ex;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it)
     if (f[it]) {
-      keys[o] = (uint32_t)r[it];
-      vals[o] = h_of_rank[r[it]];
+      if (o < cap) {  // (always: k' of them)
+        keys[o] = (uint32_t)r[it];
+        vals[o] = h_of_rank[r[it]];
+      }
       ++o;
     }
 }
@@ -1245,24 +1234,11 @@ __global__ __launch_bounds__(kSortNT) void k_sort_scatter(const uint32_t* __rest
   }
 }
 
-// Generic exclusive scan of an int32 array with host-known length.
-__global__ __launch_bounds__(kScanNT) void k_tile_reduce(const int32_t* __restrict__ a, int64_t len,
-                                                         int32_t* __restrict__ partials) {
+// Exclusive scan of the block histograms, in place, by the single-pass scan.
+__global__ __launch_bounds__(kScanNT) void k_sort_scan(int32_t* __restrict__ a, int64_t len, uint64_t* flags,
+                                                       uint32_t epoch, int32_t* __restrict__ bad) {
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  int32_t s = 0;
-#pragma unroll
-  for (int it = 0; it < kScanItems; ++it) {
-    const int64_t i = base + (int64_t)it * kScanNT + threadIdx.x;
-    if (i < len) s += a[i];
-  }
-  s = block_sum<kScanNT>(s, lds);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
-__global__ __launch_bounds__(kScanNT) void k_tile_scan(int32_t* __restrict__ a, int64_t len,
-                                                       const int32_t* __restrict__ partials) {
-  __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
+  __shared__ uint32_t excl_lds;
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   int32_t v[kScanItems];
   int32_t s = 0;
@@ -1272,11 +1248,59 @@ __global__ __launch_bounds__(kScanNT) void k_tile_scan(int32_t* __restrict__ a, 
     s += v[it];
   }
   int32_t tot;
-  int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot) + partials[blockIdx.x];
+  int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot);
+  ex += (int32_t)lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, bad, &excl_lds);
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
     if (base + it < len) a[base + it] = ex;
     ex += v[it];
+  }
+}
+
+// The whole stable sort of up to kSortOne pairs by one block, in one launch:
+// bitonic over (key, position) words in LDS. Where the bound is larger the
+// digit passes above take it: a block's 4096 words take ~12 us whatever the
+// chip, twelve launches ~40 us whatever the pairs.
+constexpr int kSortOne = 4096;
+__global__ __launch_bounds__(kScanNT) void k_sort_one(const uint32_t* __restrict__ keys,
+                                                      const int32_t* __restrict__ vals,
+                                                      const int64_t* __restrict__ n_ptr, int64_t n_const,
+                                                      int64_t bound, uint32_t* __restrict__ keys_out,
+                                                      int32_t* __restrict__ vals_out) {
+  __shared__ uint64_t w[kSortOne];
+  const int n = (int)min(min(size_of(n_ptr, n_const), bound), (int64_t)kSortOne);
+  int m = 2;
+  while (m < n) m <<= 1;
+  for (int i = threadIdx.x; i < m; i += kScanNT) w[i] = i < n ? ((uint64_t)keys[i] << 32) | (uint32_t)i : ~0ull;
+  __syncthreads();
+  for (int size = 2; size <= m; size <<= 1)
+    for (int step = size >> 1; step > 0; step >>= 1) {
+      for (int p = threadIdx.x; p < m / 2; p += kScanNT) {
+        const int i = 2 * p - (p & (step - 1)), j = i + step;  // the pair's places
+        const bool up = (i & size) == 0;
+        const uint64_t x = w[i], y = w[j];
+        if ((x > y) == up) {
+          w[i] = y;
+          w[j] = x;
+        }
+      }
+      __syncthreads();
+    }
+  // (the values are read before any is written: the two arrays may be one)
+  int32_t v[kSortOne / kScanNT];
+#pragma unroll
+  for (int it = 0; it < kSortOne / kScanNT; ++it) {
+    const int i = it * kScanNT + threadIdx.x;
+    v[it] = i < n ? vals[(uint32_t)w[i]] : 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < kSortOne / kScanNT; ++it) {
+    const int i = it * kScanNT + threadIdx.x;
+    if (i < n) {
+      keys_out[i] = (uint32_t)(w[i] >> 32);
+      vals_out[i] = v[it];
+    }
   }
 }
 
@@ -1351,8 +1375,12 @@ __global__ void k_swap(const int32_t* __restrict__ E, const int32_t* __restrict_
                        float* __restrict__ S_A, const int32_t* __restrict__ sa_idx,
                        int32_t* __restrict__ out_ev, int32_t* __restrict__ out_slot,
                        int32_t* __restrict__ out_rep, int2* __restrict__ fill, int32_t* __restrict__ bad,
-                       int32_t* __restrict__ slot_round, int32_t round_id) {
+                       int32_t* __restrict__ slot_round, int32_t round_id, uint64_t* __restrict__ tab, int64_t hcap) {
   const int64_t k = *k_ptr;
+  if (k == 0) return;
+  // (the table is rebuilt by the launch after this one)
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < hcap; i += (int64_t)gridDim.x * blockDim.x)
+    tab[i] = kEmpty;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += (int64_t)gridDim.x * blockDim.x) {
     const int32_t s = E[i], r = R[i];
     if (s < 0 || s >= cap || r < 0 || r >= H) {  // never expected: flag, do not touch memory

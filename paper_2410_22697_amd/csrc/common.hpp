@@ -162,6 +162,7 @@ struct RoundState {
   uint32_t prefix_lo, pmask_lo;  // ... and of its rank word (scores by global id)
   int64_t n_lt, n_eq;      // candidates strictly before / equal to the threshold
   int64_t nE_sel, k_sel;   // |E| and k' when k' < |E| (E must be narrowed), else 0
+  int32_t done, pad;       // blocks of the current select pass that have added their bins
 };
 
 // Totals over the context's life (device side).

@@ -121,7 +121,7 @@ struct massive_ctx {
   float alpha = 1.0f;
   int64_t W = 0;        // bitmap words
   int64_t map_words = 0;  // words of one copy of a bitmap (W and its padding)
-  int64_t pmax = 0;     // partials capacity
+  int64_t round_tiles = 0;  // tiles of a round's largest scan
   int64_t sort_cap = 0; // radix sort capacity
   int64_t hbm_blocks = 4096;  // grid bound of the HBM gather
   // Grid of the miss gather (host link). Its reads hold memory-system
@@ -229,7 +229,6 @@ struct massive_ctx {
   const int32_t* d_sa_idx = nullptr; // [H] S_A index of halo h (d_rank_of or d_gid)
   int32_t* d_gid = nullptr;          // [H] global id of halo h
   int32_t* d_rank_g = nullptr;       // [n_global] by global id: rank of that halo node, -1 elsewhere
-  int32_t* d_gpart = nullptr;        // tile partials of the global-id selection
   int64_t* d_deg = nullptr;          // [H] degrees, during init only
   uint64_t* d_tab = nullptr;
   int32_t* d_pos_of = nullptr;
@@ -243,14 +242,16 @@ struct massive_ctx {
   ms::StepSizes* hd_sz = nullptr;     // device views of the mailboxes
   int32_t* hd_bad = nullptr;
   ms::RoundState* d_rs = nullptr;
-  ms::RoundState* h_rs = nullptr;     // pinned mailbox
+  ms::RoundState* h_rs = nullptr;     // pinned mailbox of a round's k'
+  ms::RoundState* hd_rs = nullptr;    //   (device views of it and of h_ctr)
+  ms::Counters* hd_ctr = nullptr;
   ms::Counters* d_ctr = nullptr;
   ms::Counters* h_ctr = nullptr;      // pinned
   int32_t* d_slot_round = nullptr;    // [cap] round whose swap last filled the slot
   int32_t* d_landed = nullptr;        // [cap] round whose refill row has landed
-  int32_t* d_part = nullptr;
-  int32_t* d_part2 = nullptr;
-  uint64_t* d_scan_flags = nullptr;  // the seed rows' single-pass scan (rounds use d_part, d_part2)
+  uint64_t* d_round_flags = nullptr;  // [2][round_tiles] single-pass scans of the rounds (and of init's sorts)
+  uint32_t round_epoch = 0;           // of the last of them launched
+  uint64_t* d_scan_flags = nullptr;  // the seed rows' single-pass scan
   int64_t scan_tiles = 0;
   uint32_t scan_epoch = 0;           // of the last scan launched
   // gather lists by step slot (written by classify, read by the side stream)
@@ -375,29 +376,41 @@ struct massive_ctx {
 
 namespace {
 
-// one stable LSD pass: (kin, vin) -> (kout, vout) by 8-bit digit at `shift`
-int sort_pass(massive_ctx* c, hipStream_t s, const uint32_t* kin, const int32_t* vin, const int64_t* n_ptr,
-              int64_t n_const, int64_t bound, int shift, uint32_t* kout, int32_t* vout) {
-  const int64_t nb = std::max<int64_t>(1, cdiv(bound, ms::kSortTile));
-  ms::k_sort_hist<<<(unsigned)nb, ms::kSortNT, 0, s>>>(kin, n_ptr, n_const, bound, shift, nb, c->d_hist);
-  const int64_t len = 256 * nb, nb2 = std::max<int64_t>(1, cdiv(len, ms::kScanTile));
-  ms::k_tile_reduce<<<(unsigned)nb2, ms::kScanNT, 0, s>>>(c->d_hist, len, c->d_part);
-  ms::k_scan_partials<<<1, ms::kScanNT, 0, s>>>(c->d_part, nb2, nullptr, nullptr);
-  ms::k_tile_scan<<<(unsigned)nb2, ms::kScanNT, 0, s>>>(c->d_hist, len, c->d_part);
-  ms::k_sort_scatter<<<(unsigned)nb, ms::kSortNT, 0, s>>>(kin, vin, n_ptr, n_const, bound, shift, nb, c->d_hist, kout,
-                                                          vout);
-  return MASSIVE_OK;
+// The epoch of the next single-pass scan of a round (or of init's sorts), on
+// the stream that the scan runs on: rounds follow each other in stream order.
+uint32_t next_round_epoch(massive_ctx* c, hipStream_t s) {
+  if (c->round_epoch >= (1u << 30)) {
+    ms::k_fill<uint64_t><<<grid_for(2 * c->round_tiles, 256), 256, 0, s>>>(c->d_round_flags, 2 * c->round_tiles, 0ull);
+    c->round_epoch = 0;
+  }
+  return ++c->round_epoch;
 }
 
-// four passes of 8 bits; the result lands in (k0, v0), or its values in
-// `vals_final` if given.
-int sort_u32(massive_ctx* c, hipStream_t s, const int64_t* n_ptr, int64_t n_const, int64_t bound,
-             int32_t* vals_final) {
+// one stable LSD pass: (kin, vin) -> (kout, vout) by 8-bit digit at `shift`
+void sort_pass(massive_ctx* c, hipStream_t s, const uint32_t* kin, const int32_t* vin, const int64_t* n_ptr,
+               int64_t n_const, int64_t bound, int shift, uint32_t* kout, int32_t* vout) {
+  const int64_t nb = std::max<int64_t>(1, cdiv(bound, ms::kSortTile));
+  ms::k_sort_hist<<<(unsigned)nb, ms::kSortNT, 0, s>>>(kin, n_ptr, n_const, bound, shift, nb, c->d_hist);
+  const int64_t len = 256 * nb;
+  ms::k_sort_scan<<<(unsigned)cdiv(len, ms::kScanTile), ms::kScanNT, 0, s>>>(c->d_hist, len, c->d_round_flags,
+                                                                             next_round_epoch(c, s), &c->d_ctr->bad);
+  ms::k_sort_scatter<<<(unsigned)nb, ms::kSortNT, 0, s>>>(kin, vin, n_ptr, n_const, bound, shift, nb, c->d_hist, kout,
+                                                          vout);
+}
+
+// A stable sort of (k0, v0) by key; the result lands in (k0, v0), or its
+// values in `vals_final` if given. Four passes of 8 bits, or one block.
+void sort_u32(massive_ctx* c, hipStream_t s, const int64_t* n_ptr, int64_t n_const, int64_t bound,
+              int32_t* vals_final) {
+  int32_t* vals = vals_final ? vals_final : c->d_v0;
+  if (bound <= ms::kSortOne) {
+    ms::k_sort_one<<<1, ms::kScanNT, 0, s>>>(c->d_k0, c->d_v0, n_ptr, n_const, bound, c->d_k0, vals);
+    return;
+  }
   sort_pass(c, s, c->d_k0, c->d_v0, n_ptr, n_const, bound, 0, c->d_k1, c->d_v1);
   sort_pass(c, s, c->d_k1, c->d_v1, n_ptr, n_const, bound, 8, c->d_k0, c->d_v0);
   sort_pass(c, s, c->d_k0, c->d_v0, n_ptr, n_const, bound, 16, c->d_k1, c->d_v1);
-  sort_pass(c, s, c->d_k1, c->d_v1, n_ptr, n_const, bound, 24, c->d_k0, vals_final ? vals_final : c->d_v0);
-  return MASSIVE_OK;
+  sort_pass(c, s, c->d_k1, c->d_v1, n_ptr, n_const, bound, 24, c->d_k0, vals);
 }
 
 bool device_visible(const void* p) {
@@ -803,10 +816,10 @@ void free_ctx(massive_ctx* c) {
   (void)hipDeviceSynchronize();
   void* dev[] = {c->d_indptr, c->d_indices, c->d_slab, c->d_slot_id, c->d_S_E, c->d_hitcnt, c->d_S_A,
                  c->d_rank_of, c->d_h_of_rank, c->d_tab, c->d_pos_of, c->d_bits, c->d_rec, c->d_sz, c->d_rs,
-                 c->d_part, c->d_part2, c->d_scan_flags, c->d_dummy, c->d_E, c->d_R,
+                 c->d_round_flags, c->d_scan_flags, c->d_dummy, c->d_E, c->d_R,
                  c->d_fill, c->d_ctr, c->d_slot_round, c->d_landed,
                  c->d_k0, c->d_k1, c->d_v0, c->d_v1, c->d_hist, c->d_ghist, c->d_big,
-                 c->d_gid, c->d_rank_g, c->d_gpart, c->d_deg};
+                 c->d_gid, c->d_rank_g, c->d_deg};
   for (void* p : dev)
     if (p) (void)hipFree(p);
   for (int i = 0; i < kSlots; ++i)
@@ -884,8 +897,8 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   c->hmask = (uint32_t)(c->hcap - 1);
   c->W = cdiv(c->R, 32);
   c->sort_cap = std::max<int64_t>(std::max<int64_t>(c->H, c->cap), 1);
-  c->pmax = std::max(cdiv(c->R, ms::kScanTile), cdiv(256 * cdiv(c->sort_cap, ms::kSortTile), ms::kScanTile));
-  c->pmax = std::max<int64_t>(c->pmax, cdiv(c->W, ms::kScanTile)) + 8;
+  c->round_tiles = std::max(cdiv(std::max<int64_t>(c->sort_cap, c->n_sa), ms::kScanTile),
+                            cdiv(256 * cdiv(c->sort_cap, ms::kSortTile), ms::kScanTile));
   // Eq. 1 with S_E at its initial value 1: alpha = gamma^delta in fp32 products
   // (once a product no longer changes the value, e.g. at 0, the rest cannot)
   float al = 1.0f;
@@ -967,7 +980,6 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_gid, H * 4);
   if (c->layout == MASSIVE_SCORES_BY_GID) {
     CKA(c->d_rank_g, c->n_sa * 4);
-    CKA(c->d_gpart, (cdiv(c->n_sa, ms::kScanTile) + 8) * 4);
   }
   CKA(c->d_rank_of, H * 4);
   CKA(c->d_h_of_rank, H * 4);
@@ -989,8 +1001,7 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_ctr, sizeof(ms::Counters));
   CKA(c->d_slot_round, cap * 4);
   CKA(c->d_landed, cap * 4);
-  CKA(c->d_part, c->pmax * 4);
-  CKA(c->d_part2, c->pmax * 4);
+  CKA(c->d_round_flags, 2 * c->round_tiles * 8);
   c->scan_tiles = cdiv(R, ms::kScanTile) + 1;
   CKA(c->d_scan_flags, (c->scan_tiles + cdiv(R, fs.rows()) + cdiv(c->W, fs.tw)) * 8);
   c->d_tile_flags = c->d_scan_flags + c->scan_tiles;
@@ -1008,14 +1019,16 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_v0, c->sort_cap * 4);
   CKA(c->d_v1, c->sort_cap * 4);
   CKA(c->d_hist, 256 * cdiv(c->sort_cap, ms::kSortTile) * 4);
-  CKA(c->d_ghist, 256 * 4);
+  CKA(c->d_ghist, ms::kSelBins * 4);
   if (hipHostMalloc((void**)&c->h_sz, kSlots * sizeof(ms::StepSizes), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->h_rs, sizeof(ms::RoundState), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->h_bad, kSlots * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->h_ctr, sizeof(ms::Counters), hipHostMallocDefault) != hipSuccess)
     return c->fail(MASSIVE_ENOMEM, "hipHostMalloc of the size mailboxes failed");
   if (hipHostGetDevicePointer((void**)&c->hd_sz, c->h_sz, 0) != hipSuccess || !c->hd_sz ||
-      hipHostGetDevicePointer((void**)&c->hd_bad, c->h_bad, 0) != hipSuccess || !c->hd_bad)
+      hipHostGetDevicePointer((void**)&c->hd_bad, c->h_bad, 0) != hipSuccess || !c->hd_bad ||
+      hipHostGetDevicePointer((void**)&c->hd_rs, c->h_rs, 0) != hipSuccess || !c->hd_rs ||
+      hipHostGetDevicePointer((void**)&c->hd_ctr, c->h_ctr, 0) != hipSuccess || !c->hd_ctr)
     return c->fail(MASSIVE_EHIP, "the size mailboxes have no device view");
   if (c->staged()) {
     // host rows of each slot's misses (at most H per step), of a round's fill
@@ -1059,8 +1072,9 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
     c->long_rows = c->h_ctr->evicted;
   }
   CK(hipMemsetAsync(c->d_bits, 0, (fs.copies + 1) * c->map_words * 4, s));
-  CK(hipMemsetAsync(c->d_ghist, 0, 256 * 4, s));
+  CK(hipMemsetAsync(c->d_ghist, 0, ms::kSelBins * 4, s));
   CK(hipMemsetAsync(c->d_scan_flags, 0, c->scan_tiles * 8, s));
+  CK(hipMemsetAsync(c->d_round_flags, 0, 2 * c->round_tiles * 8, s));
   CK(hipMemsetAsync(c->d_ctr, 0, sizeof(ms::Counters), s));
   CK(hipMemsetAsync(c->d_slot_round, 0xFF, cap * 4, s));
   CK(hipMemsetAsync(c->d_landed, 0xFF, cap * 4, s));
@@ -1097,7 +1111,8 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   if (cap > 0) {
     ms::k_init_buffer<<<grid_for(cap, 256), 256, 0, s>>>(c->d_h_of_rank, cap, c->L, c->d_slot_id, c->d_S_E,
                                                          c->d_hitcnt, c->d_S_A, c->d_sa_idx, c->d_fill);
-    ms::k_hash_insert<<<grid_for(cap, 256), 256, 0, s>>>(c->d_tab, c->hmask, c->d_slot_id, cap, nullptr);
+    ms::k_hash_insert<<<grid_for(cap, 256), 256, 0, s>>>(c->d_tab, c->hmask, c->d_slot_id, cap, nullptr,
+                                                         ms::RoundBox{});
     // the cap best-ranked rows arrive over the host link
     c->h_rs->k = cap;
     CK(hipMemcpyAsync(&c->d_rs->k, &c->h_rs->k, 8, hipMemcpyHostToDevice, s));
@@ -1772,14 +1787,10 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
     CK(hipStreamWaitEvent(s, c->slot_both[tl % kSlots] ? c->ev_cls_done[tl % kSlots] : c->ev_hbm_done[tl % kSlots], 0));
   {
     massive_ctx::Range tr(c, s, 4);
-    ms::k_materialize<<<grid_for(cap, 256), 256, 0, s>>>(c->d_S_E, c->d_hitcnt, cap, (int32_t)(c->t - c->mat_t),
-                                                          c->gamma);
+    ms::k_round_evict<<<(unsigned)cdiv(cap, ms::kScanTile), ms::kScanNT, 0, s>>>(
+        c->d_S_E, c->d_hitcnt, cap, (int32_t)(c->t - c->mat_t), c->gamma, c->alpha, c->d_E, c->d_R, c->d_round_flags,
+        next_round_epoch(c, s), rs, c->d_ctr, H - cap);
     c->mat_t = c->t;
-    CK(hipMemsetAsync(rs, 0, sizeof(ms::RoundState), s));
-    const int64_t nbe = std::max<int64_t>(1, cdiv(cap, ms::kScanTile));
-    ms::k_evict_count<<<(unsigned)nbe, ms::kScanNT, 0, s>>>(c->d_S_E, cap, c->alpha, c->d_part, &rs->nE);
-    ms::k_evict_emit<<<(unsigned)nbe, ms::kScanNT, 0, s>>>(c->d_S_E, cap, c->alpha, c->d_part, c->d_E);
-    ms::k_round_setup<<<1, 1, 0, s>>>(rs, c->d_ctr, H - cap);
     // fewer candidates than evictions: keep the k' slots of smallest (S_E,
     // rank). With |C| = H - cap >= cap >= |E| (f <= 50%) it cannot happen and
     // the narrowing is not launched; otherwise its kernels see zero elements
@@ -1793,54 +1804,42 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
       ms::k_esel_keys_slot<<<grid_for(cap, 256), 256, 0, s>>>(c->d_v0, &rs->k_sel, c->d_k0);
       sort_u32(c, s, &rs->k_sel, 0, cap, c->d_E);
     }
-    ms::k_fill_gated<int32_t><<<grid_for(cap, 256), 256, 0, s>>>(c->d_R, cap, -1, &rs->k);
     if (c->layout == MASSIVE_SCORES_BY_GID) {
       // S_A over every global id, scanned in id order: an exact radix select
       // over the 64-bit key (score word, rank), then the k' keys below or at
       // it, sorted by rank and then stably by score
       const int64_t n = c->n_sa;
       for (int word = 0; word < 2; ++word)
-        for (int shift = 24; shift >= 0; shift -= 8) {
-          ms::k_gselect_hist<<<grid_for(cdiv(n, 4), 256, 4096), 256, 0, s>>>(c->d_S_A, c->d_rank_g, n, rs, word,
-                                                                           shift, c->d_ghist);
-          ms::k_select_pick<<<1, 256, 0, s>>>(rs, c->d_ghist, shift, &c->d_ctr->bad, word);
-        }
-      const int64_t nbg = std::max<int64_t>(1, cdiv(n, ms::kScanTile));
-      ms::k_gsel_count<<<(unsigned)nbg, ms::kScanNT, 0, s>>>(c->d_S_A, c->d_rank_g, n, rs, c->d_gpart);
-      ms::k_scan_partials<<<1, ms::kScanNT, 0, s>>>(c->d_gpart, nbg, nullptr, nullptr);
-      ms::k_gsel_emit<<<(unsigned)nbg, ms::kScanNT, 0, s>>>(c->d_S_A, c->d_rank_g, c->d_h_of_rank, n, rs,
-                                                            c->d_gpart, c->d_k0, c->d_v0);
+        for (int p = 0; p < ms::kSelPasses; ++p)
+          ms::k_select_pass<true><<<grid_for(cdiv(n, 4), 256, ms::kSelBlocks), 256, 0, s>>>(
+              c->d_S_A, c->d_rank_g, n, rs, word, ms::kSelShift[p], ms::kSelBits[p], c->d_ghist, &c->d_ctr->bad);
+      ms::k_gsel_emit<<<(unsigned)cdiv(n, ms::kScanTile), ms::kScanNT, 0, s>>>(
+          c->d_S_A, c->d_rank_g, c->d_h_of_rank, n, rs, c->d_round_flags, next_round_epoch(c, s), &c->d_ctr->bad, cap,
+          c->d_k0, c->d_v0);
       sort_u32(c, s, &rs->k, 0, cap, nullptr);
       ms::k_gsel_keys<<<grid_for(cap, 256), 256, 0, s>>>(c->d_v0, &rs->k, c->d_S_A, c->d_sa_idx, c->d_k0);
       sort_u32(c, s, &rs->k, 0, cap, c->d_R);
-    } else {
-      // radix select of the k'-th candidate key, 8 bits per pass
-      for (int shift = 24; shift >= 0; shift -= 8) {
-        ms::k_select_hist<<<grid_for(H, 256, 2048), 256, 0, s>>>(c->d_S_A, H, rs, shift, c->d_ghist);
-        ms::k_select_pick<<<1, 256, 0, s>>>(rs, c->d_ghist, shift, &c->d_ctr->bad);
-      }
-      const int64_t nbh = std::max<int64_t>(1, cdiv(H, ms::kScanTile));
-      ms::k_rank_count<<<(unsigned)nbh, ms::kScanNT, 0, s>>>(c->d_S_A, H, rs, c->d_part, c->d_part2);
-      ms::k_rank_emit<<<(unsigned)nbh, ms::kScanNT, 0, s>>>(c->d_S_A, c->d_h_of_rank, H, rs, c->d_part, c->d_part2,
-                                                            c->d_k0, c->d_v0, c->d_R);
+    } else if (H > cap) {  // (no candidates otherwise: k' = 0)
+      for (int p = 0; p < ms::kSelPasses; ++p)
+        ms::k_select_pass<false><<<grid_for(cdiv(H, 4), 256, ms::kSelBlocks), 256, 0, s>>>(
+            c->d_S_A, nullptr, H, rs, 0, ms::kSelShift[p], ms::kSelBits[p], c->d_ghist, &c->d_ctr->bad);
+      ms::k_rank_emit<<<(unsigned)cdiv(H, ms::kScanTile), ms::kScanNT, 0, s>>>(
+          c->d_S_A, c->d_h_of_rank, H, rs, c->d_round_flags, c->d_round_flags + c->round_tiles, next_round_epoch(c, s),
+          &c->d_ctr->bad, c->d_k0, c->d_v0, c->d_R);
       // candidates before the threshold: stable sort by key (S_A desc), rank order kept for ties
       sort_u32(c, s, &rs->n_lt, 0, cap, c->d_R);
     }
     c->round_id += 1;
-    ms::k_swap<<<grid_for(cap, 256), 256, 0, s>>>(c->d_E, c->d_R, &rs->k, c->L, cap, c->H, c->d_slot_id, c->d_S_E,
-                                                  c->d_S_A, c->d_sa_idx, evicted, slots, replaced, c->d_fill, &c->d_ctr->bad,
-                                                  c->d_slot_round, c->round_id);
-    ms::k_fill_gated<uint64_t><<<grid_for(c->hcap, 256), 256, 0, s>>>(c->d_tab, c->hcap, ms::kEmpty, &rs->k);
-    ms::k_hash_insert<<<grid_for(cap, 256), 256, 0, s>>>(c->d_tab, c->hmask, c->d_slot_id, cap, &rs->k);
+    ms::k_swap<<<grid_for(std::max(cap, c->hcap), 256), 256, 0, s>>>(
+        c->d_E, c->d_R, &rs->k, c->L, cap, c->H, c->d_slot_id, c->d_S_E, c->d_S_A, c->d_sa_idx, evicted, slots, replaced,
+        c->d_fill, &c->d_ctr->bad, c->d_slot_round, c->round_id, c->d_tab, c->hcap);
+    const ms::RoundBox box{&rs->k, &c->d_ctr->bad, &c->hd_rs->k, &c->hd_ctr->bad};
+    ms::k_hash_insert<<<grid_for(cap, 256), 256, 0, s>>>(c->d_tab, c->hmask, c->d_slot_id, cap, &rs->k, box);
   }
   if (c->staged()) {  // the fill list's host rows, for the worker's refill chunks
     ms::k_rows_out<<<grid_for(cap, 256, 1024), 256, 0, s>>>(c->d_fill, &rs->k, cap, c->hd_fill_rows,
                                                             c->hd_cnt + kSlots);
     CK(hipEventRecord(c->ev_fill_ready, s));
-  }
-  if (k_out) {
-    CK(hipMemcpyAsync(&c->h_rs->k, &rs->k, 8, hipMemcpyDeviceToHost, s));
-    CK(hipMemcpyAsync(c->h_ctr, c->d_ctr, sizeof(ms::Counters), hipMemcpyDeviceToHost, s));
   }
   CK(hipEventRecord(c->ev_round_done, s));
   c->round_unclassified = true;

@@ -12,15 +12,6 @@ constexpr int kScanTile = kScanNT * kScanItems;
 
 __device__ __forceinline__ int64_t size_of(const int64_t* p, int64_t c) { return p ? *p : c; }
 
-// Sum of partials[0..b) computed by the whole block (b is at most a few
-// thousand): the exclusive prefix of block b without a separate scan kernel.
-template <int NT>
-__device__ __forceinline__ int32_t preceding_sum(const int32_t* __restrict__ partials, int64_t b, int32_t* lds) {
-  int32_t s = 0;
-  for (int64_t i = threadIdx.x; i < b; i += NT) s += partials[i];
-  return block_sum<NT>(s, lds);
-}
-
 // Single-pass scan by decoupled look-back: tile b publishes its aggregate,
 // then its inclusive prefix once the tiles before it are known. flags[b] =
 // tag << 32 | value, tag = 2 * epoch (aggregate) or 2 * epoch + 1 (inclusive
@@ -191,34 +182,6 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
   for (int j = threadIdx.x; j < big_n; j += kScanNT) big_rows[big_base + j] = big_lds[j];
   for (int j = threadIdx.x; j < small_n; j += kScanNT)
     big_rows[small_end - 1 - (int64_t)(small_base + j)] = big_lds[kScanTile - 1 - j];
-}
-
-// Exclusive scan of partials[0..nb) in place (one block). Writes the total
-// to *total_out (if given) as int64, plus `add`.
-__global__ __launch_bounds__(kScanNT) void k_scan_partials(int32_t* __restrict__ partials, int64_t nb,
-                                                           int64_t* total_out, const int64_t* add) {
-  __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
-  int32_t carry = 0;
-  for (int64_t b0 = 0; b0 < nb; b0 += (int64_t)kScanNT * kScanItems) {
-    int32_t v[kScanItems];
-    int32_t s = 0;
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) {
-      const int64_t i = b0 + (int64_t)threadIdx.x * kScanItems + it;
-      v[it] = i < nb ? partials[i] : 0;
-      s += v[it];
-    }
-    int32_t tot;
-    int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot) + carry;
-#pragma unroll
-    for (int it = 0; it < kScanItems; ++it) {
-      const int64_t i = b0 + (int64_t)threadIdx.x * kScanItems + it;
-      if (i < nb) partials[i] = ex;
-      ex += v[it];
-    }
-    carry += tot;
-  }
-  if (threadIdx.x == 0 && total_out) *total_out = (int64_t)carry + (add ? *add : 0);
 }
 
 // --------------------------------------------------------------- sampler
