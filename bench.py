@@ -752,7 +752,7 @@ def pmc_summary(args):
     res = {}
     for name, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rs = rows(d, name)
-        first_step = next(i for i, x in enumerate(rs) if "k_seed_init" in x[2] or "k_row_scan" in x[2])
+        first_step = next(i for i, x in enumerate(rs) if "k_seed_rows" in x[2])
         probe = [x for x in rs[:first_step] if "copyBuffer" in x[2]][-1]
         gathers = [x[3] for x in rs if "k_gather_hbm" in x[2]]
         res[name] = (probe[3], gathers)

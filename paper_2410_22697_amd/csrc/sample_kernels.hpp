@@ -197,8 +197,8 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
 //      key T (it starts below tau's top bit), ties at T are taken in list
 //      order (= ascending j), and the chosen positions are written in
 //      ascending j.
-// The chosen ids are marked in the sampled-id bitmap as they are written. Rows longer than big_min (listed by k_row_scan) are
-// taken first. Where the frontier is small, so that its few longest rows bound
+// The chosen ids are marked in the sampled-id bitmap as they are written. Rows
+// longer than big_min (listed as the frontier's rows were written) are taken first. Where the frontier is small, so that its few longest rows bound
 // the hop's time, each of them gets a whole block: its waves filter
 // consecutive quarters of the row with the same tau, and the four candidate
 // lists, concatenated in order, are the row's list in ascending j. Otherwise
@@ -227,9 +227,9 @@ struct SampleArgs {
   uint32_t key0, key1;
   double mu32;              // (fo + 3 sqrt(fo) + 3) * 2^32
   int64_t big_min;          // rows longer than this are listed in big_rows
-  const int32_t* big_rows;  // appended by k_row_scan
+  const int32_t* big_rows;  // appended by k_seed_rows and k_frontier
   int64_t n_bound;          // bound of the frontier's rows
-  int64_t row_waves;        // k_sample_waves: small_end of k_row_scan (the other rows' list ends there)
+  int64_t row_waves;        // k_sample_waves: small_end of the row list (the other rows' part ends there)
   int64_t big_blocks;       // k_sample_blocks: blocks [0, big_blocks) walk the big list, one row per
                             // block; the rest take all other rows, one per wave
   uint32_t* bits;           // sampled-id bitmap: this block's copy is (block % copies)
