@@ -754,7 +754,10 @@ def pmc_summary(args):
         rs = rows(d, name)
         first_step = next(i for i, x in enumerate(rs) if "k_seed_rows" in x[2])
         probe = [x for x in rs[:first_step] if "copyBuffer" in x[2]][-1]
-        gathers = [x[3] for x in rs if "k_gather_hbm" in x[2]]
+        # one a step: untimed steps run both gathers in one launch, the windows the HBM gather alone
+        both = [x for x in rs if "k_gather_hbm" in x[2] or "k_gather_both" in x[2]]
+        assert all("k_gather_hbm" in x[2] for x in both[head[0]:head[1]]), "the window's gathers are not timed alone"
+        gathers = [x[3] for x in both]
         res[name] = (probe[3], gathers)
     probe_kib = 256 * 1024
     f_scale = probe_kib / res["FETCH_SIZE"][0]
@@ -765,7 +768,7 @@ def pmc_summary(args):
     a, b = src.find("// ---------------------------------------------------------------- gather"), src.find("// misses: pinned host store")
     print("probe FETCH_SIZE %.1f KiB -> factor %.4f; WRITE_SIZE %.1f KiB -> factor %.4f" %
           (res["FETCH_SIZE"][0], f_scale, res["WRITE_SIZE"][0], w_scale))
-    print("k_gather_hbm dispatches in the first context: %d; window %d..%d" % (len(res["FETCH_SIZE"][1]), head[0],
+    print("gather dispatches in the first context: %d; window %d..%d" % (len(res["FETCH_SIZE"][1]), head[0],
                                                                               head[1] - 1))
     print("HBM read per launch (scaled)  %.0f" % fe.mean())
     print("HBM write per launch (scaled) %.0f" % wr.mean())
