@@ -1262,11 +1262,11 @@ __global__ __launch_bounds__(kScanNT) void k_sort_scan(int32_t* __restrict__ a, 
 // digit passes above take it: a block's 4096 words take ~12 us whatever the
 // chip, twelve launches ~40 us whatever the pairs.
 constexpr int kSortOne = 4096;
-__global__ __launch_bounds__(kScanNT) void k_sort_one(const uint32_t* __restrict__ keys,
-                                                      const int32_t* __restrict__ vals,
+// keys_out may be keys and vals_out may be vals (none of them is restrict, and
+// the values are pinned before the barrier that the writes follow).
+__global__ __launch_bounds__(kScanNT) void k_sort_one(const uint32_t* keys, const int32_t* vals,
                                                       const int64_t* __restrict__ n_ptr, int64_t n_const,
-                                                      int64_t bound, uint32_t* __restrict__ keys_out,
-                                                      int32_t* __restrict__ vals_out) {
+                                                      int64_t bound, uint32_t* keys_out, int32_t* vals_out) {
   __shared__ uint64_t w[kSortOne];
   const int n = (int)min(min(size_of(n_ptr, n_const), bound), (int64_t)kSortOne);
   int m = 2;
@@ -1286,13 +1286,14 @@ __global__ __launch_bounds__(kScanNT) void k_sort_one(const uint32_t* __restrict
       }
       __syncthreads();
     }
-  // (the values are read before any is written: the two arrays may be one)
   int32_t v[kSortOne / kScanNT];
 #pragma unroll
   for (int it = 0; it < kSortOne / kScanNT; ++it) {
     const int i = it * kScanNT + threadIdx.x;
     v[it] = i < n ? vals[(uint32_t)w[i]] : 0;
   }
+#pragma unroll
+  for (int it = 0; it < kSortOne / kScanNT; ++it) pin(v[it]);
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < kSortOne / kScanNT; ++it) {
