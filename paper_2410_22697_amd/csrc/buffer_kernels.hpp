@@ -794,15 +794,17 @@ __global__ void k_materialize(float* __restrict__ S_E, int32_t* __restrict__ hit
 // otherwise (misses only add to it; an evicted node gets its last S_E >= 0).
 // (A round is bound by its launches where the buffer is small: 40 launches of
 // 1.5-5 us before, 8 to 19 now.)
+template <bool TICKETS>
 __global__ __launch_bounds__(kScanNT) void k_round_evict(float* __restrict__ S_E, int32_t* __restrict__ hitcnt,
                                                          int64_t cap, int32_t steps, float gamma, float alpha,
                                                          int32_t* __restrict__ E, int32_t* __restrict__ R,
                                                          uint64_t* flags, uint32_t epoch,
                                                          RoundState* __restrict__ rs, Counters* __restrict__ ctr,
-                                                         int64_t nC) {
+                                                         int64_t nC, uint32_t* ticket) {
+  const int64_t tile = scan_tile<TICKETS>(ticket);
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
   __shared__ uint32_t excl_lds;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
   float x[kScanItems];
   int32_t u[kScanItems];
   int32_t most = 0;
@@ -839,12 +841,12 @@ __global__ __launch_bounds__(kScanNT) void k_round_evict(float* __restrict__ S_E
   }
   int32_t tot;
   const int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot);
-  const uint32_t before = lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, &ctr->bad, &excl_lds);
+  const uint32_t before = lookback_exclusive(flags, tile, (uint32_t)tot, epoch, &ctr->bad, &excl_lds);
   int64_t o = (int64_t)before + ex;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it)
     if (f[it]) E[o++] = (int32_t)(base + it);
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+  if (tile == gridDim.x - 1 && threadIdx.x == 0) {
     const int64_t nE = (int64_t)before + tot, k = min(nE, nC);
     rs->nE = nE;
     rs->nC = nC;
@@ -1016,17 +1018,19 @@ __global__ __launch_bounds__(256) void k_select_pass(const float* __restrict__ S
 // rank, so the one pass reads it in order; the halo ids are read only where
 // they are written. Two single-pass scans, one per class (flags_eq after
 // flags_lt); the last tile writes n_lt and n_eq.
+template <bool TICKETS>
 __global__ __launch_bounds__(kScanNT) void k_rank_emit(const float* __restrict__ S_A,
                                                        const int32_t* __restrict__ h_of_rank, int64_t H,
                                                        RoundState* rs, uint64_t* flags_lt, uint64_t* flags_eq,
                                                        uint32_t epoch, int32_t* __restrict__ bad,
                                                        uint32_t* __restrict__ keys, int32_t* __restrict__ vals,
-                                                       int32_t* __restrict__ R) {
+                                                       int32_t* __restrict__ R, uint32_t* ticket) {
+  const int64_t tile = scan_tile<TICKETS>(ticket);
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
   __shared__ uint32_t excl_lt, excl_eq;
   const int64_t kk = rs->k, need = rs->need;
   const uint32_t T = rs->prefix;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
   float a[kScanItems];
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) a[it] = base + it < H ? S_A[base + it] : -1.0f;
@@ -1046,8 +1050,8 @@ __global__ __launch_bounds__(kScanNT) void k_rank_emit(const float* __restrict__
   int32_t tlt, teq;
   const int32_t xlt = block_exclusive_scan<kScanNT>(clt, lds, &tlt);
   const int32_t xeq = block_exclusive_scan<kScanNT>(ceq, lds, &teq);
-  const uint32_t blt = lookback_exclusive(flags_lt, blockIdx.x, (uint32_t)tlt, epoch, bad, &excl_lt);
-  const uint32_t beq = lookback_exclusive(flags_eq, blockIdx.x, (uint32_t)teq, epoch, bad, &excl_eq);
+  const uint32_t blt = lookback_exclusive(flags_lt, tile, (uint32_t)tlt, epoch, bad, &excl_lt);
+  const uint32_t beq = lookback_exclusive(flags_eq, tile, (uint32_t)teq, epoch, bad, &excl_eq);
   int64_t olt = (int64_t)blt + xlt, oeq = (int64_t)beq + xeq;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
@@ -1062,7 +1066,7 @@ __global__ __launch_bounds__(kScanNT) void k_rank_emit(const float* __restrict__
       ++oeq;
     }
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+  if (tile == gridDim.x - 1 && threadIdx.x == 0) {
     rs->n_lt = (int64_t)blt + tlt;
     rs->n_eq = (int64_t)beq + teq;
   }
@@ -1091,16 +1095,19 @@ __device__ __forceinline__ bool gsel_in(float a, uint32_t r, uint32_t th, uint32
 
 // Emits the replacements (keys <= T) in id order as (rank, halo id) pairs, by
 // the single-pass scan.
+template <bool TICKETS>
 __global__ __launch_bounds__(kScanNT) void k_gsel_emit(const float* __restrict__ S, const int32_t* __restrict__ rank_g,
                                                        const int32_t* __restrict__ h_of_rank, int64_t n,
                                                        const RoundState* __restrict__ rs, uint64_t* flags,
                                                        uint32_t epoch, int32_t* __restrict__ bad, int64_t cap,
-                                                       uint32_t* __restrict__ keys, int32_t* __restrict__ vals) {
+                                                       uint32_t* __restrict__ keys, int32_t* __restrict__ vals,
+                                                       uint32_t* ticket) {
+  const int64_t tile = scan_tile<TICKETS>(ticket);
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
   __shared__ uint32_t excl_lds;
   if (rs->k == 0) return;
   const uint32_t th = rs->prefix, tl = rs->prefix_lo;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
   bool f[kScanItems];
   int32_t r[kScanItems];
   int32_t c = 0;
@@ -1114,7 +1121,7 @@ __global__ __launch_bounds__(kScanNT) void k_gsel_emit(const float* __restrict__
   }
   int32_t tot;
   const int32_t ex = block_exclusive_scan<kScanNT>(c, lds, &tot);
-  int64_t o = (int64_t)lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, bad, &excl_lds) + ex;
+  int64_t o = (int64_t)lookback_exclusive(flags, tile, (uint32_t)tot, epoch, bad, &excl_lds) + ex;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it)
     if (f[it]) {
@@ -1235,11 +1242,13 @@ __global__ __launch_bounds__(kSortNT) void k_sort_scatter(const uint32_t* __rest
 }
 
 // Exclusive scan of the block histograms, in place, by the single-pass scan.
+template <bool TICKETS>
 __global__ __launch_bounds__(kScanNT) void k_sort_scan(int32_t* __restrict__ a, int64_t len, uint64_t* flags,
-                                                       uint32_t epoch, int32_t* __restrict__ bad) {
+                                                       uint32_t epoch, int32_t* __restrict__ bad, uint32_t* ticket) {
+  const int64_t tile = scan_tile<TICKETS>(ticket);
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
   __shared__ uint32_t excl_lds;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
   int32_t v[kScanItems];
   int32_t s = 0;
 #pragma unroll
@@ -1249,7 +1258,7 @@ __global__ __launch_bounds__(kScanNT) void k_sort_scan(int32_t* __restrict__ a, 
   }
   int32_t tot;
   int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot);
-  ex += (int32_t)lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, bad, &excl_lds);
+  ex += (int32_t)lookback_exclusive(flags, tile, (uint32_t)tot, epoch, bad, &excl_lds);
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
     if (base + it < len) a[base + it] = ex;

@@ -1,0 +1,32 @@
+// launch_rules.hpp - rules that decide how a launch is shaped, in plain C++ so
+// that they are also built and checked without a GPU.
+#pragma once
+
+#include <cstdint>
+
+namespace ms {
+
+// How the blocks of a single-pass scan take their tiles. A tile waits for the
+// tiles before it. In block order it could wait for ever if other launches kept
+// those off the chip for good, which only other scans can do, as their blocks
+// wait too. Each XCD starts a launch's blocks in order, so the XCD that the
+// first missing tile of scan A needs holds no waiting block of A: the others
+// have to fill it alone. Scans of at most ordered_scan_waves waves therefore
+// keep block order: three of them leave every XCD (32 CUs of 32 waves, which
+// every scan kernel can fill) the 16 waves of the largest block, and HIP runs a
+// process's streams on 4 hardware queues (more, if GPU_MAX_HW_QUEUES asks for
+// them: the limit falls with their number). Larger scans take tickets: a block
+// takes the next tile when it starts, so every tile before a waiting one
+// belongs to a running block, whatever else runs. Tickets cost a launch a round
+// trip before its first load and are handed out one after the other (k_frontier,
+// 282 tiles: 19.0 -> 20.5 us), which is why they are not used everywhere.
+// (Several processes on one card add up their queues; the wait is bounded too.)
+constexpr int64_t kXcdWaves = 32 * 32, kXcds = 8;
+inline int64_t ordered_scan_waves(int queues) {
+  return kXcds * (kXcdWaves - 16) / ((queues > 4 ? queues : 4) - 1);
+}
+inline bool scan_takes_tickets(int64_t tiles, int threads, int64_t ordered_waves) {
+  return (tiles + kXcds - 1) / kXcds * kXcds * (threads / 64) > ordered_waves;
+}
+
+}  // namespace ms

@@ -35,6 +35,7 @@
 #include "buffer_kernels.hpp"
 #include "common.hpp"
 #include "gather_pool.hpp"
+#include "launch_rules.hpp"
 #include "sample_kernels.hpp"
 
 namespace {
@@ -254,6 +255,8 @@ struct massive_ctx {
   uint64_t* d_scan_flags = nullptr;  // the seed rows' single-pass scan
   int64_t scan_tiles = 0;
   uint32_t scan_epoch = 0;           // of the last scan launched
+  uint32_t* d_tickets = nullptr;     // the scans' tile counters (scan_ticket), a line each
+  int64_t ordered_waves = 0;         // scans up to this many waves keep block order (ms::ordered_scan_waves)
   // gather lists by step slot (written by classify, read by the side stream)
   int2* d_hbm_list[kSlots] = {};
   int2* d_miss_list[kSlots] = {};
@@ -386,14 +389,32 @@ uint32_t next_round_epoch(massive_ctx* c, hipStream_t s) {
   return ++c->round_epoch;
 }
 
+// The counter that a scan of `tiles` blocks takes its tiles from, or nullptr
+// for block order (which: 0 seed rows, 1 frontier, 2 rounds and init's sorts:
+// scans of one counter follow each other in stream order).
+enum ScanOf { kSeedScan, kFrontierScan, kRoundScan };
+uint32_t* scan_ticket(massive_ctx* c, ScanOf which, int64_t tiles, int threads) {
+  return ms::scan_takes_tickets(tiles, threads, c->ordered_waves) ? c->d_tickets + which * 32 : nullptr;
+}
+
+// Launches a scan of `tiles` blocks of kScanNT threads; its last argument is
+// the counter.
+#define MS_SCAN(KERNEL, which, tiles, s, ...)                                                                \
+  do {                                                                                                       \
+    uint32_t* ticket_ = scan_ticket(c, which, tiles, ms::kScanNT);                                           \
+    if (ticket_)                                                                                             \
+      ms::KERNEL<true><<<(unsigned)(tiles), ms::kScanNT, 0, s>>>(__VA_ARGS__, ticket_);                      \
+    else                                                                                                     \
+      ms::KERNEL<false><<<(unsigned)(tiles), ms::kScanNT, 0, s>>>(__VA_ARGS__, ticket_);                     \
+  } while (0)
+
 // one stable LSD pass: (kin, vin) -> (kout, vout) by 8-bit digit at `shift`
 void sort_pass(massive_ctx* c, hipStream_t s, const uint32_t* kin, const int32_t* vin, const int64_t* n_ptr,
                int64_t n_const, int64_t bound, int shift, uint32_t* kout, int32_t* vout) {
   const int64_t nb = std::max<int64_t>(1, cdiv(bound, ms::kSortTile));
   ms::k_sort_hist<<<(unsigned)nb, ms::kSortNT, 0, s>>>(kin, n_ptr, n_const, bound, shift, nb, c->d_hist);
-  const int64_t len = 256 * nb;
-  ms::k_sort_scan<<<(unsigned)cdiv(len, ms::kScanTile), ms::kScanNT, 0, s>>>(c->d_hist, len, c->d_round_flags,
-                                                                             next_round_epoch(c, s), &c->d_ctr->bad);
+  const int64_t len = 256 * nb, tiles = cdiv(len, ms::kScanTile);
+  MS_SCAN(k_sort_scan, kRoundScan, tiles, s, c->d_hist, len, c->d_round_flags, next_round_epoch(c, s), &c->d_ctr->bad);
   ms::k_sort_scatter<<<(unsigned)nb, ms::kSortNT, 0, s>>>(kin, vin, n_ptr, n_const, bound, shift, nb, c->d_hist, kout,
                                                           vout);
 }
@@ -816,7 +837,7 @@ void free_ctx(massive_ctx* c) {
   (void)hipDeviceSynchronize();
   void* dev[] = {c->d_indptr, c->d_indices, c->d_slab, c->d_slot_id, c->d_S_E, c->d_hitcnt, c->d_S_A,
                  c->d_rank_of, c->d_h_of_rank, c->d_tab, c->d_pos_of, c->d_bits, c->d_rec, c->d_sz, c->d_rs,
-                 c->d_round_flags, c->d_scan_flags, c->d_dummy, c->d_E, c->d_R,
+                 c->d_round_flags, c->d_scan_flags, c->d_tickets, c->d_dummy, c->d_E, c->d_R,
                  c->d_fill, c->d_ctr, c->d_slot_round, c->d_landed,
                  c->d_k0, c->d_k1, c->d_v0, c->d_v1, c->d_hist, c->d_ghist, c->d_big,
                  c->d_gid, c->d_rank_g, c->d_deg};
@@ -926,6 +947,9 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   if (const char* e = getenv("MASSIVE_BIG_ROW")) c->big_min = std::max<int64_t>(256, atoll(e));
   if (const char* e = getenv("MASSIVE_BIG_BLOCKS")) c->big_blocks = std::max<int64_t>(1, atoll(e));
   if (const char* e = getenv("MASSIVE_TAU_ITERS")) c->tau_iters = std::min(std::max(0, atoi(e)), ms::kTauIters);
+  const char* queues = getenv("GPU_MAX_HW_QUEUES");
+  c->ordered_waves = ms::ordered_scan_waves(queues ? atoi(queues) : 0);
+  if (const char* e = getenv("MASSIVE_ORDERED_WAVES")) c->ordered_waves = std::max<int64_t>(0, atoll(e));
   if (const char* e = getenv("MASSIVE_RING_BYTES")) c->ring_bytes = std::max<int64_t>(1, atoll(e));
   c->s_main = (hipStream_t)a->stream;
   c->link_mode = a->link_mode;
@@ -1005,6 +1029,7 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   c->scan_tiles = cdiv(R, ms::kScanTile) + 1;
   CKA(c->d_scan_flags, (c->scan_tiles + cdiv(R, fs.rows()) + cdiv(c->W, fs.tw)) * 8);
   c->d_tile_flags = c->d_scan_flags + c->scan_tiles;
+  CKA(c->d_tickets, 3 * 32 * 4);
   for (int i = 0; i < kSlots; ++i) {
     CKA(c->d_hbm_list[i], R * 8);
     CKA(c->d_miss_list[i], R * 8);
@@ -1075,6 +1100,7 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CK(hipMemsetAsync(c->d_ghist, 0, ms::kSelBins * 4, s));
   CK(hipMemsetAsync(c->d_scan_flags, 0, c->scan_tiles * 8, s));
   CK(hipMemsetAsync(c->d_round_flags, 0, 2 * c->round_tiles * 8, s));
+  CK(hipMemsetAsync(c->d_tickets, 0, 3 * 32 * 4, s));
   CK(hipMemsetAsync(c->d_ctr, 0, sizeof(ms::Counters), s));
   CK(hipMemsetAsync(c->d_slot_round, 0xFF, cap * 4, s));
   CK(hipMemsetAsync(c->d_landed, 0xFF, cap * 4, s));
@@ -1291,12 +1317,19 @@ void launch_sampler(bool by_waves, int quads, unsigned grid, hipStream_t s, hipE
 }
 
 void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream_t s, const ms::FrontierArgs& fa) {
-#define MS_FR(NT, TW, COPIES)                                         \
-  do {                                                                \
-    if (last)                                                         \
-      ms::k_frontier<NT, TW, true, COPIES><<<grid, NT, 0, s>>>(fa);   \
-    else                                                              \
-      ms::k_frontier<NT, TW, false, COPIES><<<grid, NT, 0, s>>>(fa);  \
+#define MS_FR2(NT, TW, COPIES, TICKETS)                                        \
+  do {                                                                         \
+    if (last)                                                                  \
+      ms::k_frontier<NT, TW, true, COPIES, TICKETS><<<grid, NT, 0, s>>>(fa);   \
+    else                                                                       \
+      ms::k_frontier<NT, TW, false, COPIES, TICKETS><<<grid, NT, 0, s>>>(fa);  \
+  } while (0)
+#define MS_FR(NT, TW, COPIES)            \
+  do {                                   \
+    if (fa.ticket)                       \
+      MS_FR2(NT, TW, COPIES, true);      \
+    else                                 \
+      MS_FR2(NT, TW, COPIES, false);     \
   } while (0)
   if (f.tw == 64)
     MS_FR(256, 64, ms::kSmallCopies);
@@ -1305,6 +1338,7 @@ void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream
   else
     MS_FR(512, 2048, 1);
 #undef MS_FR
+#undef MS_FR2
 }
 
 // Enqueues one step with the per-step buffers sb: sampling and classify on the
@@ -1330,10 +1364,9 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
     const int64_t bit_tiles = cdiv(c->W, fs.tw);
     {
       const int64_t nbk = std::max<int64_t>(1, cdiv(nb[0], ms::kScanTile));
-      ms::k_seed_rows<<<(unsigned)nbk, ms::kScanNT, 0, s>>>(
-          c->d_indptr, seeds, n0, c->L, io->nodes, sz, c->fo[0], io->indptr[0], sb.flags, sb.epoch, c->d_pos_of,
-          c->d_seen, c->d_rec, sb.big, c->big_min, nb[0] > ms::kBlockRowsMax ? nb[0] : 0,
-          reinterpret_cast<int32_t*>(sb.next_sz));
+      MS_SCAN(k_seed_rows, kSeedScan, nbk, s, c->d_indptr, seeds, n0, c->L, io->nodes, sz, c->fo[0], io->indptr[0],
+              sb.flags, sb.epoch, c->d_pos_of, c->d_seen, c->d_rec, sb.big, c->big_min,
+              nb[0] > ms::kBlockRowsMax ? nb[0] : 0, reinterpret_cast<int32_t*>(sb.next_sz));
     }
     for (int k = 1; k <= c->K; ++k) {
       const int64_t nprev = nb[k - 1];
@@ -1388,6 +1421,7 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
       fa.sz = sz;
       fa.hop = k;
       fa.flags = c->d_tile_flags;
+      fa.ticket = scan_ticket(c, kFrontierScan, old_tiles + bit_tiles, fs.nt);
       fa.old_tiles = old_tiles;
       fa.n_bound = nprev;
       fa.nodes = io->nodes;
@@ -1787,9 +1821,9 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
     CK(hipStreamWaitEvent(s, c->slot_both[tl % kSlots] ? c->ev_cls_done[tl % kSlots] : c->ev_hbm_done[tl % kSlots], 0));
   {
     massive_ctx::Range tr(c, s, 4);
-    ms::k_round_evict<<<(unsigned)cdiv(cap, ms::kScanTile), ms::kScanNT, 0, s>>>(
-        c->d_S_E, c->d_hitcnt, cap, (int32_t)(c->t - c->mat_t), c->gamma, c->alpha, c->d_E, c->d_R, c->d_round_flags,
-        next_round_epoch(c, s), rs, c->d_ctr, H - cap);
+    const int64_t tiles = cdiv(cap, ms::kScanTile);
+    MS_SCAN(k_round_evict, kRoundScan, tiles, s, c->d_S_E, c->d_hitcnt, cap, (int32_t)(c->t - c->mat_t), c->gamma,
+            c->alpha, c->d_E, c->d_R, c->d_round_flags, next_round_epoch(c, s), rs, c->d_ctr, H - cap);
     c->mat_t = c->t;
     // fewer candidates than evictions: keep the k' slots of smallest (S_E,
     // rank). With |C| = H - cap >= cap >= |E| (f <= 50%) it cannot happen and
@@ -1813,9 +1847,9 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
         for (int p = 0; p < ms::kSelPasses; ++p)
           ms::k_select_pass<true><<<grid_for(cdiv(n, 4), 256, ms::kSelBlocks), 256, 0, s>>>(
               c->d_S_A, c->d_rank_g, n, rs, word, ms::kSelShift[p], ms::kSelBits[p], c->d_ghist, &c->d_ctr->bad);
-      ms::k_gsel_emit<<<(unsigned)cdiv(n, ms::kScanTile), ms::kScanNT, 0, s>>>(
-          c->d_S_A, c->d_rank_g, c->d_h_of_rank, n, rs, c->d_round_flags, next_round_epoch(c, s), &c->d_ctr->bad, cap,
-          c->d_k0, c->d_v0);
+      const int64_t tiles = cdiv(n, ms::kScanTile);
+      MS_SCAN(k_gsel_emit, kRoundScan, tiles, s, c->d_S_A, c->d_rank_g, c->d_h_of_rank, n, rs, c->d_round_flags,
+              next_round_epoch(c, s), &c->d_ctr->bad, cap, c->d_k0, c->d_v0);
       sort_u32(c, s, &rs->k, 0, cap, nullptr);
       ms::k_gsel_keys<<<grid_for(cap, 256), 256, 0, s>>>(c->d_v0, &rs->k, c->d_S_A, c->d_sa_idx, c->d_k0);
       sort_u32(c, s, &rs->k, 0, cap, c->d_R);
@@ -1823,9 +1857,9 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
       for (int p = 0; p < ms::kSelPasses; ++p)
         ms::k_select_pass<false><<<grid_for(cdiv(H, 4), 256, ms::kSelBlocks), 256, 0, s>>>(
             c->d_S_A, nullptr, H, rs, 0, ms::kSelShift[p], ms::kSelBits[p], c->d_ghist, &c->d_ctr->bad);
-      ms::k_rank_emit<<<(unsigned)cdiv(H, ms::kScanTile), ms::kScanNT, 0, s>>>(
-          c->d_S_A, c->d_h_of_rank, H, rs, c->d_round_flags, c->d_round_flags + c->round_tiles, next_round_epoch(c, s),
-          &c->d_ctr->bad, c->d_k0, c->d_v0, c->d_R);
+      const int64_t tiles = cdiv(H, ms::kScanTile);
+      MS_SCAN(k_rank_emit, kRoundScan, tiles, s, c->d_S_A, c->d_h_of_rank, H, rs, c->d_round_flags,
+              c->d_round_flags + c->round_tiles, next_round_epoch(c, s), &c->d_ctr->bad, c->d_k0, c->d_v0, c->d_R);
       // candidates before the threshold: stable sort by key (S_A desc), rank order kept for ties
       sort_u32(c, s, &rs->n_lt, 0, cap, c->d_R);
     }

@@ -16,11 +16,27 @@ __device__ __forceinline__ int64_t size_of(const int64_t* p, int64_t c) { return
 // then its inclusive prefix once the tiles before it are known. flags[b] =
 // tag << 32 | value, tag = 2 * epoch (aggregate) or 2 * epoch + 1 (inclusive
 // prefix); the epoch differs for every launch, so flags are never cleared.
-// Tiles are blocks in blockIdx order. Each XCD dispatches its blocks in
-// order, so the lowest unfinished tile is always resident and every wait
-// ends. The wait is bounded all the same: past the limit the step is flagged
-// (status bit 8) and the tile goes on with the values it has.
+// A wait ends if every tile before the waiting one gets a block: see scan_tile.
+// It is bounded all the same: past the limit the step is flagged (status bit
+// 8) and the tile goes on with the values it has.
 constexpr int kLookbackSpins = 1 << 20;
+
+// The tile of this block of a scan: its index, or with TICKETS (launches that
+// scan_takes_tickets names) the next ticket. The last block to take one puts
+// the counter back to zero for the next scan of the same stream. Whole block,
+// before a check that makes the block leave.
+template <bool TICKETS>
+__device__ __forceinline__ int64_t scan_tile(uint32_t* ticket) {
+  if constexpr (!TICKETS) return (int64_t)blockIdx.x;
+  __shared__ uint32_t tile;
+  if (threadIdx.x == 0) {
+    const uint32_t t = atomicAdd(ticket, 1u);
+    tile = t;
+    if (t == gridDim.x - 1) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  return (int64_t)(uint32_t)wave_uniform((int32_t)tile);
+}
 
 __device__ __forceinline__ uint32_t lookback_exclusive(uint64_t* flags, int64_t b, uint32_t agg, uint32_t epoch,
                                                        int32_t* status, uint32_t* excl_lds) {
@@ -88,13 +104,16 @@ __device__ __forceinline__ v4r row_record(int32_t v, int64_t start, int64_t d) {
 // `seen` keeps it) and placed: F_0 = seeds, pos_of[seed] = its position, its
 // row record, n_0 = n0. A bad seed sets the step's status, which every later
 // kernel checks first.
+template <bool TICKETS>
 __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict__ csr_indptr,
                                                        const int32_t* __restrict__ seeds, int32_t n0, int32_t L,
                                                        int32_t* __restrict__ nodes, StepSizes* sz, int32_t fo,
                                                        int32_t* __restrict__ bptr, uint64_t* flags, uint32_t epoch,
                                                        int32_t* __restrict__ pos_of, uint32_t* __restrict__ seen,
                                                        v4r* __restrict__ rec, int32_t* __restrict__ big_rows,
-                                                       int64_t big_min, int64_t small_end, int32_t* next_sizes) {
+                                                       int64_t big_min, int64_t small_end, int32_t* next_sizes,
+                                                       uint32_t* ticket) {
+  const int64_t tile = scan_tile<TICKETS>(ticket);
   __shared__ int32_t lds[kScanNT / MS_WAVE + 1];
   __shared__ int32_t big_lds[kScanTile];  // long rows from the front, the others from the back
   __shared__ int32_t big_n, small_n;
@@ -102,14 +121,14 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
   __shared__ uint32_t excl_lds;
   // (the step's sizes are clear here: no status to check)
   const int64_t n = n0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) sz->n[0] = n;
-  if (blockIdx.x == 0 && next_sizes && threadIdx.x < sizeof(StepSizes) / 4) next_sizes[threadIdx.x] = 0;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  if (tile == 0 && threadIdx.x == 0) sz->n[0] = n;
+  if (tile == 0 && next_sizes && threadIdx.x < sizeof(StepSizes) / 4) next_sizes[threadIdx.x] = 0;
+  const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
   if (threadIdx.x == 0) big_n = small_n = 0;
   __syncthreads();
   int32_t c[kScanItems] = {};
   int32_t s = 0;
-  if ((int64_t)blockIdx.x * kScanTile < n) {
+  if (tile * kScanTile < n) {
     int32_t v[kScanItems];
     int64_t lo[kScanItems], hi[kScanItems];
 #pragma unroll
@@ -162,7 +181,7 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
   }
   int32_t tot;
   const int32_t ex = block_exclusive_scan<kScanNT>(s, lds, &tot);  // (its barriers complete the big_lds appends)
-  const uint32_t before = lookback_exclusive(flags, blockIdx.x, (uint32_t)tot, epoch, &sz->status, &excl_lds);
+  const uint32_t before = lookback_exclusive(flags, tile, (uint32_t)tot, epoch, &sz->status, &excl_lds);
   int64_t run = (int64_t)before + ex;
 #pragma unroll
   for (int it = 0; it < kScanItems; ++it) {
@@ -173,8 +192,8 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
     }
   }
   if (threadIdx.x == 0) {
-    if (blockIdx.x == 0) bptr[0] = 0;
-    if (blockIdx.x == gridDim.x - 1) sz->e[0] = (int64_t)before + tot;
+    if (tile == 0) bptr[0] = 0;
+    if (tile == gridDim.x - 1) sz->e[0] = (int64_t)before + tot;
     big_base = big_n ? atomicAdd((unsigned long long*)&sz->n_big[0], (unsigned long long)big_n) : 0ull;
     small_base = small_n ? atomicAdd((unsigned long long*)&sz->n_small[0], (unsigned long long)small_n) : 0ull;
   }
@@ -855,7 +874,11 @@ __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleA
 // rows in a launch of their own; 6.5-7.9 us for both here. Of a launch on a
 // small frontier (6.2 us) most is the chain of dependent steps: loads,
 // look-back, loads.
-constexpr int kFrItems = 8;  // rows in flight per thread
+// Rows in flight per thread. Four, as a launch then holds its share of the chip
+// at 64 registers (see scan_takes_tickets), and as fast as eight at 112: us per
+// pass, eight -> four: eight look-ahead steps on 487K words 2778 -> 2762, five
+// on 3.4K words 389 -> 385, on 50K words 5344 -> 5340.
+constexpr int kFrItems = 4;
 
 struct FrontierArgs {
   uint32_t* bits;      // COPIES copies of the sampled-id bitmap
@@ -866,6 +889,7 @@ struct FrontierArgs {
   StepSizes* sz;
   int32_t hop;  // 1-based: the hop just sampled
   uint64_t* flags;
+  uint32_t* ticket;  // scan_tile's counter (TICKETS)
   int64_t old_tiles;
   int64_t n_bound;  // bound of n_{hop-1}
   int32_t* nodes;
@@ -949,8 +973,8 @@ __device__ __forceinline__ FrSums fr_lookback(uint64_t* flags, int64_t b, uint32
   return x;
 }
 
-template <int NT, int TW, bool LAST, int COPIES>
-__global__ __launch_bounds__(NT) void k_frontier(FrontierArgs a) {
+template <int NT, int TW, bool LAST, int COPIES, bool TICKETS>
+__global__ __launch_bounds__(NT, 8) void k_frontier(FrontierArgs a) {
   constexpr int kFrNT = NT, kFrWaves = NT / MS_WAVE, kFrChunk = NT * kFrItems;
   constexpr int WPT = TW > NT ? TW / NT : 1;  // words per thread (of the first TW / WPT threads)
   static_assert(WPT == 1 || (WPT == 4 && COPIES == 1), "one word or one 16-byte vector");
@@ -962,15 +986,24 @@ __global__ __launch_bounds__(NT) void k_frontier(FrontierArgs a) {
   __shared__ int32_t big_n, small_n;
   __shared__ unsigned long long base_of[2];
   const int lane = lane_id(), wave = wave_id();
-  const bool old = (int64_t)blockIdx.x < a.old_tiles;
-  const int64_t row0 = (int64_t)blockIdx.x * kFrChunk;             // of a tile of old rows
-  const int64_t word0 = ((int64_t)blockIdx.x - a.old_tiles) * TW;  // of a bitmap tile
+  // the step's status and sizes, and the tile's words or row lengths, in one
+  // round of loads; with tickets the sizes come under the ticket's round trip,
+  // and the kernel's arguments before it
+  if constexpr (TICKETS)
+    asm volatile("" ::"s"(a.bits), "s"(a.seen), "s"(a.W), "s"(a.L), "s"(a.hop), "s"(a.old_tiles), "s"(a.n_bound),
+                 "s"(a.rec), "s"(a.flags), "s"(a.csr_indptr), "s"(a.bptr), "s"(a.nodes), "s"(a.ticket), "s"(a.fo));
+  int32_t status = a.sz->status;
+  int64_t n_prev = a.sz->n[a.hop - 1];
+  const int64_t tile = scan_tile<TICKETS>(a.ticket);
+  if constexpr (TICKETS) {
+    pin(status);
+    pin(n_prev);
+  }
+  const bool old = tile < a.old_tiles;
+  const int64_t row0 = tile * kFrChunk;             // of a tile of old rows
+  const int64_t word0 = (tile - a.old_tiles) * TW;  // of a bitmap tile
   const int64_t i0w = word0 + (int64_t)threadIdx.x * WPT;          // this thread's first word
   const bool words = !old && (int)threadIdx.x * WPT < TW && i0w < a.W;
-  // the step's status and sizes, and the tile's words or row lengths, in one
-  // round of loads
-  const int32_t status = a.sz->status;
-  const int64_t n_prev = a.sz->n[a.hop - 1];
   uint32_t w[WPT], sn[WPT];
   uint32_t d[kFrItems] = {};
 #pragma unroll
@@ -1106,15 +1139,15 @@ __global__ __launch_bounds__(NT) void k_frontier(FrontierArgs a) {
                        : 0ull;
     }
   }
-  const FrSums before = fr_lookback<NT>(a.flags, blockIdx.x, old ? 0u : (uint32_t)tot, (uint32_t)sum_e, &a.sz->status);
+  const FrSums before = fr_lookback<NT>(a.flags, tile, old ? 0u : (uint32_t)tot, (uint32_t)sum_e, &a.sz->status);
   if (below >= 0) a.sz->n_local_new[a.hop - 1] = (int64_t)before.n + below;
   if (threadIdx.x == 0) {
-    if (blockIdx.x == gridDim.x - 1) {
+    if (tile == gridDim.x - 1) {
       a.sz->n[a.hop] = n_prev + before.n + (old ? 0 : tot);
       if (!LAST) a.sz->e[a.hop] = (int64_t)before.e + sum_e;
       if ((int64_t)(a.L >> 5) >= a.W) a.sz->n_local_new[a.hop - 1] = (int64_t)before.n + tot;  // every id is below L
     }
-    if (!LAST && blockIdx.x == 0) a.bptr[0] = 0;
+    if (!LAST && tile == 0) a.bptr[0] = 0;
   }
   const int64_t i0 = old ? row0 : n_prev + before.n;  // frontier row of item 0
   __syncthreads();  // (base_of)

@@ -50,7 +50,11 @@ def _kernels():
 def _launches():
     text = _read("massive.hip")
     for m in re.finditer(r"ms::(k_\w+)(?:<[^<>;]*>)?<<<[^;]*?>>>\s*(\()", text, re.S):
-        yield m.group(1), _split(_balanced(text, m.start(2)))
+        if "__VA_ARGS__" not in _balanced(text, m.start(2)):
+            yield m.group(1), _split(_balanced(text, m.start(2)))
+    for m in re.finditer(r"\bMS_SCAN(\()(?=k_)", text):  # kernel, which scan, tiles, stream, its arguments
+        kernel, _, _, _, *args = _split(_balanced(text, m.start(1)))
+        yield kernel, args
 
 
 def _clash(params, args):
