@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "launch_rules.hpp"
 #include "sample_kernels.hpp"
 
 namespace ms {
@@ -955,7 +956,7 @@ __global__ __launch_bounds__(256) void k_select_pass(const float* __restrict__ S
 #pragma unroll
     for (int y = 0; y < kSelUnroll; ++y) {
       const int64_t q = q0 + y * stride;
-      x[y] = S4[q < n4 ? q : 0];  // (S is never empty; a vector past the whole ones is read again below)
+      x[y] = S4[score_vector(q, n)];
     }
 #pragma unroll
     for (int y = 0; y < kSelUnroll; ++y) {

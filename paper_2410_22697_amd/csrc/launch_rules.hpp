@@ -1,4 +1,4 @@
-// launch_rules.hpp - rules that decide how a launch is shaped, in plain C++ so
+// launch_rules.hpp - rules that shape launches and their reads, in plain C++ so
 // that they are also built and checked without a GPU.
 #pragma once
 
@@ -28,5 +28,12 @@ inline int64_t ordered_scan_waves(int queues) {
 inline bool scan_takes_tickets(int64_t tiles, int threads, int64_t ordered_waves) {
   return (tiles + kXcds - 1) / kXcds * kXcds * (threads / 64) > ordered_waves;
 }
+
+// A round's select passes read the n scores in 16-byte vectors: vector q of the
+// grid, or vector 0 past the whole ones (those lanes read their last scores one
+// by one and drop the vector). The array therefore has room for one vector,
+// also where it holds fewer than four scores.
+constexpr int64_t score_vector(int64_t q, int64_t n) { return q < n / 4 ? q : 0; }
+inline int64_t score_bytes(int64_t n) { return n < 4 ? 16 : n * 4; }
 
 }  // namespace ms

@@ -1000,7 +1000,7 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   CKA(c->d_slot_id, cap * 4);
   CKA(c->d_S_E, cap * 4);
   CKA(c->d_hitcnt, cap * 4);
-  CKA(c->d_S_A, c->n_sa * 4);
+  CKA(c->d_S_A, ms::score_bytes(c->n_sa));
   CKA(c->d_gid, H * 4);
   if (c->layout == MASSIVE_SCORES_BY_GID) {
     CKA(c->d_rank_g, c->n_sa * 4);

@@ -38,3 +38,15 @@ def test_round_every_step(H, pct, layout):
     gm = make_gpu(prob, score_layout=layout, n_global=3 * H)
     rounds, _, _ = run_parity("rounds H=%d pct=%d %s" % (H, pct, layout), prob, lambda t: seeds[t], 6, gm=gm)
     assert rounds >= (0 if pct == 100 else 4 if H > 100 else 1)
+
+
+@pytest.mark.parametrize("layout", ["rank", "gid"])
+@pytest.mark.parametrize("H,pct", [(2, 50), (3, 34), (3, 67), (4, 50), (5, 40)])
+def test_round_of_the_smallest_halos(H, pct, layout):
+    # score arrays below and just above one 16-byte vector
+    prob = _problem(H, pct, (40,), 0.5)
+    prob.halo_gid = np.arange(H, dtype=np.int32)[::-1].copy()
+    gm = make_gpu(prob, score_layout=layout, n_global=H)
+    assert gm.cap >= 1
+    seeds = [np.arange(t, dtype=np.int32) for t in (0, 0, 3, 0, 0)]
+    run_parity("rounds H=%d pct=%d %s" % (H, pct, layout), prob, lambda t: seeds[t], 5, gm=gm)
