@@ -599,13 +599,15 @@ __global__ __launch_bounds__(256) void k_gather_both(MissArgs a, uint32_t blocks
                                                      const int64_t* __restrict__ count,
                                                      const uint8_t* __restrict__ src, int64_t rb, uint32_t cpr,
                                                      uint64_t magic) {
-  if (blockIdx.x < blocks)
+  if (blockIdx.x < blocks) {
     miss_body<V, ONE>(a, rb, cpr, magic, blocks);
-  else if (blockIdx.x == blocks)
+  } else if (blockIdx.x == blocks) {
     publish_step(a.tail);
-  else
-    gather_body<V, ONE, 4>(list, count, a.bound, src, a.dst, rb, cpr, magic, blockIdx.x - blocks - 1,
-                           gridDim.x - blocks - 1);
+  } else {
+    const uint64_t b = blockIdx.x - blocks - 1;
+    const uint64_t share = hbm_share((uint64_t)*count, (uint64_t)*a.count, gridDim.x - blocks - 1);
+    if (b < share) gather_body<V, ONE, 4>(list, count, a.bound, src, a.dst, rb, cpr, magic, b, share);
+  }
 }
 
 // The step's completion as a kernel of its own, where no miss gather ends

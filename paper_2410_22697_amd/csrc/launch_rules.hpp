@@ -1,5 +1,6 @@
 // launch_rules.hpp - rules that shape launches and their reads, in plain C++ so
-// that they are also built and checked without a GPU.
+// that they are also built and checked without a GPU (constexpr ones run in
+// kernels too).
 #pragma once
 
 #include <cstdint>
@@ -35,5 +36,24 @@ inline bool scan_takes_tickets(int64_t tiles, int threads, int64_t ordered_waves
 // also where it holds fewer than four scores.
 constexpr int64_t score_vector(int64_t q, int64_t n) { return q < n / 4 ? q : 0; }
 inline int64_t score_bytes(int64_t n) { return n < 4 ? 16 : n * 4; }
+
+// Blocks that move a step's HBM rows beside its miss gather, of the `blocks`
+// launched: the rows have the link's time to move in, so they take few blocks
+// and leave the chip to the next step's sampling (and the memory system to the
+// link). A block moves a row about 1/8 as fast as the whole link does, so 16
+// blocks for each HBM row per host row need half the link's time. Eight
+// look-ahead steps on the 111M-node share (9 HBM rows per host row), us per pass
+// by blocks: 4096 2990, 512 2960, 256 2865, 128 2765, 64 2765, 32 2783; on the
+// 2.45M-node graph 4096 5330, 128 5292, 32 5290; a step waited for on the
+// 111M-node share 4096 557, by this rule 548. By the step's own lists: few misses
+// (the link is done early) get the whole grid (190K HBM rows, 880 host rows: 126
+// us a step, 153 with the share of a step of 7 and 1).
+constexpr uint64_t kMinHbmShare = 96;
+constexpr uint64_t hbm_share(uint64_t n_hbm, uint64_t n_host, uint64_t blocks) {
+  if (n_host == 0) return blocks;
+  const uint64_t want = 16 * n_hbm / n_host;
+  const uint64_t share = want > kMinHbmShare ? want : kMinHbmShare;
+  return share < blocks ? share : blocks;
+}
 
 }  // namespace ms

@@ -133,7 +133,6 @@ struct massive_ctx {
   int64_t host_blocks = 16;
   int64_t host_blocks_light = 12;
   int64_t host_rows_seen = -1;  // host rows of the last step waited for (-1: none yet)
-  int64_t hbm_rows_seen = -1;   // and its HBM rows
   bool slot_clear[MASSIVE_MAX_INFLIGHT] = {};  // the slot's sizes were cleared by its last step's miss gather
   int64_t refill_blocks = 16; // grid of the refill (host link, off the critical path)
   double mu32[MASSIVE_MAX_HOPS] = {};    // sampler threshold targets, x 2^32
@@ -473,17 +472,7 @@ void launch_gather(massive_ctx* c, GatherKind kind, hipStream_t s, const int2* l
   const uint64_t magic = cpr > 1 ? (~0ull) / cpr + 1 : 0;
   const uint64_t bound = (uint64_t)std::max<int64_t>(max_rows, 1);
   const int64_t chunks = (int64_t)bound * cpr;
-  // Beside the miss gather the HBM rows have the link's time to move in, so they
-  // take few blocks and leave the chip to the next step's sampling: a block
-  // moves a row about 1/8 as fast as the whole link does, so 16 blocks for each
-  // HBM row per host row (of the last step waited for) need half the link's
-  // time. Eight look-ahead steps on the 111M-node share (9 HBM rows per host
-  // row), us per pass by blocks: 4096 2990, 512 2960, 256 2865, 128 2765, 64
-  // 2765, 32 2783; on the 2.45M-node graph 4096 5330, 128 5292, 32 5290.
-  int64_t hbm_blocks = c->hbm_blocks;
-  if (kind == kBoth && c->host_rows_seen > 0)
-    hbm_blocks = std::min(hbm_blocks, std::max<int64_t>(96, 16 * c->hbm_rows_seen / c->host_rows_seen));
-  const unsigned hbm_grid = grid_for(chunks / 4, 256, hbm_blocks), host_grid = grid_for(chunks / 4, 256, host_blocks);
+  const unsigned hbm_grid = grid_for(chunks / 4, 256, c->hbm_blocks), host_grid = grid_for(chunks / 4, 256, host_blocks);
 #define MS_ONE(V, ONE)                                                                                          \
   do {                                                                                                          \
     if (kind == kHbm) {                                                                                         \
@@ -1711,7 +1700,6 @@ int massive_batch_wait(massive_ctx* c, massive_batch* io) {
   io->misses = z.misses;
   io->host_rows = z.n_miss;
   c->host_rows_seen = z.n_miss;
-  c->hbm_rows_seen = z.n_hbm;
   return MASSIVE_OK;
 }
 
