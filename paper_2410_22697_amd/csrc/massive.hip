@@ -924,6 +924,7 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
     const double mu = std::min(fo + 3.0 * std::sqrt(fo) + 3.0, 0.5 * (fo + ms::kCandCap));
     c->mu32[k] = mu * 4294967296.0;
     c->quad_slots[k] = ms::quad_slots(mu);
+    if (const char* e = getenv("MASSIVE_FIRST_KEYS")) c->mu32[k] = std::max(0.01, atof(e)) * 4294967296.0;
   }
 
   if (const char* e = getenv("MASSIVE_HBM_BLOCKS")) c->hbm_blocks = std::max(1, atoi(e));

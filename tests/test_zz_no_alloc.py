@@ -3,7 +3,8 @@ against massive_sample: the same step, element by element, with its per-step
 scratch in the library's static device array instead of the context's
 buffers. Two calls in a row, the second with a smaller batch; contexts of
 different graphs sharing the one array; the no-alloc step between ordinary
-ones; and the size limit."""
+ones; refused batches (whose sizes and status the array must not hand on); and
+the size limit."""
 import numpy as np
 import pytest
 
@@ -89,6 +90,47 @@ def test_noalloc_contexts_share_the_array():
         steps[id(p)] = t + 1
     for p in (a, b):
         _assert_same_state("shared array end", p[4], p[5])
+
+
+def test_noalloc_after_refused_batches():
+    # a refused batch leaves its sizes and its status in the array; the next
+    # calls, of this context and of another one, each start from clear sizes
+    # (two calls a context, as the calls take the array's two sizes in turn)
+    from paper_2410_22697_amd import MassiveError
+    a, b = _pair("cl10k", delta=3), _pair("cl170k", delta=2)
+    steps = {id(a): 0, id(b): 0}
+
+    def refused(p, seeds):
+        log("no-alloc refused: %s" % seeds)
+        with pytest.raises(MassiveError) as ei:
+            p[5].sample_noalloc(to_dev(np.array(seeds, np.int32)), p[7])
+        assert ei.value.code == -1
+
+    def good(p):
+        prob, sched, w, store, ref, na, bb_ref, bb_na = p
+        t = steps[id(p)]
+        log("no-alloc after a refused batch: t=%d L=%d" % (t, prob.L))
+        r_ref = ref.sample(to_dev(sched.seeds(t)), bb_ref)
+        r_na = na.sample_noalloc(to_dev(sched.seeds(t)), bb_na)
+        x, y = _outputs(r_ref, bb_ref, len(prob.fanout)), _outputs(r_na, bb_na, len(prob.fanout))
+        for o in (x, y):  # (a refused batch moves a refill chunk on: host_rows, the last size, differs)
+            o["sizes"] = o["sizes"][:-1]
+        _assert_same("t=%d" % t, x, y)
+        assert ref.evict_step() == na.evict_step()
+        steps[id(p)] = t + 1
+
+    L = a[0].L
+    for bad in ([5, 5], [L], [0, -1, 2], [7] * 200):
+        for first, second in ((a, b), (b, a)):
+            refused(a, bad)
+            for p in (first, first, second, second):
+                good(p)
+    refused(b, [1, 1])
+    refused(a, [L])
+    good(b)
+    good(a)
+    for p in (a, b):
+        _assert_same_state("after refused batches", p[4], p[5])
 
 
 def test_noalloc_size_limit():
