@@ -18,6 +18,15 @@ below it (the fanout-th smallest key); every key below T is taken, and the
 ties at T in list order until fanout are reached; emission is slot-major,
 lane-minor, which is list order.
 
+Quads (fanouts up to 56): the list holds whole Philox blocks, the four keys of
+positions 4q..4q+3 with at least one below tau, up to 64 or 128 of them but
+counted in full; slot s of lane x reads entry 64 s + x, and keys past the row's
+end or not below tau count as the largest key and not as valid. If the valid
+keys are more than the fanout, a bisection looks for a bound below which exactly
+fanout keys lie and ends at the fanout-th key where ties leave none; keys below
+the bound are taken, then ties at it in list order. A row of at most 256
+positions is one quad per lane, with no threshold.
+
 The model restates those steps (the keys are given: Philox itself is pinned
 elsewhere) and checks them against sorting by (key, j), with ties, rows whose
 length is not a multiple of four or 256, and tau at 2^32. It restates the
@@ -188,3 +197,84 @@ def test_both_append_paths_taken():
     assert PATHS["one_per_lane"] > before["one_per_lane"]
     assert PATHS["general"] > before["general"]
     assert PATHS["skip"] > before["skip"]
+
+
+MAX32 = (1 << 32) - 1
+
+
+def choose_quads(quads, fo, tm1, d):
+    """quads: (q, four keys) in list order, one per lane and slot."""
+    keys, valid = [], []
+    for q, k4 in quads:
+        v = [4 * q + s < d and k4[s] <= tm1 for s in range(4)]
+        valid.append(v)
+        keys.append([k if ok else MAX32 for k, ok in zip(k4, v)])
+    total = sum(map(sum, valid))
+    assert total >= fo
+
+    def below(x):
+        return sum(k < x for k4 in keys for k in k4)
+
+    if total == fo:
+        sel = valid
+    else:
+        lo, hi, exact, x = 0, tm1, False, 0
+        while lo < hi:
+            x = lo + ((hi - lo) >> 1) + 1
+            n = below(x)
+            if n == fo:
+                exact = True
+                break
+            if n < fo:
+                lo = x
+            else:
+                hi = x - 1
+        if not exact:
+            x = lo
+        sel = [[k < x for k in k4] for k4 in keys]
+        if not exact:
+            need = fo - below(x)
+            assert need > 0
+            for i, (k4, v) in enumerate(zip(keys, valid)):
+                for s in range(4):
+                    if v[s] and k4[s] == x:
+                        if need > 0:
+                            sel[i][s] = True
+                        need -= 1
+    return [4 * q + s for (q, _), m in zip(quads, sel) for s in range(4) if m[s]]
+
+
+def quads_of(keys, tm1, slots, waves=1):
+    """The filter's list of (q, four keys) and its full count."""
+    d, ng = len(keys), (len(keys) + 3) // 4
+    per = -(-ng // (waves * WAVE)) * WAVE
+    out = []
+    for w in range(waves):
+        for q in range(min(ng, w * per), min(ng, (w + 1) * per)):
+            k4 = [keys[4 * q + s] if 4 * q + s < d else MAX32 for s in range(4)]
+            if min(k4) <= tm1:
+                out.append((q, k4))
+    return out[:slots * WAVE], len(out)
+
+
+@pytest.mark.parametrize("fo,slots", [(1, 1), (5, 1), (18, 1), (19, 2), (56, 2)])
+@pytest.mark.parametrize("distinct", [1 << 32, 40, 3])
+def test_quads_equal_sort(fo, slots, distinct):
+    rnd = random.Random(fo * 5 + distinct)
+    pool = None if distinct > 1000 else [rnd.getrandbits(32) for _ in range(distinct - 1)] + [MAX32]
+    for d in (fo + 1, 255, 256, 257, 1023, 4100):
+        if d <= fo:
+            continue
+        keys = [rnd.getrandbits(32) if pool is None else rnd.choice(pool) for _ in range(d)]
+        if d <= 256:
+            lanes = [(q, [keys[4 * q + s] if 4 * q + s < d else 0 for s in range(4)]) for q in range(WAVE)]
+            assert choose_quads(lanes, fo, MAX32, d) == reference(keys, fo), (fo, d)
+        ran = 0
+        for tau in sorted(set(keys))[::max(1, len(set(keys)) // 60)] + [MAX32 + 1]:
+            for waves in (1, 4):
+                quads, n = quads_of(keys, tau - 1, slots, waves)
+                if n > slots * WAVE or sum(k < tau for k in keys) < fo:
+                    continue
+                assert choose_quads(quads, fo, tau - 1, d) == reference(keys, fo), (fo, d, tau)
+                ran += 1
+        assert ran or pool is not None or d > 256

@@ -7,7 +7,9 @@ error would show first: just below and at multiples of cpr, up to the
 largest index whose rows fit in 2^40 bytes of memory. A model of the
 flattened loop (U chunks per lane per pass) checks that every chunk is stored
 exactly once and that every load, those of lanes past the end included,
-stays inside the list and the row."""
+stays inside the list and the row. A model of the miss gather's reads of rows
+that 16-byte vectors do not fit (aligned 16-byte chunks, element by element
+where a chunk reaches past the store) checks the same for every element."""
 import random
 
 import pytest
@@ -61,3 +63,30 @@ def test_every_chunk_stored_once_and_loads_in_range(n, cpr, grid):
     loads, stores = flattened_passes(n, cpr, grid)
     assert sorted(stores) == [(r, o) for r in range(n) for o in range(cpr)]
     assert all(0 <= r < n and 0 <= o < cpr for r, o in loads)
+
+
+@pytest.mark.parametrize("off", [0, 4, 8, 12])
+@pytest.mark.parametrize("rb", [4, 8, 12, 16, 20, 100, 200, 512, 1028, 2052])
+def test_aligned_chunks_cover_a_row_once(rb, off):
+    lo, rows = 4096 + off, 5
+    hi = lo + rows * rb  # the store: any byte outside it must not be read
+    elem = 8 if rb % 8 == 0 and off % 8 == 0 else 4
+    lanes_log2 = 0
+    while lanes_log2 < 6 and (1 << lanes_log2) < (rb + 14) // 16 + 1:
+        lanes_log2 += 1
+    chunks = (rb + 14) // 16 + 1
+    for r in range(rows):
+        row, stored = lo + r * rb, []
+        for lane in range(1 << lanes_log2):
+            for c in range(lane, chunks, 1 << lanes_log2):
+                p = (row & ~15) + 16 * c
+                o = p - row
+                if o >= rb:
+                    continue  # (reads the dummy row)
+                whole = p >= lo and p + 16 <= hi
+                for k in range(16 // elem):
+                    at = o + k * elem
+                    if 0 <= at < rb:
+                        assert whole or (lo <= row + at and row + at + elem <= hi)
+                        stored.append(at)
+        assert sorted(stored) == list(range(0, rb, elem))

@@ -1,107 +1,156 @@
-"""A model of the dedup/relabel route (the NeighborSampler's frontier update
-of Algorithm 2 in the DGL block convention): while writing a sampled id u,
-the sampler sets bit u of a bitmap over the partition-local ids if u is not
-yet in the frontier (pos_of[u] < 0); k_bits_scan then gives every tile of
-4096 words (1024 threads x 4 consecutive words) its exclusive popcount prefix
-(block scan plus look-back across tiles), and each thread emits the set bits
-of its words in ascending order as F[n_prev + prefix + ...] = 32 * word + bit,
-with pos_of[u] = that position, clearing the words; relabel maps every
-sampled id through pos_of.
+"""A model of the frontier scan (the NeighborSampler's frontier update of
+Algorithm 2 in the DGL block convention). The sampler sets bit u of one copy of
+the sampled-id bitmap for every id u that it writes; k_frontier then takes
 
-The model restates those steps and checks them against the definition: the
-new nodes are the ascending unique sampled ids not already in the frontier,
-every relabelled index points at its id, and the bitmap ends empty. It
-restates the kernels' steps; the GPU tests exercise the kernels."""
+- tiles of old rows (the rows of the frontier so far, NT * ITEMS each; none
+  after the last hop), then tiles of TW bitmap words, in any order of blocks;
+- in a bitmap tile, w = (copies or-ed) & ~seen: the new nodes. The thread's
+  words give its place in the tile (exclusive scan of their counts); the set
+  bits are spread into a list of NT * ITEMS entries, chunk by chunk, so that
+  thread x of a chunk takes items x, x + NT, ...; every copy's words are cleared,
+  the new bits join `seen` (after the last hop `seen` is cleared instead);
+- each tile's count of new nodes and of sampled positions (min(row length,
+  fanout) of its rows) and their sums over the tiles before it; item j of the
+  tile is then row n_prev + nodes before + j (old tiles: row0 + j), with offset
+  positions before + those of the tile's items up to j.
+
+Checked against the definition: the new nodes are the ascending unique sampled
+ids not in the frontier; every id points at its row; offsets are the prefix sums
+over all rows; the count of new local ids is written once; bitmaps end clear (or
+hold exactly the frontier). The model restates the kernel's steps at its three
+tile shapes; the GPU tests exercise the kernel."""
 import random
 
 import pytest
 
-NT, ITEMS = 1024, 4
-TILE = NT * ITEMS
+ITEMS = 4
+SHAPES = [(256, 64, 8), (256, 256, 1), (512, 2048, 1)]  # threads, words per tile, bitmap copies
 
 
 def popcount(x):
     return bin(x).count("1")
 
 
-def hop(F, pos_of, sampled, R, L=None):
-    W = -(-R // 32)
-    bits = [0] * (W + 4)
-    for u in sampled:  # emit_id: mark ids not yet in the frontier
-        if pos_of[u] < 0:
-            bits[u >> 5] |= 1 << (u & 31)
+def frontier_scan(shape, F, seen, pos_of, bits, L, last, deg, fo, bptr, rnd):
+    NT, TW, copies = shape
+    W, chunk = len(seen), NT * ITEMS
+    wpt = max(1, TW // NT)
     n_prev = len(F)
-    ntiles = max(1, -(-W // TILE))
-    # per tile: the block's exclusive scan of per-thread popcounts, then the
-    # tile's exclusive prefix over the tiles before it (the look-back's result)
-    tile_tot = []
-    for b in range(ntiles):
-        tile_tot.append(sum(popcount(bits[w]) for w in range(b * TILE, min((b + 1) * TILE, W))))
-    newF = list(F) + [None] * sum(tile_tot)
-    before = 0
-    local_new = []  # written by the thread whose words hold id L (or the last tile)
-    wL = None if L is None else L >> 5
-    for b in range(ntiles):
-        ex = 0
-        for x in range(NT):
-            base = b * TILE + x * ITEMS
-            words = [bits[base + i] if base + i < W else 0 for i in range(ITEMS)]
-            if wL is not None and wL < W and base <= wL < base + ITEMS:
-                below = sum(popcount(words[i]) for i in range(ITEMS) if base + i < wL)
-                below += popcount(words[wL - base] & ((1 << (L & 31)) - 1))
-                local_new.append(before + ex + below)
-            off = n_prev + before + ex
-            for i, wd in enumerate(words):
-                while wd:
-                    low = wd & -wd
-                    u = ((base + i) << 5) + low.bit_length() - 1
-                    wd ^= low
-                    assert newF[off] is None
-                    newF[off] = u
-                    pos_of[u] = off
-                    off += 1
-                if words[i]:
-                    bits[base + i] = 0
-            ex += sum(popcount(wd) for wd in words)
-        before += tile_tot[b]
-    if wL is not None and wL >= W:
-        local_new.append(before)  # the last tile: every id is below L
-    assert not any(bits), "bitmap not cleared"
-    relabelled = [pos_of[u] for u in sampled]
-    if L is None:
-        return newF, relabelled
-    assert len(local_new) == 1, "one writer of the local count"
-    return newF, relabelled, local_new[0]
+    old_tiles = 0 if last else -(-n_prev // chunk)
+    ntiles = old_tiles + -(-W // TW)
+    # every tile's own part: items in order, words cleared
+    tiles, below = [None] * ntiles, []
+    for b in rnd.sample(range(ntiles), ntiles):
+        if b < old_tiles:
+            tiles[b] = [("old", i, F[i]) for i in range(b * chunk, min((b + 1) * chunk, n_prev))]
+            continue
+        word0, items, place = (b - old_tiles) * TW, {}, 0
+        for x in range(min(NT, TW)):
+            i0 = word0 + x * wpt
+            if i0 >= W:
+                continue
+            words = [i0 + y for y in range(wpt) if i0 + y < W]
+            new = []
+            for i in words:
+                got = 0
+                for c in range(copies):
+                    got |= bits[c][i]
+                    bits[c][i] = 0
+                new.append(got & ~seen[i])
+                seen[i] = 0 if last else seen[i] | new[-1]
+            if words[0] <= L >> 5 <= words[-1]:
+                n = sum(popcount(w) for i, w in zip(words, new) if i < L >> 5)
+                below.append((b, place + n + popcount(new[(L >> 5) - words[0]] & ((1 << (L & 31)) - 1))))
+            o = place
+            for i, w in zip(words, new):
+                for bit in range(32):
+                    if w >> bit & 1:
+                        items[o] = 32 * (i - word0) + bit  # (the list entry: relative to the tile)
+                        o += 1
+            place = o
+        assert sorted(items) == list(range(place)), "every item of the tile exactly once"
+        tiles[b] = [("new", j, (word0 << 5) + items[j]) for j in range(place)]
+    # sums over the tiles before each (the look-back's result), then the emission
+    newF, offs = list(F) + [None] * sum(len(t) for t in tiles[old_tiles:]), {}
+    nodes = positions = 0
+    sums = []
+    for t in tiles:
+        sums.append((nodes, positions))
+        nodes += sum(k == "new" for k, _, _ in t)
+        positions += sum(min(deg[v], fo) for _, _, v in t)
+    for b in rnd.sample(range(ntiles), ntiles):
+        n_before, run = sums[b]
+        for c0 in range(0, len(tiles[b]), chunk):
+            for kind, j, v in tiles[b][c0:c0 + chunk]:  # items in list order: NT threads x ITEMS
+                i = j if kind == "old" else n_prev + n_before + j
+                if kind == "new":
+                    assert newF[i] is None
+                    newF[i] = v
+                    pos_of[v] = i
+                run += min(deg[v], fo)
+                assert i + 1 not in offs
+                offs[i + 1] = run
+    if not last:
+        bptr[:] = [0] + [offs[i + 1] for i in range(len(newF))]
+    local = [sums[b][0] + n for b, n in below]
+    if L >> 5 >= W:
+        local.append(nodes)  # the last tile: every id is below L
+    assert len(local) == 1, "one writer of the local count"
+    return newF, local[0]
 
 
-@pytest.mark.parametrize("R,density", [(1, 1.0), (31, 0.5), (33, 0.5), (4096 * 32 + 5, 0.01),
-                                       (3 * 4096 * 32 + 100, 0.002), (50_000, 0.3)])
-def test_new_nodes_are_ascending_unique_and_relabel_points_back(R, density):
-    rnd = random.Random(R)
-    pos_of = [-1] * R
-    F = rnd.sample(range(R), max(1, R // 50))
-    for i, v in enumerate(F):
+def run_hops(shape, R, L, density, hops, seed):
+    rnd = random.Random(seed)
+    W = -(-R // 32)
+    deg = [rnd.choice([0, 1, 3, 7, 40]) for _ in range(R)]
+    F = rnd.sample(range(L), max(1, L // 50)) if L else []
+    pos_of = [rnd.randrange(-5, 5) for _ in range(R)]  # stale positions of earlier steps
+    seen = [0] * W
+    for i, v in enumerate(F):  # the seeds' launch
+        seen[v >> 5] |= 1 << (v & 31)
         pos_of[v] = i
-    k = max(1, int(R * density))
-    sampled = [rnd.randrange(R) for _ in range(k)] + F[:3]  # repeats and ids already in F
-    newF, rel = hop(F, pos_of, sampled, R)
-    want_new = sorted(set(sampled) - set(F))
-    assert newF[:len(F)] == F and newF[len(F):] == want_new
-    assert all(newF[p] == u for p, u in zip(rel, sampled))
-    assert all(pos_of[u] == p for p, u in enumerate(newF))
+    bits = [[0] * W for _ in range(shape[2])]
+    for hop in range(1, hops + 1):
+        sampled = [rnd.randrange(R) for _ in range(int(R * density))] + F[:3]  # repeats and ids already in F
+        for u in sampled:
+            bits[rnd.randrange(shape[2])][u >> 5] |= 1 << (u & 31)
+        bptr, fo = [], rnd.randint(1, 9)
+        newF, local = frontier_scan(shape, F, seen, pos_of, bits, L, hop == hops, deg, fo, bptr, rnd)
+        want = sorted(set(sampled) - set(F))
+        assert newF == F + want
+        assert local == sum(u < L for u in want)
+        assert all(newF[pos_of[u]] == u for u in sampled)
+        assert not any(any(c) for c in bits), "bitmap not cleared"
+        if hop < hops:
+            acc = [0]
+            for v in newF:
+                acc.append(acc[-1] + min(deg[v], fo))
+            assert bptr == acc
+            assert [u for u in range(R) if seen[u >> 5] >> (u & 31) & 1] == sorted(newF)
+        F = newF
+    assert not any(seen), "the frontier bitmap is clear for the next step"
 
 
-@pytest.mark.parametrize("R,density", [(40, 0.5), (4096 * 32 + 5, 0.01), (3 * 4096 * 32 + 100, 0.002)])
-def test_local_count_is_the_prefix_at_L(R, density):
-    """The new nodes below L (local ids), counted by the one thread whose
-    words hold id L, for L at word boundaries, inside words, at tile
-    boundaries, at 0 and at R (every id local)."""
-    rnd = random.Random(R + 1)
-    for L in sorted({0, 1, 31, 32, 33, R // 2, R - 1, R, TILE * 32, TILE * 32 + 7, 2 * TILE * 32 - 1} & set(range(R + 1))):
-        pos_of = [-1] * R
-        F = rnd.sample(range(R), max(1, R // 50))
-        for i, v in enumerate(F):
-            pos_of[v] = i
-        sampled = [rnd.randrange(R) for _ in range(max(1, int(R * density)))]
-        newF, rel, local_new = hop(F, pos_of, sampled, R, L)
-        assert local_new == sum(1 for u in newF[len(F):] if u < L), (R, L)
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("R,density,hops", [(33, 0.5, 2), (700, 0.4, 3), (64 * 32 + 5, 0.6, 2), (3 * 64 * 32 + 40, 0.05, 3)])
+def test_new_nodes_rows_and_offsets(shape, R, density, hops):
+    for seed, L in enumerate((R, R // 2, 1, (R // 64) * 32, R - 1)):
+        run_hops(shape, R, L, density, hops, 100 * R + seed)
+
+
+def test_tiles_of_several_chunks():
+    # 2048 words nearly all set: 32 chunks of a tile; and two tiles
+    run_hops((512, 2048, 1), 2048 * 32 + 77, 40000, 1.5, 1, 5)
+    # more old rows than a tile of them holds
+    run_hops((256, 64, 8), 5000, 4000, 1.0, 3, 6)
+
+
+def test_planted_mistake_fails():
+    # without `seen` a node of the frontier that is sampled again is new again
+    with pytest.raises(AssertionError):
+        rnd = random.Random(1)
+        F, pos_of = [3, 9], [0] * 64
+        pos_of[9] = 1
+        newF, _ = frontier_scan(SHAPES[0], F, [0, 0], pos_of, [[1 << 9, 2] if c == 0 else [0, 0] for c in range(8)], 20,
+                                True, [1] * 64, 1, [], rnd)
+        assert newF == F + [33]

@@ -1,27 +1,25 @@
-"""A model of the row list that k_row_scan writes for the one-wave-per-row
-sampler (the NeighborSampler's per-node draws of Algorithm 2, one wavefront
-per frontier row). Each block of the scan takes one tile of rows; inside the
-block every row longer than the long-row limit goes to the front of an LDS
-array and every other row to its back (LDS atomics, in any order); the
-block's first thread then takes one base per part from two global counters
-(blocks in any order), and the block writes its long rows at
-list[base_long + j] and its other rows at list[end - 1 - (base_other + j)],
-where end is the frontier bound. Wave w of the sampler takes list[w] if
-w < n_long, list[end - 1 - (w - n_long)] if w < n, and nothing otherwise.
+"""A model of the row list for the one-wave-per-row sampler (the
+NeighborSampler's per-node draws of Algorithm 2, one wavefront per frontier
+row). Each block of the launches that write a frontier's rows (k_seed_rows, then
+k_frontier) takes one tile of rows: every row longer than the long-row limit
+goes to the front of the list and every other row to its back. The block takes
+one base per part from two global counters (blocks in any order), and its rows
+take places inside the block's part by shared counters (in any order): long rows
+at list[base_long + j], the others at list[end - 1 - (base_other + j)], where
+end is the frontier bound. The sampler's waves stride over the list: wave w
+takes entries w, w + waves, ... below n, entry x being list[x] if x < n_long,
+else list[end - 1 - (x - n_long)].
 
-The model restates those steps, with blocks and the LDS appends in random
-orders, and checks: every row of the frontier is taken by exactly one wave,
-the waves [0, n_long) take exactly the long rows, no two parts overlap, and
-the waves from n on take nothing. It restates the kernel's steps; the GPU
-tests exercise the kernels."""
+The model restates those steps, with blocks and places in random orders, and
+checks: every row of the frontier is taken by exactly one wave, entries
+[0, n_long) are exactly the long rows, no two parts overlap, and nothing is
+taken from n on. It restates the kernels' steps; the GPU tests exercise the
+kernels."""
 import random
 
 import pytest
 
-TILE = 4096
-
-
-def row_list(deg, n, end, big_min, rnd):
+def row_list(deg, n, end, big_min, rnd, TILE=4096):
     """deg: row lengths of frontier rows 0..n-1 (n <= end)."""
     lst = [None] * end
     counters = [0, 0]
@@ -52,13 +50,9 @@ def row_list(deg, n, end, big_min, rnd):
     return lst, counters
 
 
-def wave_rows(lst, n_long, n, end, grid_waves):
-    taken = []
-    for w in range(grid_waves):
-        if w >= n:
-            continue
-        taken.append((w, lst[w if w < n_long else end - 1 - (w - n_long)]))
-    return taken
+def wave_rows(lst, n_long, n, end, waves):
+    """(list entry, row) of every wave's rows."""
+    return [(x, lst[x if x < n_long else end - 1 - (x - n_long)]) for w in range(waves) for x in range(w, n, waves)]
 
 
 @pytest.mark.parametrize("n,end", [(0, 1), (1, 1), (5, 9), (4095, 4096), (4096, 4096), (4097, 5000),
@@ -68,14 +62,14 @@ def test_every_row_taken_once_long_rows_first(n, end):
     for mix in (0.0, 0.05, 0.5, 1.0):
         big_min = 2048
         deg = [rnd.randint(2049, 60000) if rnd.random() < mix else rnd.randint(0, 2048) for _ in range(n)]
-        lst, (n_long, n_small) = row_list(deg, n, end, big_min, rnd)
+        lst, (n_long, n_small) = row_list(deg, n, end, big_min, rnd, rnd.choice([1024, 2048, 4096]))
         assert n_long + n_small == n
         assert n_long == sum(d > big_min for d in deg)
-        taken = wave_rows(lst, n_long, n, end, end)  # the grid is the frontier bound
+        taken = wave_rows(lst, n_long, n, end, rnd.choice([2, 1000, end + 1]))  # (131,072 waves at most)
         rows = [r for _, r in taken]
         assert sorted(rows) == list(range(n)), "every row exactly once"
-        assert all(deg[r] > big_min for w, r in taken if w < n_long)
-        assert all(deg[r] <= big_min for w, r in taken if w >= n_long)
+        assert all(deg[r] > big_min for x, r in taken if x < n_long)
+        assert all(deg[r] <= big_min for x, r in taken if x >= n_long)
 
 
 def test_planted_mistake_fails():
@@ -84,5 +78,5 @@ def test_planted_mistake_fails():
     n, end = 5000, 6000
     deg = [rnd.randint(0, 5000) for _ in range(n)]
     lst, (n_long, _) = row_list(deg, n, end, 2048, rnd)
-    wrong = [lst[w] if w < n_long else lst[w] for w in range(n)]
+    wrong = [lst[x] for x in range(n)]
     assert sorted(r for r in wrong if r is not None) != list(range(n))

@@ -2,13 +2,15 @@
 
 Replacements: the candidates are the unbuffered halo nodes (S_A >= 0), held
 in rank order; each gets the key ~bits(S_A), so ascending key is descending
-S_A. Four radix-select passes of 8 bits, from the top, find the key T of the
-k'-th candidate: each pass histograms the digit of the candidates matching
-the prefix so far, picks the digit whose exclusive count is below `need` and
-whose inclusive count reaches it, and lowers `need` by the count before it.
-Then the candidates with key < T, in rank order, are stably sorted by key
-(LSD, 8 bits a pass) into R[0 : n_lt], and the first `need` with key == T, in
-rank order, fill R[n_lt : k'].
+S_A. Three radix-select passes of 11, 11 and 10 bits, from the top, find the key
+T of the k'-th candidate: in each pass every block adds the digits of its own
+candidates that match the prefix so far to the one histogram, and the block that
+is last to add picks the digit whose exclusive count is below `need` and whose
+inclusive count reaches it, lowers `need` by the count before it and clears the
+histogram. Then the candidates with key < T, in rank order, are stably sorted by
+key into R[0 : n_lt], and the first `need` with key == T, in rank order, fill
+R[n_lt : k']. The sort is one block's bitonic exchange of (key, position) words
+for up to 4096 pairs, else LSD passes of 8 bits.
 
 Evictions when there are fewer candidates than flagged slots: E (ascending
 slot) is stably sorted by the rank of the slot's node, then by the bits of
@@ -44,69 +46,96 @@ def lsd_sort(pairs):
     return pairs
 
 
+PASSES = ((21, 11), (10, 11), (0, 10))  # shift, bits
+SORT_ONE = 4096
+
+
+def sort_one(pairs):
+    # one block: bitonic over (key, position) words, padded to a power of two
+    m = 2
+    while m < len(pairs):
+        m *= 2
+    w = [(k << 32) | i for i, (k, _) in enumerate(pairs)] + [(1 << 64) - 1] * (m - len(pairs))
+    size = 2
+    while size <= m:
+        step = size // 2
+        while step:
+            for p in range(m // 2):
+                i = 2 * p - (p & (step - 1))
+                j = i + step
+                if (w[i] > w[j]) == ((i & size) == 0):
+                    w[i], w[j] = w[j], w[i]
+            step //= 2
+        size *= 2
+    return [(x >> 32, pairs[x & 0xFFFFFFFF][1]) for x in w[:len(pairs)]]
+
+
+def sort_pairs(pairs):
+    return sort_one(pairs) if len(pairs) <= SORT_ONE else lsd_sort(pairs)
+
+
+def radix_select(words, k, rnd, blocks=5):
+    """Candidates as tuples of 32-bit words; the prefix words of the k'-th
+    smallest, and how many equal to it are still to take. Blocks add their part
+    in any order; the last one picks."""
+    nw = len(words[0]) if words else 1
+    need, pre, msk = k, [0] * nw, [0] * nw
+    for word in range(nw):
+        for shift, bits in PASSES:
+            ghist, done = [0] * (1 << bits), 0
+            for b in rnd.sample(range(blocks), blocks):
+                for c in words[b::blocks]:
+                    if all((x & m) == p for x, m, p in zip(c, msk, pre)):
+                        ghist[(c[word] >> shift) & ((1 << bits) - 1)] += 1
+                done += 1
+                if done < blocks:
+                    continue
+                ex, pick, before = 0, -1, 0
+                for d, n in enumerate(ghist):
+                    if ex < need <= ex + n:
+                        pick, before = d, ex
+                    ex += n
+                assert pick >= 0, "fewer candidates than asked for"
+                need -= before
+                pre[word] |= pick << shift
+                msk[word] |= ((1 << bits) - 1) << shift
+    return pre, need
+
+
 def select_replacements(S_A_by_rank, h_of_rank, k):
     """The kernels' steps: radix select of T, then emit and sort."""
     keys = [(~f32_bits(a)) & 0xFFFFFFFF if a >= 0.0 else None for a in S_A_by_rank]
-    need, prefix, pmask = k, 0, 0
-    if k > 0:
-        for shift in (24, 16, 8, 0):
-            hist = [0] * 256
-            for key in keys:
-                if key is not None and (key & pmask) == prefix:
-                    hist[(key >> shift) & 255] += 1
-            ex, pick, before = 0, -1, 0
-            for d in range(256):
-                if ex < need <= ex + hist[d]:
-                    pick, before = d, ex
-                ex += hist[d]
-            assert pick >= 0, "fewer candidates than asked for"
-            need -= before
-            prefix |= pick << shift
-            pmask |= 255 << shift
-    T = prefix
+    if k == 0:
+        return []
+    (T,), need = radix_select([(x,) for x in keys if x is not None], k, random.Random(k))
     lt = [(key, h_of_rank[r]) for r, key in enumerate(keys) if key is not None and key < T]
     eq = [h_of_rank[r] for r, key in enumerate(keys) if key is not None and key == T]
     assert len(lt) == k - need and len(eq) >= need
-    return [h for _, h in lsd_sort(lt)] + eq[:need]
+    return [h for _, h in sort_pairs(lt)] + eq[:need]
 
 
 def select_replacements_by_gid(S_A_by_gid, rank_g, h_of_rank, gid_of, k):
     """The kernels' steps with S_A over every global id, scanned in id order:
-    an exact radix select over the 64-bit key (~bits(S_A), rank), 8 bits a
-    pass (four on the score word, four on the rank word), then the k' keys
-    at or below it, in id order, stably sorted by rank and then by score."""
+    an exact radix select over the 64-bit key (~bits(S_A), rank), three passes
+    on the score word and three on the rank word, then the k' keys at or below
+    it, in id order, stably sorted by rank and then by score."""
     cands = [((~f32_bits(a)) & 0xFFFFFFFF, rank_g[g]) for g, a in enumerate(S_A_by_gid) if a >= 0.0]
-    need, pre, msk = k, [0, 0], [0, 0]
-    if k > 0:
-        for word in (0, 1):
-            for shift in (24, 16, 8, 0):
-                hist = [0] * 256
-                for c in cands:
-                    if (c[0] & msk[0]) == pre[0] and (c[1] & msk[1]) == pre[1]:
-                        hist[(c[word] >> shift) & 255] += 1
-                ex, pick, before = 0, -1, 0
-                for d in range(256):
-                    if ex < need <= ex + hist[d]:
-                        pick, before = d, ex
-                    ex += hist[d]
-                assert pick >= 0, "fewer candidates than asked for"
-                need -= before
-                pre[word] |= pick << shift
-                msk[word] |= 255 << shift
-        assert need == 1, "ranks are unique: one key at the threshold"
-    T = (pre[0], pre[1])  # the k'-th smallest key
-    emitted = [(c[1], h_of_rank[c[1]]) for c in cands if k > 0 and c <= T]
+    if k == 0:
+        return []
+    pre, need = radix_select(cands, k, random.Random(k))
+    assert need == 1, "ranks are unique: one key at the threshold"
+    emitted = [(c[1], h_of_rank[c[1]]) for c in cands if c <= tuple(pre)]  # (T: the k'-th smallest key)
     assert len(emitted) == k
-    by_rank = lsd_sort(emitted)
-    keyed = [((~f32_bits(S_A_by_gid[gid_of[h]])) & 0xFFFFFFFF, h) for _, h in by_rank] if by_rank else []
-    return [h for _, h in lsd_sort(keyed)]
+    by_rank = sort_pairs(emitted)
+    keyed = [((~f32_bits(S_A_by_gid[gid_of[h]])) & 0xFFFFFFFF, h) for _, h in by_rank]
+    return [h for _, h in sort_pairs(keyed)]
 
 
 def narrow_evictions(E, S_E, rank_of_slot, k):
     """The kernels' steps: two stable sorts (rank, then S_E bits), keep k, sort by slot."""
-    pairs = lsd_sort([(rank_of_slot[s], s) for s in E])
-    pairs = lsd_sort([(f32_bits(S_E[s]), s) for _, s in pairs])
-    return [s for _, s in lsd_sort([(s, s) for _, s in pairs[:k]])]
+    pairs = sort_pairs([(rank_of_slot[s], s) for s in E])
+    pairs = sort_pairs([(f32_bits(S_E[s]), s) for _, s in pairs])
+    return [s for _, s in sort_pairs([(s, s) for _, s in pairs[:k]])]
 
 
 def score_mix(rnd, n, zero_frac=0.7):
@@ -193,3 +222,14 @@ def test_replacement_select_by_global_id_matches_sort(seed):
                                              key=lambda r: (-S_by_rank[r], r))][:k]
         assert select_replacements_by_gid(S_by_gid, rank_g, h_of_rank, gid_of, k) == want, (seed, H, k)
         assert select_replacements(S_by_rank, h_of_rank, k) == want
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3, 63, 64, 65, 1000, 4095, 4096])
+def test_both_sorts_are_stable(n):
+    rnd = random.Random(n)
+    for span in (1, 7, 1 << 32):
+        pairs = [(rnd.randrange(span), i) for i in range(n)]
+        want = sorted(pairs, key=lambda kv: kv[0])
+        assert sort_one(pairs) == want and lsd_sort(pairs) == want
+    pairs = [(0xFFFFFFFF, i) for i in range(n)]  # the padding's key is no smaller
+    assert sort_one(pairs) == pairs

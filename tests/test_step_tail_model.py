@@ -12,8 +12,15 @@ interleaving and grid size: the sizes are cleared exactly once; no block
 reads its count, and block 0 does not publish, after the clear; the mailbox
 holds the step's sizes; and the sizes end cleared with the counter at zero,
 ready for the slot's next step. A planted mistake (the clear by block 0 after
-its own publish, without the counter) fails it. It restates the kernel's
-protocol; the GPU tests exercise the kernel."""
+its own publish, without the counter) fails it.
+
+Where both gathers run in one launch, nothing at the end of a step clears its
+sizes: the first launch of the step before the slot's next one does, if that slot
+is no longer in flight by then, and a fill at the start of the next step if it
+still was. The second model runs calls in random orders (look-ahead, waited-for,
+timed, waits) and checks that every step starts from clear sizes and that no
+clear meets a slot in flight. The models restate the kernels' and the calls'
+protocol; the GPU tests exercise them."""
 import random
 
 import pytest
@@ -80,3 +87,41 @@ def test_planted_mistake_fails():
         _, _, events, _, want = run(4, rnd, clear_by_block0=True)
         bad += any(e[0] == "read" and e[2] != want["n_miss"] for e in events)
     assert bad > 0
+
+
+SLOTS = 3
+
+
+@pytest.mark.parametrize("seed", range(20))
+def test_sizes_are_clear_when_a_step_starts(seed):
+    rnd = random.Random(seed)
+    sizes, clear, flying, t, fills = [0] * SLOTS, [False] * SLOTS, {}, 0, 0
+
+    def wait(slot):
+        if flying.pop(slot):  # split launches: the step's own miss gather cleared its sizes
+            sizes[slot] = 0
+
+    for _ in range(400):
+        slot, nxt = t % SLOTS, (t + 1) % SLOTS
+        if slot in flying or (flying and rnd.random() < 0.4):
+            wait(rnd.choice(sorted(flying)) if slot not in flying else slot)
+            continue
+        split = rnd.random() < 0.3  # gathers timed: k_gather_miss ends the step
+        ahead = not clear[nxt] and nxt not in flying
+        if not clear[slot]:
+            sizes[slot] = 0
+            fills += 1
+        clear[slot] = False
+        assert sizes[slot] == 0, "a step starts from another step's sizes"
+        if ahead:
+            assert nxt not in flying, "the sizes of a step in flight are cleared"
+            sizes[nxt] = 0
+            clear[nxt] = True
+        sizes[slot] = t + 1
+        flying[slot] = split
+        if split:
+            clear[slot] = True
+        t += 1
+        if rnd.random() < 0.3 and len(flying) == 1:  # waited for at once
+            wait(slot)
+    assert t > 50 and fills < t, "the clears ahead are used"
