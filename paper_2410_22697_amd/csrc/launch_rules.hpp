@@ -45,7 +45,10 @@ inline int64_t score_bytes(int64_t n) { return n < 4 ? 16 : n * 4; }
 // look-ahead steps on the 111M-node share (9 HBM rows per host row), us per pass
 // by blocks: 4096 2990, 512 2960, 256 2865, 128 2765, 64 2765, 32 2783; on the
 // 2.45M-node graph 4096 5330, 128 5292, 32 5290; a step waited for on the
-// 111M-node share 4096 557, by this rule 548. By the step's own lists: few misses
+// 111M-node share 4096 557, by this rule 548. Least share and factor: 32 and 4,
+// 96 and 16, 256 and 64: 16 steps with a round on the 170K-node graph 5242, 4937,
+// 4932; eight on the 111M-node share 2762, 2776, 2952, on the 2.45M-node graph
+// 5303, 5305, 5324. By the step's own lists: few misses
 // (the link is done early) get the whole grid (190K HBM rows, 880 host rows: 126
 // us a step, 153 with the share of a step of 7 and 1).
 constexpr uint64_t kMinHbmShare = 96;

@@ -874,7 +874,13 @@ void free_ctx(massive_ctx* c) {
 // the ids new), so many small tiles spread the work; in large ones a tile
 // holds few new nodes and the look-back over the tiles bounds the launch:
 // 487K words (15.6M ids), per launch: 2048 words by 512 threads 13.4 us, 1024
-// by 256 17.2, 512 by 512 27.3.
+// by 256 17.2, 512 by 512 27.3. The lines lie where the shapes cross: us of a
+// step waited for (1024 seeds, fanouts 15, 10, 5, 64-byte rows) / of four
+// look-ahead steps, 64 words and eight copies - 256 words - 2048 words:
+//     1K words 109/397 - 149/611 - 214/956   4K 140/573 - 147/596 - 221/1024
+//     8K 158/656 - 155/664 - 203/950         16K 175/745 - 169/720 - 197/889
+//    64K 249/1100 - 194/877 - 195/914        96K 285/1273 - 202/948 - 196/927
+//   128K 325/1466 - 217/1015 - 205/973      256K 434/1951 - 270/1293 - 215/1086
 struct FrontierShape {
   int nt, tw;
   int copies;  // of the sampled-id bitmap (ms::mark_bits)
@@ -882,8 +888,8 @@ struct FrontierShape {
 };
 
 FrontierShape frontier_shape(int64_t W) {
-  if (W <= 16384) return {256, 64, (int)ms::kSmallCopies};
-  if (W <= 131072) return {256, 256, 1};
+  if (W <= 8192) return {256, 64, (int)ms::kSmallCopies};
+  if (W <= 81920) return {256, 256, 1};
   return {512, 2048, 1};
 }
 

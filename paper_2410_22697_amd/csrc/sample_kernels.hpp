@@ -231,7 +231,12 @@ constexpr int kCandCap = kCandSlots * MS_WAVE;  // candidates per wave (LDS): 32
 constexpr int64_t kBigRow = 2048;
 constexpr int64_t kBigBlocks = 2048;  // blocks that walk the big list (8 per CU)
 constexpr int64_t kBlockRowsMax = 65536;  // frontiers up to this size sample long rows by blocks
-constexpr int64_t kRowWavesMax = 131072;  // waves of k_sample_waves at most
+// Waves of k_sample_waves at most: enough for the frontiers that occur, where a
+// grid for the bound would dispatch many waves that find no row. Look-ahead
+// steps, us per pass by this limit: eight on the 111M-node share 32K 2879, 64K
+// 2761, 128K 2750, the whole bound 2780; four bf16 ones of 4096 seeds on the
+// 2.45M-node graph 128K 7555-7650, the whole bound (1.4M) 7750-7810.
+constexpr int64_t kRowWavesMax = 131072;
 constexpr int kTauIters = 64;         // threshold passes: x4 growth (<= 16) then bisection (<= 33)
 
 struct SampleArgs {
