@@ -40,9 +40,9 @@ HBM_PEAK_GBPS = 8000.0       # MI355X HBM3E
 PCIE_PEAK_GBPS = 64.0        # PCIe 5.0 x16, one direction
 LINK_CEILING_GBPS = 55.0     # measured: zero-copy row reads of a pinned store by 16 blocks
 # Batches in flight (the library allows up to three): with two, the next
-# step's sampling overlaps the current step's host-link reads and never the
-# HBM gather; a third lets sampling run beside the HBM gather too, which
-# slows it, with no gain while the host link bounds the step.
+# step's sampling overlaps the current step's host-link reads (the HBM rows move
+# beside them, or, where the gathers are timed, before them and alone); a third
+# has no gain while the host link bounds the step.
 DEFAULT_DEPTH = 2
 # VALU issue peak of the sampler, in Philox keys per second: 256 CUs issue one
 # wave64 VALU instruction per clock each (four SIMDs, four clocks per wave64

@@ -25,17 +25,7 @@ __device__ __forceinline__ uint32_t fmix32(uint32_t x) {
 }
 
 // Open-addressing table (linear probing, load <= 1/2): entry = slot << 32 | h.
-__device__ __forceinline__ int32_t hash_find(const uint64_t* __restrict__ tab, uint32_t mask, int32_t h) {
-  uint32_t i = fmix32((uint32_t)h) & mask;
-  while (true) {
-    const uint64_t e = tab[i];
-    if ((uint32_t)e == (uint32_t)h) return (int32_t)(e >> 32);
-    if (e == kEmpty) return -1;
-    i = (i + 1) & mask;
-  }
-}
-
-// The same search continued from entry i (after a window of entries that
+// The search of h from entry i on (classify's, after a window of entries that
 // held neither h nor an empty entry).
 __device__ __forceinline__ int32_t hash_find_from(const uint64_t* __restrict__ tab, uint32_t mask, int32_t h,
                                                   uint32_t i) {
@@ -424,9 +414,9 @@ __global__ __launch_bounds__(256) void k_gather_hbm(const int2* __restrict__ lis
 // a replacement row crosses the link once, together with the misses (the
 // merged fetch of Algorithm 2), and the lane that writes its first chunk
 // stamps the slot landed. Every kernel that reads a buffer row because of
-// that stamp (a later HBM gather) runs after this one in stream order; a
+// that stamp (a later step's HBM rows) runs after this one in stream order; a
 // refill chunk that sees it skips a row this kernel writes anyway (same
-// bytes). Block 0 publishes the step (the completion above) once its share
+// bytes). As a launch of its own (gathers timed), block 0 publishes the step (the completion above) once its share
 // of the rows is done, so no kernel follows this one in the step (publishing
 // first, beside the next step's sampling, measured ~2% slower before the
 // first round; publishing from the last block to finish, ~1% slower in the
@@ -586,10 +576,12 @@ __global__ __launch_bounds__(256) void k_gather_miss(MissArgs a, int64_t rb, uin
 // Both gathers of a step in one launch: the first `blocks` blocks are the miss
 // gather's, the next one publishes the step (no other block writes what it
 // reads, and the host looks once the launch has ended), the others are the HBM
-// gather's. The HBM rows then move while the
-// link's rows are under way, and cost the link nothing measurable (the
-// 111M-node share: 250 us for both, 250 for the miss gather after the HBM
-// gather's 44), though the HBM gather itself slows beside host reads. us per
+// gather's (as many as hbm_share names; the rest leave at once). The HBM rows
+// then move while the link's rows are under way, and cost the link nothing
+// measurable (the 111M-node share: 250 us for both, 250 for the miss gather
+// after the HBM gather's 44), though the HBM gather itself slows beside host
+// reads. One vector width serves both (a store off a 16-byte boundary bounds the
+// launch by its host rows whatever the HBM part's is: 6156 and 6209 us). us per
 // pass against one after the other: eight look-ahead steps on the 2.45M-node
 // graph 5773 -> 5323, on the 111M-node share 3038 -> 2984, four bf16 steps with
 // a round 7936 -> 7688, 16 steps with a round on the 170K-node graph 5219 ->
@@ -795,8 +787,9 @@ __global__ void k_materialize(float* __restrict__ S_E, int32_t* __restrict__ hit
 // up. |C| = H - cap always: a halo node has S_A = -1 exactly while it is
 // buffered (init, and the swap's S_A := -1 for a replacement) and S_A >= 0
 // otherwise (misses only add to it; an evicted node gets its last S_E >= 0).
-// (A round is bound by its launches where the buffer is small: 40 launches of
-// 1.5-5 us before, 8 to 19 now.)
+// (A round is bound by its launches where the buffer is small: 38 launches of
+// 1.5-5 us before. Now, S_A by rank: 8 with up to kSortOne slots, 19 with more;
+// by global id 13 and 35; the narrowing at f > 50% adds 6 and 39.)
 template <bool TICKETS>
 __global__ __launch_bounds__(kScanNT) void k_round_evict(float* __restrict__ S_E, int32_t* __restrict__ hitcnt,
                                                          int64_t cap, int32_t steps, float gamma, float alpha,
@@ -856,7 +849,7 @@ __global__ __launch_bounds__(kScanNT) void k_round_evict(float* __restrict__ S_E
     rs->k = k;
     rs->need = k;
     rs->prefix = rs->pmask = rs->prefix_lo = rs->pmask_lo = 0;
-    rs->n_lt = rs->n_eq = 0;
+    rs->n_lt = 0;
     rs->nE_sel = k < nE ? nE : 0;
     rs->k_sel = k < nE ? k : 0;
     rs->done = 0;
@@ -1020,7 +1013,7 @@ __global__ __launch_bounds__(256) void k_select_pass(const float* __restrict__ S
 // the first `need` with key == T go straight to R[n_lt + ...]. S_A is kept by
 // rank, so the one pass reads it in order; the halo ids are read only where
 // they are written. Two single-pass scans, one per class (flags_eq after
-// flags_lt); the last tile writes n_lt and n_eq.
+// flags_lt); the last tile writes n_lt.
 template <bool TICKETS>
 __global__ __launch_bounds__(kScanNT) void k_rank_emit(const float* __restrict__ S_A,
                                                        const int32_t* __restrict__ h_of_rank, int64_t H,
@@ -1071,7 +1064,6 @@ __global__ __launch_bounds__(kScanNT) void k_rank_emit(const float* __restrict__
   }
   if (tile == gridDim.x - 1 && threadIdx.x == 0) {
     rs->n_lt = (int64_t)blt + tlt;
-    rs->n_eq = (int64_t)beq + teq;
   }
 }
 

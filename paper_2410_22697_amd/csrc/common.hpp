@@ -101,13 +101,6 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T* lds, T* total) {
   return res;
 }
 
-template <int NT, typename T>
-__device__ __forceinline__ T block_sum(T v, T* lds) {
-  T total;
-  (void)block_exclusive_scan<NT>(v, lds, &total);
-  return total;
-}
-
 // a ^ b ^ key in one instruction: gfx950's three-input bitwise operation
 // (truth table 0x96 = XOR of all three); key is wave-uniform (an SGPR, the
 // one scalar operand the instruction may take).
@@ -115,24 +108,6 @@ __device__ __forceinline__ uint32_t xor3_key(uint32_t a, uint32_t b, uint32_t ke
   uint32_t r;
   asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "s"(key));
   return r;
-}
-
-// Philox4x32-10 block function (Salmon, Moraes, Dror, Shaw, SC'11): ten
-// rounds; each round takes the 64-bit products of counter words 0 and 2
-// with two fixed multipliers, mixes their high halves with words 1 and 3
-// and the round key, and the key advances by two Weyl constants per round.
-__device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    const uint64_t a = (uint64_t)0xD2511F53u * c.x;
-    const uint64_t b = (uint64_t)0xCD9E8D57u * c.z;
-    const uint4 n = make_uint4((uint32_t)(b >> 32) ^ c.y ^ k0, (uint32_t)b,
-                               (uint32_t)(a >> 32) ^ c.w ^ k1, (uint32_t)a);
-    c = n;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  return c;
 }
 
 __device__ __forceinline__ uint32_t word_of(const uint4& w, int s) {
@@ -160,7 +135,7 @@ struct RoundState {
   int64_t need;            // ties at the threshold still to take
   uint32_t prefix, pmask;  // radix-select prefix of the threshold key (S_A word)
   uint32_t prefix_lo, pmask_lo;  // ... and of its rank word (scores by global id)
-  int64_t n_lt, n_eq;      // candidates strictly before / equal to the threshold
+  int64_t n_lt;            // candidates strictly before the threshold
   int64_t nE_sel, k_sel;   // |E| and k' when k' < |E| (E must be narrowed), else 0
   int32_t done, pad;       // blocks of the current select pass that have added their bins
 };

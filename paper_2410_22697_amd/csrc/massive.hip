@@ -59,8 +59,9 @@ inline unsigned grid_for(int64_t n, int nt, int64_t cap = 16384) {
 // massive_sample_noalloc takes a step's per-step buffers (sizes, the two
 // gather lists, the write-through slots, the sampler's row list, the scan flags)
 // from this file-scope array instead of the context's. Layout: two StepSizes
-// (512 B each; the calls take them in turn, and each clears the other's) | hbm list int2[kNoAllocMaxRows] | miss list int2[..] | write-through
-// slots int32[..] | big rows int32[..] | scan flags uint64[kNoAllocFlagWords].
+// (512 B each; the calls take them in turn, and each clears the other's) | hbm
+// list int2[kNoAllocMaxRows] | miss list int2[..] | write-through slots int32[..]
+// | big rows int32[..] | scan flags uint64[kNoAllocFlagWords].
 // Each GPU holds its own copy (~30 MiB) while the library is loaded; its device
 // address is looked up once per device, in massive_init.
 constexpr int64_t kNoAllocMaxRows = 1310720;  // frontier rows (covers a 1,081,344-row bound)
@@ -133,7 +134,9 @@ struct massive_ctx {
   int64_t host_blocks = 16;
   int64_t host_blocks_light = 12;
   int64_t host_rows_seen = -1;  // host rows of the last step waited for (-1: none yet)
-  bool slot_clear[MASSIVE_MAX_INFLIGHT] = {};  // the slot's sizes were cleared by its last step's miss gather
+  // the slot's sizes are clear for its next step: its last step's miss gather
+  // clears them (gathers in two launches), or the first launch of a later step
+  bool slot_clear[MASSIVE_MAX_INFLIGHT] = {};
   int64_t refill_blocks = 16; // grid of the refill (host link, off the critical path)
   double mu32[MASSIVE_MAX_HOPS] = {};    // sampler threshold targets, x 2^32
   int quad_slots[MASSIVE_MAX_HOPS] = {};  // the sampler's candidate list (ms::quad_slots)
@@ -198,13 +201,16 @@ struct massive_ctx {
   std::vector<TimedRange> lpending;
   bool staged() const { return link_mode == MASSIVE_LINK_STAGED; }
   // per step slot (step t uses slot t % MASSIVE_MAX_INFLIGHT): classify done
-  // (main), HBM gather done and miss gather + mailbox done (side)
+  // (main), HBM gather done (side; only where the gathers are two launches) and
+  // gathers + mailbox done (side)
   hipEvent_t ev_cls_done[kSlots] = {}, ev_hbm_done[kSlots] = {}, ev_batch_done[kSlots] = {};
   hipEvent_t ev_round_done = nullptr, ev_refill_done = nullptr;
   bool slot_both[kSlots] = {};  // the slot's step ran both gathers in one launch (ev_hbm_done was not recorded)
   bool round_unclassified = false;  // a round was enqueued that no classify has waited for yet
-  // The refill of the last round is copied in chunks, one after each of the
-  // next steps' HBM gathers (host-link reads never overlap an HBM gather).
+  // The refill of the last round is copied in chunks, one in each of the next
+  // steps: beside the step's shared gather launch, after its classify; where the
+  // gathers are two launches (timed) after the HBM gather, which then has the
+  // memory system to itself.
   int32_t round_id = 0;          // rounds so far, as stamped in slot_round / landed
   int32_t refill_chunks = 1;     // chunks per round: min(delta - 1, 32), one per step of the interval
   int32_t chunks_left = 0;       // chunks of round_id's refill not yet launched
@@ -549,7 +555,7 @@ void launch_refill(massive_ctx* c, hipStream_t s, const int64_t* count, int64_t 
 }
 
 // Launches the next `count` pending refill chunks on the copy stream, after
-// event `after` (the HBM gather they must not overlap).
+// event `after` (the step's classify, or a timed HBM gather).
 int launch_refill_chunks(massive_ctx* c, int count, hipEvent_t after) {
   while (count-- > 0 && c->chunks_left > 0) {
     if (after) {
@@ -936,8 +942,8 @@ int init_impl(massive_ctx* c, const massive_init_args* a) {
   if (const char* e = getenv("MASSIVE_HBM_BLOCKS")) c->hbm_blocks = std::max(1, atoi(e));
   if (const char* e = getenv("MASSIVE_HOST_BLOCKS")) c->host_blocks = c->host_blocks_light = std::max(1, atoi(e));
   if (const char* e = getenv("MASSIVE_REFILL_BLOCKS")) c->refill_blocks = std::max(1, atoi(e));
-  // one chunk after each of the next steps' HBM gathers, all launched before
-  // the step of the next round, so that round never waits for a chunk in flight
+  // one chunk in each of the next steps, all launched before the step of the
+  // next round, so that round never waits for a chunk in flight
   c->refill_chunks = std::max<int32_t>(1, std::min<int32_t>(a->delta - 1, 32));
   if (const char* e = getenv("MASSIVE_REFILL_CHUNKS")) c->refill_chunks = std::max(1, atoi(e));
   if (const char* e = getenv("MASSIVE_BIG_ROW")) c->big_min = std::max<int64_t>(256, atoll(e));
@@ -1657,9 +1663,9 @@ int massive_batch_wait(massive_ctx* c, massive_batch* io) {
     return c->fail(MASSIVE_EHIP, "hipEventSynchronize: %s", hipGetErrorString(e));
   }
   // Steps issued before this one and still in flight decide whether it is
-  // valid: a step that failed on the device skipped its dedup scan and its
-  // classify, so its bitmap marks and frontier positions stayed set, and every
-  // later step sampled against them.
+  // valid: a step that failed on the device skipped its frontier scans and its
+  // classify, so its marks in the bitmaps stayed set, and every later step
+  // sampled against them.
   for (int i = 0; i < kSlots; ++i)
     if (c->infl[i].io && c->infl[i].step < f.step) {
       CK(hipEventSynchronize(c->ev_batch_done[i]));
@@ -1790,7 +1796,8 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
   // the main stream (the next classify waits for it). It follows, in stream
   // order, the previous round's refill chunks, which read the fill list, the
   // round state and the slot stamps that it rewrites; it starts after this
-  // step's classify and HBM gather (hit counts, scores; the gather runs alone).
+  // step's classify (hit counts, scores; the gathers read nothing that it
+  // writes), and after a timed HBM gather, which runs alone.
   hipStream_t s = c->s_copy;
   const int64_t cap = c->cap, H = c->H;
   ms::RoundState* rs = c->d_rs;
@@ -1872,11 +1879,11 @@ int evict_step_impl(massive_ctx* c, int32_t* evicted, int32_t* slots, int32_t* r
   }
   CK(hipEventRecord(c->ev_round_done, s));
   c->round_unclassified = true;
-  // the refill is copied in chunks after the next steps' HBM gathers; the last
-  // step's miss gather may still write rows of the previous round's
-  // replacements into slots this round reassigns, so the new refill comes after
-  // it (in the staged mode the link stream orders them: the worker enqueues
-  // the new chunks after that step's tail)
+  // the refill is copied in chunks in the next steps; the last step's miss
+  // gather may still write rows of the previous round's replacements into slots
+  // this round reassigns, so the new refill comes after it (in the staged mode
+  // the link stream orders them: the worker enqueues the new chunks after that
+  // step's tail)
   if (!c->staged() && step_in_flight) CK(hipStreamWaitEvent(s, c->ev_batch_done[tl % kSlots], 0));
   c->chunks_left = c->refill_chunks;
   c->round_pending_rows = true;

@@ -205,24 +205,27 @@ __global__ __launch_bounds__(kScanNT) void k_seed_rows(const int64_t* __restrict
 
 // --------------------------------------------------------------- sampler
 // One wavefront per frontier node. Rows with d <= fanout are copied. For
-// longer rows the choice is the fanout positions of smallest (key, j),
-// found in two stages:
-//   1. a threshold pass draws every key (lane q of an iteration draws one
-//      Philox block = keys of positions 4q..4q+3) and keeps, in ascending j,
-//      the (key, j) pairs with key < tau; tau is set so that about
-//      fanout + 3*sqrt(fanout) + 3 keys survive, and is bisected if fewer than
-//      fanout or more than the list capacity survive (rare);
-//   2. a bitwise search over ballots finds the fanout-th smallest surviving
-//      key T (it starts below tau's top bit), ties at T are taken in list
-//      order (= ascending j), and the chosen positions are written in
-//      ascending j.
+// longer rows the choice is the fanout positions of smallest (key, j), written
+// in ascending j:
+//   - rows of up to 256 positions: every key is in the wave's registers (one
+//     Philox block a lane), and choose_quads takes the smallest;
+//   - longer rows, fanouts up to 56: a threshold pass draws every key (lane q of
+//     an iteration draws one Philox block = keys of positions 4q..4q+3, a quad)
+//     and keeps, in ascending q, the quads with a key < tau; choose_quads then
+//     chooses among their keys;
+//   - longer rows, larger fanouts: the pass keeps the (key, j) pairs with
+//     key < tau, and select_emit finds the fanout-th smallest key T by a bitwise
+//     search over ballots (from below tau's top bit); ties at T are taken in
+//     list order (= ascending j).
+// tau is set so that about fanout + 3*sqrt(fanout) + 3 keys survive, and is
+// bisected if fewer than fanout or more than the list holds survive (rare).
 // The chosen ids are marked in the sampled-id bitmap as they are written. Rows
-// longer than big_min (listed as the frontier's rows were written) are taken first. Where the frontier is small, so that its few longest rows bound
-// the hop's time, each of them gets a whole block: its waves filter
-// consecutive quarters of the row with the same tau, and the four candidate
-// lists, concatenated in order, are the row's list in ascending j. Otherwise
-// (many rows keep the chip busy) each gets one wave, ahead of the shorter
-// rows. Other rows get one wave each.
+// longer than big_min (listed as the frontier's rows were written) are taken
+// first. Where the frontier is small, so that its few longest rows bound the
+// hop's time, each of them gets a whole block: its waves filter consecutive
+// quarters of the row with the same tau, and the four lists, concatenated in
+// order, are the row's list. Otherwise (many rows keep the chip busy) each gets
+// one wave, ahead of the shorter rows. Other rows get one wave each.
 constexpr int kSampleWaves = 4;  // k_sample_blocks: waves per block (a long row's quarters)
 constexpr int kRowWaves = 2;     // k_sample_waves: waves per workgroup (one row each)
 constexpr int kCandSlots = 5;                   // candidates per lane in the selection
@@ -302,7 +305,7 @@ struct Row {
 // of the counter are the same across the row, so round 1's product of word 2
 // (t) and round 2's product of word 0 (which round 1 builds from t, v and the
 // key only) are computed once per row; the other rounds are the published
-// block function unchanged (see philox4x32_10).
+// block function unchanged.
 struct PhiloxRow {
   uint32_t x1, y1;      // words 0 and 1 after round 1
   uint32_t a2hi, a2lo;  // round 2's 64-bit product of word 0
