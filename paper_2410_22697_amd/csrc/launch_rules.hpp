@@ -13,15 +13,16 @@ namespace ms {
 // wait too. Each XCD starts a launch's blocks in order, so the XCD that the
 // first missing tile of scan A needs holds no waiting block of A: the others
 // have to fill it alone. Scans of at most ordered_scan_waves waves therefore
-// keep block order: three of them leave every XCD (32 CUs of 32 waves, which
-// every scan kernel can fill) the 16 waves of the largest block, and HIP runs a
-// process's streams on 4 hardware queues (more, if GPU_MAX_HW_QUEUES asks for
-// them: the limit falls with their number). Larger scans take tickets: a block
-// takes the next tile when it starts, so every tile before a waiting one
-// belongs to a running block, whatever else runs. Tickets cost a launch a round
-// trip before its first load and are handed out one after the other (k_frontier,
-// 282 tiles: 19.0 -> 20.5 us), which is why they are not used everywhere.
-// (Several processes on one card add up their queues; the wait is bounded too.)
+// keep block order: three of them leave every XCD (32 CUs of 32 waves; those of
+// a kernel whose registers leave room for half as many count twice) the 16 waves
+// of the largest block, and HIP runs a process's streams on 4 hardware queues
+// (more, if GPU_MAX_HW_QUEUES asks for them: the limit falls with their number).
+// Larger scans take tickets: a block takes the next tile when it starts, so
+// every tile before a waiting one belongs to a running block, whatever else
+// runs. Tickets cost a launch a round trip before its first load and are handed
+// out one after the other (k_frontier, 282 tiles: 19.0 -> 20.5 us; k_round_evict,
+// 845 tiles: 39 -> 49), which is why they are not used everywhere. (Several
+// processes on one card add up their queues; the wait is bounded too.)
 constexpr int64_t kXcdWaves = 32 * 32, kXcds = 8;
 inline int64_t ordered_scan_waves(int queues) {
   return kXcds * (kXcdWaves - 16) / ((queues > 4 ? queues : 4) - 1);

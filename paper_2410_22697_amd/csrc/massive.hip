@@ -875,28 +875,40 @@ void free_ctx(massive_ctx* c) {
   delete c;
 }
 
-// Threads per block and bitmap words per tile of the frontier scans, by the
-// words of the id space. Small spaces are dense (a hop finds a large part of
-// the ids new), so many small tiles spread the work; in large ones a tile
-// holds few new nodes and the look-back over the tiles bounds the launch:
+// Threads per block, bitmap words per tile and rows per thread of the frontier
+// scans, by the words of the id space. Small spaces are dense (a hop finds a
+// large part of the ids new), so many small tiles spread the work; in large ones
+// a tile holds few new nodes and the look-back over the tiles bounds the launch:
 // 487K words (15.6M ids), per launch: 2048 words by 512 threads 13.4 us, 1024
-// by 256 17.2, 512 by 512 27.3. The lines lie where the shapes cross: us of a
-// step waited for (1024 seeds, fanouts 15, 10, 5, 64-byte rows) / of four
-// look-ahead steps, 64 words and eight copies - 256 words - 2048 words:
-//     1K words 109/397 - 149/611 - 214/956   4K 140/573 - 147/596 - 221/1024
-//     8K 158/656 - 155/664 - 203/950         16K 175/745 - 169/720 - 197/889
-//    64K 249/1100 - 194/877 - 195/914        96K 285/1273 - 202/948 - 196/927
-//   128K 325/1466 - 217/1015 - 205/973      256K 434/1951 - 270/1293 - 215/1086
+// by 256 17.2, 512 by 512 27.3. us of a step waited for (fanouts 15, 10, 5,
+// 16-byte rows):
+//     128, 1024, 4096 seeds   64 words, 8 copies   256 words
+//       8.5K words             92, 132, 184         87, 131, 190
+//        11K                   92, 133, 194         86, 129, 195
+//        15K                   95, 140, 207         88, 134, 206
+//     1024, 4096 seeds         256 words            2048 words
+//        65K                  163, 281             165, 305
+//       100K                  178, 311             170, 320
+//       131K                  189, 332             175, 333
+//       200K                  225, 387             182, 348
+// The lines lie where the larger tile is no slower for any of these batches.
+// Rows per thread: eight in the small tile, whose 2048 ids are then one chunk
+// (831 seeds on 591 words: 131 us a step, 136 with four, two chunks a dense tile);
+// four in the others, which then take 64 registers instead of 112 and hold their
+// share of the chip with twice the waves (scan_takes_tickets), as fast: us per
+// pass, eight -> four: eight look-ahead steps on 487K words 2778 -> 2762, on 50K
+// words 5344 -> 5340, a step of 4096 seeds on 60K words 276 -> 276.
 struct FrontierShape {
   int nt, tw;
+  int items;   // rows in flight per thread
   int copies;  // of the sampled-id bitmap (ms::mark_bits)
-  int64_t rows() const { return (int64_t)nt * ms::kFrItems; }  // rows of a tile of old rows
+  int64_t rows() const { return (int64_t)nt * items; }  // rows of a tile of old rows
 };
 
 FrontierShape frontier_shape(int64_t W) {
-  if (W <= 8192) return {256, 64, (int)ms::kSmallCopies};
-  if (W <= 81920) return {256, 256, 1};
-  return {512, 2048, 1};
+  if (W <= 12288) return {256, 64, 8, (int)ms::kSmallCopies};
+  if (W <= 131072) return {256, 256, 4, 1};
+  return {512, 2048, 4, 1};
 }
 
 int init_impl(massive_ctx* c, const massive_init_args* a) {
@@ -1319,26 +1331,26 @@ void launch_sampler(bool by_waves, int quads, unsigned grid, hipStream_t s, hipE
 }
 
 void launch_frontier(const FrontierShape& f, bool last, unsigned grid, hipStream_t s, const ms::FrontierArgs& fa) {
-#define MS_FR2(NT, TW, COPIES, TICKETS)                                        \
-  do {                                                                         \
-    if (last)                                                                  \
-      ms::k_frontier<NT, TW, true, COPIES, TICKETS><<<grid, NT, 0, s>>>(fa);   \
-    else                                                                       \
-      ms::k_frontier<NT, TW, false, COPIES, TICKETS><<<grid, NT, 0, s>>>(fa);  \
+#define MS_FR2(NT, TW, IT, COPIES, TICKETS)                                        \
+  do {                                                                             \
+    if (last)                                                                      \
+      ms::k_frontier<NT, TW, IT, true, COPIES, TICKETS><<<grid, NT, 0, s>>>(fa);   \
+    else                                                                           \
+      ms::k_frontier<NT, TW, IT, false, COPIES, TICKETS><<<grid, NT, 0, s>>>(fa);  \
   } while (0)
-#define MS_FR(NT, TW, COPIES)            \
-  do {                                   \
-    if (fa.ticket)                       \
-      MS_FR2(NT, TW, COPIES, true);      \
-    else                                 \
-      MS_FR2(NT, TW, COPIES, false);     \
+#define MS_FR(NT, TW, IT, COPIES)            \
+  do {                                       \
+    if (fa.ticket)                           \
+      MS_FR2(NT, TW, IT, COPIES, true);      \
+    else                                     \
+      MS_FR2(NT, TW, IT, COPIES, false);     \
   } while (0)
   if (f.tw == 64)
-    MS_FR(256, 64, ms::kSmallCopies);
+    MS_FR(256, 64, 8, ms::kSmallCopies);
   else if (f.tw == 256)
-    MS_FR(256, 256, 1);
+    MS_FR(256, 256, 4, 1);
   else
-    MS_FR(512, 2048, 1);
+    MS_FR(512, 2048, 4, 1);
 #undef MS_FR
 #undef MS_FR2
 }
@@ -1423,7 +1435,7 @@ int enqueue_step(massive_ctx* c, const int32_t* seeds, int32_t n0, massive_batch
       fa.sz = sz;
       fa.hop = k;
       fa.flags = c->d_tile_flags;
-      fa.ticket = scan_ticket(c, kFrontierScan, old_tiles + bit_tiles, fs.nt);
+      fa.ticket = scan_ticket(c, kFrontierScan, old_tiles + bit_tiles, fs.nt * 8 / ms::frontier_waves(fs.items));
       fa.old_tiles = old_tiles;
       fa.n_bound = nprev;
       fa.nodes = io->nodes;

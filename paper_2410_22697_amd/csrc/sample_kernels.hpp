@@ -882,11 +882,9 @@ __global__ __launch_bounds__(kSampleWaves* MS_WAVE) void k_sample_blocks(SampleA
 // rows in a launch of their own; 6.5-7.9 us for both here. Of a launch on a
 // small frontier (6.2 us) most is the chain of dependent steps: loads,
 // look-back, loads.
-// Rows in flight per thread. Four, as a launch then holds its share of the chip
-// at 64 registers (see scan_takes_tickets), and as fast as eight at 112: us per
-// pass, eight -> four: eight look-ahead steps on 487K words 2778 -> 2762, five
-// on 3.4K words 389 -> 385, on 50K words 5344 -> 5340.
-constexpr int kFrItems = 4;
+// Waves per SIMD that the kernel's registers leave room for, by its rows per
+// thread (kFrItems).
+constexpr int frontier_waves(int items) { return items > 4 ? 4 : 8; }
 
 struct FrontierArgs {
   uint32_t* bits;      // COPIES copies of the sampled-id bitmap
@@ -981,8 +979,8 @@ __device__ __forceinline__ FrSums fr_lookback(uint64_t* flags, int64_t b, uint32
   return x;
 }
 
-template <int NT, int TW, bool LAST, int COPIES, bool TICKETS>
-__global__ __launch_bounds__(NT, 8) void k_frontier(FrontierArgs a) {
+template <int NT, int TW, int kFrItems, bool LAST, int COPIES, bool TICKETS>
+__global__ __launch_bounds__(NT, frontier_waves(kFrItems)) void k_frontier(FrontierArgs a) {
   constexpr int kFrNT = NT, kFrWaves = NT / MS_WAVE, kFrChunk = NT * kFrItems;
   constexpr int WPT = TW > NT ? TW / NT : 1;  // words per thread (of the first TW / WPT threads)
   static_assert(WPT == 1 || (WPT == 4 && COPIES == 1), "one word or one 16-byte vector");

@@ -23,8 +23,7 @@ import random
 
 import pytest
 
-ITEMS = 4
-SHAPES = [(256, 64, 8), (256, 256, 1), (512, 2048, 1)]  # threads, words per tile, bitmap copies
+SHAPES = [(256, 64, 8, 8), (256, 256, 4, 1), (512, 2048, 4, 1)]  # threads, words per tile, items, bitmap copies
 
 
 def popcount(x):
@@ -32,8 +31,8 @@ def popcount(x):
 
 
 def frontier_scan(shape, F, seen, pos_of, bits, L, last, deg, fo, bptr, rnd):
-    NT, TW, copies = shape
-    W, chunk = len(seen), NT * ITEMS
+    NT, TW, items_, copies = shape
+    W, chunk = len(seen), NT * items_
     wpt = max(1, TW // NT)
     n_prev = len(F)
     old_tiles = 0 if last else -(-n_prev // chunk)
@@ -109,11 +108,11 @@ def run_hops(shape, R, L, density, hops, seed):
     for i, v in enumerate(F):  # the seeds' launch
         seen[v >> 5] |= 1 << (v & 31)
         pos_of[v] = i
-    bits = [[0] * W for _ in range(shape[2])]
+    bits = [[0] * W for _ in range(shape[3])]
     for hop in range(1, hops + 1):
         sampled = [rnd.randrange(R) for _ in range(int(R * density))] + F[:3]  # repeats and ids already in F
         for u in sampled:
-            bits[rnd.randrange(shape[2])][u >> 5] |= 1 << (u & 31)
+            bits[rnd.randrange(shape[3])][u >> 5] |= 1 << (u & 31)
         bptr, fo = [], rnd.randint(1, 9)
         newF, local = frontier_scan(shape, F, seen, pos_of, bits, L, hop == hops, deg, fo, bptr, rnd)
         want = sorted(set(sampled) - set(F))
@@ -140,9 +139,9 @@ def test_new_nodes_rows_and_offsets(shape, R, density, hops):
 
 def test_tiles_of_several_chunks():
     # 2048 words nearly all set: 32 chunks of a tile; and two tiles
-    run_hops((512, 2048, 1), 2048 * 32 + 77, 40000, 1.5, 1, 5)
+    run_hops(SHAPES[2], 2048 * 32 + 77, 40000, 1.5, 1, 5)
     # more old rows than a tile of them holds
-    run_hops((256, 64, 8), 5000, 4000, 1.0, 3, 6)
+    run_hops(SHAPES[0], 5000, 4000, 1.0, 3, 6)
 
 
 def test_planted_mistake_fails():
